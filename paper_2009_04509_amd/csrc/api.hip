@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "rows.h"
 
 using namespace pointid;
 
@@ -340,18 +341,15 @@ class EndsCall {
   bool on_;
 };
 
-// Pre-cut fp32 batches up to this size are rounded to 16 bits inside the
-// fused kernel (measured crossover: about 4,096 patches).
-constexpr int64_t kInKernelCast = 4096;
-
 // Scratch bytes of one call: 16-bit or fp32 patches (when the call makes
 // them) and the FC1 split-K partials.
+size_t patch_bytes(int precision, int64_t n) {
+  return (precision == POINTID_FP32 ? 4 : 2) * (size_t)n * kPatchPix;
+}
 size_t scratch_bytes(int precision, int64_t n, bool makes_patches) {
-  const bool half = precision != POINTID_FP32;
-  size_t b = 0;
-  if (makes_patches) b += pad256((half ? 2 : 4) * (size_t)n * kPatchPix);
+  size_t b = makes_patches ? pad256(patch_bytes(precision, n)) : 0;
   const int S = precision == POINTID_FP8 ? conv_fc1_8_splits()
-                : half ? conv_fc1_16_splits() : conv_fc1_f32_splits();
+                : precision != POINTID_FP32 ? conv_fc1_16_splits() : conv_fc1_f32_splits();
   b += pad256(sizeof(float) * (size_t)S * n * kFc1Out);
   return b;
 }
@@ -380,28 +378,16 @@ int run_network_fp32(pointid_handle h, const float* patches, int64_t n, float* s
   return POINTID_OK;
 }
 
-// Element type of the patches a handle's network reads: 8-bit handles run
-// their conv on fp16 patches.
-int patch_dtype(int precision) { return precision == POINTID_FP8 ? POINTID_FP16 : precision; }
-
-// 16-bit and 8-bit handles: patches (bf16 or fp16 [n][2304], or fp32 when
-// f32_in, rounded by the fused 16-bit kernel) -> scores.
-int run_network_16(pointid_handle h, const void* patches, bool f32_in, int64_t n, float* scores,
-                   hipStream_t stream, Workspace& ws, const RequestTable* reqs = nullptr) {
-  const bool fp8 = h->precision == POINTID_FP8;
-  const int S = fp8 ? conv_fc1_8_splits() : conv_fc1_16_splits();
+// 8-bit handles: fp16 patches [n][2304] -> scores.
+int run_network_8(pointid_handle h, const uint16_t* patches, int64_t n, float* scores,
+                  hipStream_t stream, Workspace& ws, const RequestTable* reqs = nullptr) {
+  const int S = conv_fc1_8_splits();
   float* part = nullptr;
   hipError_t e = ws.get(sizeof(float) * (size_t)S * n * kFc1Out, (void**)&part);
   if (e != hipSuccess) return hip_fail(e, "workspace (FC1 partials)");
-  if (fp8 && f32_in) return fail(POINTID_EUNSUPPORTED, "8-bit handles read 16-bit patches");
-  if (fp8) {
+  {
     KernelTimer kt("conv_fc1_8", stream);
-    e = launch_conv_fc1_8(static_cast<const uint16_t*>(patches), n, 0, n, h->w.fc1_frag8,
-                          h->w.conv_frag, part, stream);
-  } else {
-    KernelTimer kt("conv_fc1_16", stream);
-    e = launch_conv_fc1_16(h->precision == POINTID_FP16, patches, f32_in, n, 0, n, h->w.fc1_frag,
-                           h->w.conv_frag, part, stream);
+    e = launch_conv_fc1_8(patches, n, 0, n, h->w.fc1_frag8, h->w.conv_frag, part, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "conv_fc1 launch");
   {
@@ -415,8 +401,88 @@ int run_network_16(pointid_handle h, const void* patches, bool f32_in, int64_t n
   return POINTID_OK;
 }
 
-// The hit paths: gather, then the network.  Scratch comes from the handle's
-// pool, or, when `fixed` is given, from that buffer (already sized).
+// 16-bit handles: patches or hits -> scores.
+int run_network_16(pointid_handle h, const RowInput& in, int64_t n, float* scores, int cus,
+                   hipStream_t stream, Workspace& ws, const RequestTable* reqs = nullptr) {
+  const int S = conv_fc1_16_splits();
+  hipError_t e;
+  float* part = nullptr;
+  e = ws.get(sizeof(float) * (size_t)S * n * kFc1Out, (void**)&part);
+  if (e != hipSuccess) return hip_fail(e, "workspace (FC1 partials)");
+  {
+    KernelTimer kt("conv_fc1_16", stream);
+    e = launch_conv_fc1_16(h->precision == POINTID_FP16, in, n, h->w.fc1_frag, h->w.conv_frag, part,
+                           cus, stream);
+  }
+  if (e != hipSuccess) return hip_fail(e, "conv_fc1 launch");
+  {
+    KernelTimer kt("tail", stream);
+    EndsCall end(ws);
+    e = reqs ? launch_tail_requests(part, S, h->w, *reqs, stream)
+             : launch_tail(part, S, n, h->w, scores, stream);
+    end.launched(e);
+  }
+  if (e != hipSuccess) return hip_fail(e, "tail launch");
+  return POINTID_OK;
+}
+
+// An empty request table (unused starts past every patch index).
+void clear_requests(RequestTable* t) {
+  std::memset(t, 0, sizeof(*t));
+  for (int64_t& s : t->start) s = INT64_MAX;
+  t->start[0] = 0;
+}
+void add_request(RequestTable* t, const int32_t* hits, int64_t n, int32_t plane, float* scores) {
+  t->hits[t->n] = hits;
+  t->scores[t->n] = scores;
+  t->plane[t->n] = plane < 0 ? -1 : plane;
+  t->start[t->n + 1] = t->start[t->n] + n;
+  ++t->n;
+}
+
+// The hits of `reqs` -> scores (of one array, or into each request's output).
+// Scratch comes from `ws`.
+int classify_table(pointid_handle h, const PlaneTable& planes, const RequestTable& reqs,
+                   int tick_div, float* scores, hipStream_t stream, Workspace& ws) {
+  const int64_t n = reqs.start[reqs.n];
+  const RequestTable* out = scores ? nullptr : &reqs;
+  hipError_t e = ws.reserve(scratch_bytes(h->precision, n, true));
+  if (e != hipSuccess) return hip_fail(e, "scratch buffer");
+  RowInput in;
+  in.planes = &planes;
+  in.reqs = &reqs;
+  in.div = tick_div;
+  const bool fp8 = h->precision == POINTID_FP8, half = !fp8 && h->precision != POINTID_FP32;
+  int cus = 0;
+  e = device_cus(&cus);
+  if (e != hipSuccess) return hip_fail(e, "device attribute");
+  // batches that fill at most one round of thin tiles: the fused kernel takes
+  // the hits itself, which saves the gather's launch (128 hits, fp16: 27.3 ->
+  // 26.0 us per call with the same fused kernel)
+  if (half && conv_fc1_16_thin_tile(n, cus))
+    return run_network_16(h, in, n, scores, cus, stream, ws, out);
+  void* patches = nullptr;
+  e = ws.get(patch_bytes(h->precision, n), &patches);
+  if (e != hipSuccess) return hip_fail(e, "workspace (patches)");
+  {
+    KernelTimer kt("gather", stream);
+    const int dt = fp8 ? POINTID_FP16 : h->precision;
+    e = scores ? launch_gather(planes, reqs.hits[0], reqs.plane[0] < 0 ? 3 : 2, n, patches, dt, stream,
+                               tick_div)
+               : launch_gather_requests(planes, reqs, patches, dt, stream);
+  }
+  if (e != hipSuccess) return hip_fail(e, "gather launch");
+  if (half) {
+    in.patches16 = static_cast<const uint16_t*>(patches);
+    return run_network_16(h, in, n, scores, cus, stream, ws, out);
+  }
+  if (fp8) return run_network_8(h, static_cast<const uint16_t*>(patches), n, scores, stream, ws, out);
+  return run_network_fp32(h, static_cast<const float*>(patches), n, scores, stream, ws, out);
+}
+
+// One array of hits (stride 2: (wire, tick) on plane 0; 3: (plane, wire,
+// tick)).  Scratch comes from the handle's pool, or, when `fixed` is given,
+// from that buffer (already sized).
 int classify_hits(pointid_handle h, const PlaneTable& planes, const int32_t* hits,
                   int stride, int64_t n, float* scores, void* stream_, int tick_div = 1,
                   Workspace* fixed = nullptr) {
@@ -424,20 +490,10 @@ int classify_hits(pointid_handle h, const PlaneTable& planes, const int32_t* hit
   DeviceScope dev(h->device);
   if (dev.error() != hipSuccess) return hip_fail(dev.error(), "hipSetDevice");
   Workspace pooled(h->scratch, stream);
-  Workspace& ws = fixed ? *fixed : pooled;
-  hipError_t e = ws.reserve(scratch_bytes(h->precision, n, true));
-  if (e != hipSuccess) return hip_fail(e, "scratch buffer");
-  const bool half = h->precision != POINTID_FP32;
-  void* patches = nullptr;
-  e = ws.get((half ? 2 : 4) * (size_t)n * kPatchPix, &patches);
-  if (e != hipSuccess) return hip_fail(e, "workspace (patches)");
-  {
-    KernelTimer kt("gather", stream);
-    e = launch_gather(planes, hits, stride, n, patches, patch_dtype(h->precision), stream, tick_div);
-  }
-  if (e != hipSuccess) return hip_fail(e, "gather launch");
-  if (half) return run_network_16(h, patches, false, n, scores, stream, ws);
-  return run_network_fp32(h, static_cast<const float*>(patches), n, scores, stream, ws);
+  RequestTable one;
+  clear_requests(&one);
+  add_request(&one, hits, n, stride == 2 ? 0 : -1, scores);
+  return classify_table(h, planes, one, tick_div, scores, stream, fixed ? *fixed : pooled);
 }
 
 int check_planes(const pointid_plane* planes, int32_t n_planes, PlaneTable* t) {
@@ -458,26 +514,13 @@ int check_planes(const pointid_plane* planes, int32_t n_planes, PlaneTable* t) {
 }
 
 // One batch of at most kMaxRequests non-empty requests: their hits are
-// gathered into one patch buffer and classified together; the tail writes
-// every patch's scores into its request's output.
+// classified together; the tail writes every patch's scores into its
+// request's output.
 int classify_request_batch(pointid_handle h, const PlaneTable& planes, const RequestTable& reqs,
                            hipStream_t stream) {
-  const int64_t n = reqs.start[reqs.n];
-  if (n == 0) return POINTID_OK;
+  if (reqs.start[reqs.n] == 0) return POINTID_OK;
   Workspace ws(h->scratch, stream);
-  hipError_t e = ws.reserve(scratch_bytes(h->precision, n, true));
-  if (e != hipSuccess) return hip_fail(e, "scratch buffer");
-  const bool half = h->precision != POINTID_FP32;
-  void* patches = nullptr;
-  e = ws.get((half ? 2 : 4) * (size_t)n * kPatchPix, &patches);
-  if (e != hipSuccess) return hip_fail(e, "workspace (patches)");
-  {
-    KernelTimer kt("gather", stream);
-    e = launch_gather_requests(planes, reqs, patches, patch_dtype(h->precision), stream);
-  }
-  if (e != hipSuccess) return hip_fail(e, "gather launch");
-  if (half) return run_network_16(h, patches, false, n, nullptr, stream, ws, &reqs);
-  return run_network_fp32(h, static_cast<const float*>(patches), n, nullptr, stream, ws, &reqs);
+  return classify_table(h, planes, reqs, 1, nullptr, stream, ws);
 }
 
 // ---- scratch for pointid_classify_planes_noalloc: a fixed device array,
@@ -888,7 +931,7 @@ int pointid_classify_requests(pointid_handle h, const pointid_plane* planes, int
   DeviceScope dev(h->device);
   if (dev.error() != hipSuccess) return hip_fail(dev.error(), "hipSetDevice");
   RequestTable tab;
-  std::memset(&tab, 0, sizeof(tab));
+  clear_requests(&tab);
   for (int32_t r = 0; r <= n_requests; ++r) {
     // flush a full table, and the last one
     if (r == n_requests || tab.n == kMaxRequests) {
@@ -896,16 +939,12 @@ int pointid_classify_requests(pointid_handle h, const pointid_plane* planes, int
         rc = classify_request_batch(h, t, tab, stream);
         if (rc != POINTID_OK) return rc;
       }
-      std::memset(&tab, 0, sizeof(tab));
+      clear_requests(&tab);
       if (r == n_requests) break;
     }
     const pointid_request& q = requests[r];
     if (q.n_hits == 0) continue;
-    tab.hits[tab.n] = q.hits;
-    tab.scores[tab.n] = q.scores;
-    tab.plane[tab.n] = q.plane < 0 ? -1 : q.plane;
-    tab.start[tab.n + 1] = tab.start[tab.n] + q.n_hits;
-    ++tab.n;
+    add_request(&tab, q.hits, q.n_hits, q.plane, q.scores);
   }
   return POINTID_OK;
 }
@@ -921,26 +960,28 @@ int pointid_classify_patches(pointid_handle h, const float* patches, int64_t n,
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   DeviceScope dev(h->device);
   if (dev.error() != hipSuccess) return hip_fail(dev.error(), "hipSetDevice");
-  // 16-bit handles: up to kInKernelCast patches the fused kernel rounds the
-  // fp32 rows itself (one launch fewer, which is what a small batch pays for);
-  // above, a separate cast writes 16-bit patches, whose rows the fused kernel
-  // then reads at half the bytes
-  const bool half = h->precision != POINTID_FP32;
-  const bool cast = half && (n > kInKernelCast || h->precision == POINTID_FP8);
+  const bool fp8 = h->precision == POINTID_FP8;
   Workspace ws(h->scratch, stream);
-  hipError_t e = ws.reserve(scratch_bytes(h->precision, n, cast));
+  hipError_t e = ws.reserve(scratch_bytes(h->precision, n, fp8));
   if (e != hipSuccess) return hip_fail(e, "scratch buffer");
-  if (!half) return run_network_fp32(h, patches, n, scores, stream, ws);
-  if (!cast) return run_network_16(h, patches, true, n, scores, stream, ws);
+  if (h->precision == POINTID_FP32) return run_network_fp32(h, patches, n, scores, stream, ws);
+  if (!fp8) {
+    RowInput in;
+    in.patches = patches;
+    int cus = 0;
+    e = device_cus(&cus);
+    if (e != hipSuccess) return hip_fail(e, "device attribute");
+    return run_network_16(h, in, n, scores, cus, stream, ws);
+  }
   uint16_t* pb = nullptr;
-  e = ws.get(2 * (size_t)n * kPatchPix, (void**)&pb);
+  e = ws.get(patch_bytes(h->precision, n), (void**)&pb);
   if (e != hipSuccess) return hip_fail(e, "workspace (16-bit patches)");
   {
     KernelTimer kt("patches_to_16", stream);
-    e = launch_patches_to_16(patch_dtype(h->precision) == POINTID_FP16, patches, n, pb, stream);
+    e = launch_patches_to_16(true, patches, n, pb, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "16-bit cast launch");
-  return run_network_16(h, pb, false, n, scores, stream, ws);
+  return run_network_8(h, pb, n, scores, stream, ws);
 }
 
 int pointid_gather(const float* image, int32_t n_wires, int32_t n_ticks,

@@ -8,10 +8,11 @@
 //
 // Work split.  A block owns 96 patches (64 in the blocks of the last rounds of
 // some batches: see conv_fc1_16_tiles; small batches run the thin tiles
-// further below, with the same sums) and one of kSplits contiguous ranges of
-// map positions (split-K); blockIdx % 8 selects the range, so every block on one
-// XCD reads the same 1/8 of the FC1 weights and that slice (2.97 MB) stays in
-// the XCD's 4 MB L2.  Positions are taken in pairs (x, x+1) with x even: the
+// further below, with the same sums) and one of kSplits16 contiguous ranges of
+// map positions (split-K), or 2 or 4 consecutive ones one after the other in
+// batches of whole rounds of such blocks; blockIdx % 8 selects the range, so the
+// blocks that run on one XCD stream the same weights (2.97 MB per range)
+// through its 4 MB L2 at the same time.  Positions are taken in pairs (x, x+1) with x even: the
 // 5x6 pixel window of a pair (30 values) fits one K=32 MFMA operand, shared by
 // both positions.  The block's 8 waves (2 per SIMD, so one wave's conversions
 // overlap the other's MFMAs) form 4 position groups x 2 output halves.  The two
@@ -41,6 +42,7 @@
 // written as fp32 partials [split][patch][128]; the tail kernel adds the splits.
 #include "internal.h"
 #include "op16.h"
+#include "rows.h"
 
 namespace pointid {
 namespace {
@@ -50,20 +52,24 @@ constexpr int kNHalves = 2;                   // output halves
 constexpr int kWaves = kKGroups * kNHalves;   // 8
 constexpr int kThreads = kWaves * 64;         // 512
 constexpr int kMT = 8 / kNHalves;             // 16-output tiles per wave
+constexpr int kSplits16 = 8;                  // position ranges (split-K), one per XCD
 constexpr int kPairsPerRow = kFm / 2;         // 22
 constexpr int kRing = 8;                      // patch-row ring slots
-// rows the first two steps of a split need: pairs P0 .. P0 + 2 kKGroups - 1 span
-// at most two map rows, plus the filter height
+// rows the first steps of a range need: their pairs span at most two map rows,
+// plus the filter height
 constexpr int kPrologueRows = 2 + 5 - 1;
 constexpr int kRP = 26;                       // LDS row pitch, dwords (24 used)
 constexpr int kBigTile = 96;                  // patches per block (most blocks)
 constexpr int kMidTile = 64;                  // patches per block (the last rounds, some batches)
 
+// First step (kKGroups pairs) of position range s, of 242 in all.
+__host__ __device__ constexpr int range_begin(int s) {
+  return (kPos / 2 / kKGroups) * s / kSplits16;
+}
+
 // Layout of a block of kBt patches.  LDS (dwords): ring | conv filter
-// fragments | swap buffers; the final reduction reuses it from the start.
-// A patch row (96 B) of each of the block's patches is kBt x 6 chunks of 16 B:
-// chunk c = tid for the first kRowMain threads, plus c = kThreads + tid for
-// the first kRowExtra threads (whole waves, so no lane diverges).
+// fragments | swap buffers; the reduction uses the swap buffers and the LDS
+// behind them.
 template <int kBt>
 struct Tile {
   static constexpr int kTiles = kBt / 16;                 // 16-patch MFMA tiles
@@ -73,93 +79,101 @@ struct Tile {
   static constexpr int kSwapOff = kConvOff + 6 * 64 * 4;
   static constexpr int kSwapWave = kOwn * 64 * 4;         // one wave's fragments
   static constexpr int kSwapBuf = kWaves * kSwapWave;     // one buffer
-  // the reduction: per output half, 3 tiles from the other groups per accumulator tile
-  static constexpr int kRed = kNHalves * kMT * kTiles * (kKGroups - 1) * 4 * 64;
-  static constexpr int kMain = kSwapOff + 2 * kSwapBuf;
-  static constexpr int kLdsDwords = (kMain > kRed) ? kMain : kRed;
-  static constexpr int kRowChunks = kBt * 6;
-  static constexpr int kRowMain = kRowChunks < kThreads ? kRowChunks : kThreads;
-  static constexpr int kRowExtra = kRowChunks - kRowMain;
+  // the reduction: kRedTiles accumulator tiles per position group and pass, of
+  // each one from each of the other three groups, per output half
+  static constexpr int kRedTiles = kMT * kTiles / kKGroups / 2;
+  static constexpr int kRed = kNHalves * kKGroups * kRedTiles * (kKGroups - 1) * 64 * 4;
+  static constexpr int kLdsDwords = kSwapOff + (2 * kSwapBuf > kRed ? 2 * kSwapBuf : kRed);
+  static_assert(kLdsDwords >= 2 * kRed, "one pass");
   static_assert(kTiles % kNHalves == 0 && kOwn <= 3, "whole tiles per output half");
-  static_assert(kRowMain % 64 == 0 && kRowExtra % 64 == 0 && kRowExtra <= kThreads,
-                "row chunking in whole waves");
 };
 static_assert(Tile<kBigTile>::kLdsDwords >= Tile<kMidTile>::kLdsDwords, "LDS sized by the big tile");
+static_assert(Tile<kBigTile>::kLdsDwords * 4 <= 160 * 1024, "LDS of one block");
 
-// Patches past the end of the batch are read from the last patch instead:
-// their results are never stored.  `In` is the patches' element type: 16-bit
-// bit patterns (from the gather or the cast), or fp32 pre-cut patches rounded
-// here, on the way into LDS, with the same round-to-nearest-even as the cast.
-template <int kBt, bool kFp16, class In>
-__device__ __forceinline__ uint4 row_chunk_load(const In* __restrict__ patches, int64_t n,
-                                                int64_t p_base, int r, int c) {
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  const int p = c / 6, h = c - (c / 6) * 6;
-  int64_t gp = p_base + p;
-  gp = gp < n ? gp : n - 1;
-  // streamed once per block: non-temporal, so it does not push the block's FC1
-  // weight slice out of L2
-  const In* src = patches + gp * kPatchPix + r * kPatch + h * 8;
-  if constexpr (sizeof(In) == 2) {
-    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src)));
-  } else {
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    const f32x4 a = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src));
-    const f32x4 b = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src) + 1);
-    using Op = Op16<kFp16>;
-    return make_uint4(Op::pack(a[0], a[1]), Op::pack(a[2], a[3]), Op::pack(b[0], b[1]),
-                      Op::pack(b[2], b[3]));
+// A patch row of each of a block's kBt patches, in chunks of 16 bytes of `In`
+// (16-bit patches from the gather, or fp32 pre-cut patches): chunk
+// c = tid + k * kThreads, the last k for the first threads only (whole waves,
+// so no lane diverges).  Patches past the end of the batch are read from the
+// last patch instead: their results are never stored.  fp32 pixels stay as
+// they are in registers and are rounded (nearest even) on their way into LDS,
+// so that nothing waits for their loads in between.  (Rounding them in the
+// kernel saves a pass that writes 16-bit patches: 31 of 429 us at 16,384
+// patches.  Reading the rows of hits from the plane images here, without the
+// gather's pass, gained nothing over an event: the conv's share of the power
+// limit went to eight times the image reads.)
+template <int kBt, class In>
+struct Rows {
+  static constexpr int kPix = 16 / (int)sizeof(In);
+  static constexpr int kPerRow = kPatch / kPix;
+  static constexpr int kAll = kBt * kPerRow;
+  static constexpr int kPer = (kAll + kThreads - 1) / kThreads;      // chunks per thread
+  static_assert(kAll % 64 == 0, "row chunks in whole waves");
+  uint4 v[kPer];
+
+  // streamed once per block: non-temporal, so the rows do not push the FC1
+  // weights out of L2
+  __device__ __forceinline__ void load(const In* __restrict__ patches, int64_t n, int64_t p_base, int r) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int c = threadIdx.x + k * kThreads;
+      if (c < kAll) {
+        const int p = c / kPerRow, h = c - (c / kPerRow) * kPerRow;
+        int64_t gp = p_base + p;
+        gp = gp < n ? gp : n - 1;
+        const In* src = patches + gp * kPatchPix + r * kPatch + h * kPix;
+        v[k] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src)));
+      }
+    }
   }
-}
-
-template <int kBt>
-__device__ __forceinline__ void row_chunk_store(uint32_t* lds, int r, int c, const uint4& v) {
-  const int p = c / 6, h = c - (c / 6) * 6;
-  uint32_t* d = lds + (r & (kRing - 1)) * Tile<kBt>::kSlot + p * kRP + h * 4;
-  *reinterpret_cast<uint2*>(d) = make_uint2(v.x, v.y);
-  *reinterpret_cast<uint2*>(d + 2) = make_uint2(v.z, v.w);
-}
-
-// `main` and `extra`: wave-uniform, whether this thread has a first / second chunk
-template <int kBt, bool kFp16, class In>
-__device__ __forceinline__ void row_load(const In* __restrict__ patches, int64_t n,
-                                         int64_t p_base, int r, bool main, bool extra,
-                                         uint4 (&v)[2]) {
-  if (main) v[0] = row_chunk_load<kBt, kFp16, In>(patches, n, p_base, r, threadIdx.x);
-  if (extra) v[1] = row_chunk_load<kBt, kFp16, In>(patches, n, p_base, r, threadIdx.x + kThreads);
-}
-
-template <int kBt>
-__device__ __forceinline__ void row_store(uint32_t* lds, int r, bool main, bool extra,
-                                          const uint4 (&v)[2]) {
-  if (main) row_chunk_store<kBt>(lds, r, threadIdx.x, v[0]);
-  if (extra) row_chunk_store<kBt>(lds, r, threadIdx.x + kThreads, v[1]);
-}
+  template <bool kFp16>
+  __device__ __forceinline__ void store(uint32_t* lds, int r) const {
+    using Op = Op16<kFp16>;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int c = threadIdx.x + k * kThreads;
+      if (c < kAll) {
+        const int p = c / kPerRow, h = c - (c / kPerRow) * kPerRow;
+        uint32_t* d = lds + (r & (kRing - 1)) * Tile<kBt>::kSlot + p * kRP + h * (kPix / 2);
+        if constexpr (sizeof(In) == 2) {
+          *reinterpret_cast<uint2*>(d) = make_uint2(v[k].x, v[k].y);
+          *reinterpret_cast<uint2*>(d + 2) = make_uint2(v[k].z, v[k].w);
+        } else {
+          *reinterpret_cast<uint2*>(d) =
+              make_uint2(Op::pack(__uint_as_float(v[k].x), __uint_as_float(v[k].y)),
+                         Op::pack(__uint_as_float(v[k].z), __uint_as_float(v[k].w)));
+        }
+      }
+    }
+  }
+};
 
 // One block: patches p_base .. p_base + kBt - 1 (clamped to the batch) and
-// position range `split`.
-template <bool kFp16, int kSplits, int kBt, class In>
+// `ranges` consecutive position ranges from `split0`.  The pairs of a range
+// follow those of the range before it, so the patch rows in the ring run on
+// over their boundary.  (kMulti: more than one; a kernel of its own for one,
+// because the loop around the ranges costs registers and a pass.)
+template <bool kFp16, int kBt, class In, bool kMulti>
 __device__ __forceinline__ void conv_fc1_block(
-    uint32_t* lds, int split, int64_t p_base,
-    const In* __restrict__ patches, int64_t n, const uint4* __restrict__ w1p,
-    const uint4* __restrict__ convp, float* __restrict__ part, int64_t row0, int64_t n_total) {
+    uint32_t* lds, int split0, int ranges_, int64_t p_base, const In* __restrict__ patches, int64_t n,
+    const uint4* __restrict__ w1p, const uint4* __restrict__ convp, float* __restrict__ part) {
   using T = Tile<kBt>;
+  const int ranges = kMulti ? ranges_ : 1;
   constexpr int kTiles = T::kTiles, kOwn = T::kOwn, kSlot = T::kSlot;
+  constexpr int kSlots = kMT * kTiles;       // accumulator tiles of a wave
+  constexpr int kPer = kSlots / kKGroups;    // tiles a wave finishes
+  static_assert(kSlots % kKGroups == 0, "whole quarters");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = wave % kKGroups;            // position group
   const int nh = wave / kKGroups;            // output half; also the half of the tiles it convolves
   const int partner = kg + kKGroups * (1 - nh);
-  const bool rmain = wave < T::kRowMain / 64;   // wave-uniform
-  const bool extra = wave < T::kRowExtra / 64;
   const int col = lane & 15;                 // MFMA column (patch within tile) / row
   const int grp = lane >> 4;                 // MFMA K-slot group
-  // split boundaries on whole steps of kKGroups pairs: every wave runs `steps` pairs
-  constexpr int kGroups = kPos / 2 / kKGroups;          // 242
-  const int G0 = (kGroups * split) / kSplits;
-  const int steps = (kGroups * (split + 1)) / kSplits - G0;
-  const int P0 = kKGroups * G0;
+  // range boundaries on whole steps of kKGroups pairs: every wave runs as many pairs
+  const int P0 = kKGroups * range_begin(split0);
+  const int P_last = kKGroups * range_begin(split0 + ranges) - 1;
   using Op = Op16<kFp16>;
 
   // conv filter fragments [shift][channel tile] in LDS; a K-step reads two
@@ -169,50 +183,43 @@ __device__ __forceinline__ void conv_fc1_block(
   // swap buffers: [buffer][wave][own tile][lane] x 16 B
   uint4* swp = reinterpret_cast<uint4*>(lds + T::kSwapOff);
 
-  // this lane's 4 window dwords: slot pair f = 8*grp + 2d -> pixel (u, c)
-  int woff[4], wrow[4];
+  // this lane's 4 window dwords: slot pair f = 8*grp + 2d -> pixel (u, c), kept
+  // as u | c / 2 << 4 in byte d (registers are what bounds this kernel)
+  uint32_t wpix = 0;
 #pragma unroll
   for (int d = 0; d < 4; ++d) {
     int f = 8 * grp + 2 * d;
     if (f > 28) f = 28;                      // slots 30-31 are constants (masked below)
-    wrow[d] = f / 6;
-    woff[d] = (f % 6) / 2 + col * kRP + nh * kOwn * 16 * kRP;
+    wpix |= (uint32_t)((f / 6) | (f % 6) / 2 << 4) << (8 * d);
   }
+  const int wcol = col * kRP + nh * kOwn * 16 * kRP;
   const bool const_slot = (grp == 3);
 
-  // accumulators for the wave's own conv tiles (block tiles nh*kOwn + i) and
-  // for the partner's (tiles (1-nh)*kOwn + i); indexed statically only, so
-  // they stay in registers
-  floatx4 acc_own[kMT][kOwn], acc_oth[kMT][kOwn];
-#pragma unroll
-  for (int m = 0; m < kMT; ++m)
-#pragma unroll
-    for (int i = 0; i < kOwn; ++i) {
-      acc_own[m][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
-      acc_oth[m][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
-    }
-
-  // ---- patch rows.  The ring is filled two steps ahead of the step being
-  // computed, so the window of step s+1 can be read during step s.
+  // ---- patch rows.  The window of step s+1 is read during step s, and a new
+  // row's loads are issued a step before it goes into the ring: the ring is
+  // filled kAhead steps ahead of the step being computed.
+  constexpr int kAhead = 3;
+  static_assert(kKGroups * kAhead + kKGroups - 1 < kPairsPerRow && 1 + kK < kRing,
+                "rows up to 1 + 4 past a step's first");
   auto top_row = [&](int step) {             // highest input row a step needs
     int pl = P0 + kKGroups * step + kKGroups - 1;
-    if (pl > kPos / 2 - 1) pl = kPos / 2 - 1;
+    if (pl > P_last) pl = P_last;
     return pl / kPairsPerRow + kK - 1;
   };
   // all rows in flight at once (at most kPrologueRows), then into the ring
-  int loaded_hi = top_row(1);
+  int loaded_hi = top_row(kAhead - 1);
   {
     const int r0 = P0 / kPairsPerRow;
-    uint4 v[kPrologueRows][2], fv;
+    Rows<kBt, In> v[kPrologueRows];
+    uint4 fv;
     if (tid < 6 * 64) fv = convp[tid];
 #pragma unroll
     for (int j = 0; j < kPrologueRows; ++j)
-      if (r0 + j <= loaded_hi)
-        row_load<kBt, kFp16, In>(patches, n, p_base, r0 + j, rmain, extra, v[j]);
+      if (r0 + j <= loaded_hi) v[j].load(patches, n, p_base, r0 + j);
     if (tid < 6 * 64) cwl[tid] = fv;
 #pragma unroll
     for (int j = 0; j < kPrologueRows; ++j)
-      if (r0 + j <= loaded_hi) row_store<kBt>(lds, r0 + j, rmain, extra, v[j]);
+      if (r0 + j <= loaded_hi) v[j].template store<kFp16>(lds, r0 + j);
   }
   __syncthreads();
 
@@ -222,8 +229,13 @@ __device__ __forceinline__ void conv_fc1_block(
     const int y = P / kPairsPerRow;
     const int xh = P - y * kPairsPerRow;     // x / 2
     int base[4];
+    uint32_t wp = wpix;
+    asm volatile("" : "+v"(wp));            // unpacked here, not once for the loop
 #pragma unroll
-    for (int d = 0; d < 4; ++d) base[d] = ((y + wrow[d]) & (kRing - 1)) * kSlot + woff[d] + xh;
+    for (int d = 0; d < 4; ++d) {
+      const int u = (wp >> (8 * d)) & 15, c2 = (wp >> (8 * d + 4)) & 15;
+      base[d] = ((y + u) & (kRing - 1)) * kSlot + wcol + c2 + xh;
+    }
 #pragma unroll
     for (int i = 0; i < kOwn; ++i) {
       const int o = i * 16 * kRP;
@@ -258,32 +270,51 @@ __device__ __forceinline__ void conv_fc1_block(
   };
 
   // FC1 fragments of this wave's outputs through a buffer resource: the
-  // fragment base is a scalar offset and the output tiles are immediate
-  // offsets, so the loads need no per-lane address arithmetic; reads past the
-  // end return 0.
+  // fragment's place is a scalar offset, so the loads need one per-lane
+  // register and no per-lane arithmetic; reads past the end return 0.
   const __amdgpu_buffer_rsrc_t w1r = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint4*>(w1p), (short)0, (int)(kFc1Frags * 16), 0x00020000);
-  const int voff = lane * 16 + nh * kMT * 1024;
+  const int voff = lane * 16;
   auto load_one = [&](int P, int q, int m) {
-    return __builtin_bit_cast(
-        uint4, __builtin_amdgcn_raw_buffer_load_b128(w1r, voff + m * 1024, (P * 3 + q) * 8 * 1024, 0));
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                         w1r, voff, ((P * 3 + q) * 8 + nh * kMT + m) * 1024, 0));
   };
+
+  int step = 0;                              // of the block's first range on
+  bool row_pending = false;                  // row loaded_hi + 1 is on its way, in rv
+  Rows<kBt, In> rv;
+#pragma unroll
+  for (int k = 0; k < Rows<kBt, In>::kPer; ++k) rv.v[k] = make_uint4(0, 0, 0, 0);
+#pragma unroll 1
+  for (int split = split0; split < split0 + ranges; ++split) {
+  const int step_end = range_begin(split + 1) - range_begin(split0);
+  // accumulators for the wave's own conv tiles (block tiles nh*kOwn + i) and
+  // for the partner's (tiles (1-nh)*kOwn + i); indexed statically only, so
+  // they stay in registers
+  floatx4 acc_own[kMT][kOwn], acc_oth[kMT][kOwn];
+#pragma unroll
+  for (int m = 0; m < kMT; ++m)
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+      acc_own[m][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+      acc_oth[m][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    }
 
   // ---- software pipeline.  Entering a K-step, this wave's own conv fragments
   // are in registers and the partner's are in swap buffer `buf` (published by
   // the last barrier).  While the FC1 MFMAs run, the conv of the next K-step is
   // issued, converted and published in the other buffer.  The FC1 weights sit
-  // in a ring of 3 register sets, one per K-step of a pair (set q for K-step
-  // q), each loaded two K-steps before it is used.
+  // in 3 register sets, one per K-step of a pair (set q for K-step q), each
+  // fragment reloaded for the next pair as soon as its MFMAs have issued, two
+  // and a half K-steps before it is used.
   uint4 w[3][kMT], win[kOwn], own[kOwn];
-#pragma unroll
-  for (int m = 0; m < kMT; ++m) {
-    w[0][m] = load_one(P0 + kg, 0, m);
-    w[1][m] = load_one(P0 + kg, 1, m);
-  }
-  read_win_raw(P0 + kg, win);
-  fix_win(win);
   {
+    const int P = P0 + kKGroups * step + kg;
+#pragma unroll
+    for (int i = 0; i < 3 * kMT; ++i)        // in the loop's order, for exact wait counts
+      w[i / kMT][i % kMT] = load_one(P, i / kMT, i % kMT);
+    read_win_raw(P, win);
+    fix_win(win);
     uint4 fa, fb;
     read_filters(0, fa, fb);
     const floatx4 z = {0.f, 0.f, 0.f, 0.f};
@@ -296,29 +327,18 @@ __device__ __forceinline__ void conv_fc1_block(
   __syncthreads();
 
 #pragma unroll 1
-  for (int step = 0; step < steps; ++step) {
-    // the patch row two steps ahead (at most one per step; block-uniform)
-    uint4 rv[2];
-    const int want_hi = top_row(step + 2);
-    const bool new_row = want_hi > loaded_hi;
-    if (new_row) row_load<kBt, kFp16, In>(patches, n, p_base, want_hi, rmain, extra, rv);
-
+  for (; step < step_end; ++step) {
     const int P = P0 + kKGroups * step + kg;
     uint4 win_next[kOwn];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const int nq = (q + 1) % 3;            // the next K-step
-      const int fq = (q + 2) % 3;            // the K-step after it
-      const int fP = (q < 1) ? P : P + kKGroups;
       uint4 oth[kOwn], nxt[kOwn], fa, fb;
       floatx4 ca[kOwn], cb[kOwn];
       const floatx4 z = {0.f, 0.f, 0.f, 0.f};
       // One K-step in ten groups of 3 MFMAs, the other work spread between
       // them: the two waves sharing a SIMD run the same sequence at about the
-      // same time, so neither may bunch its VALU or LDS work.  The weight
-      // register set q is used by groups 0-1, 4-5 (own tiles) and 6-9
-      // (partner's tiles); set fq, last used in the previous K-step, is
-      // reloaded for two K-steps ahead (past the end of the weights this reads 0).
+      // same time, so neither may bunch its VALU or LDS work.
       auto own_group = [&](int m) {
 #pragma unroll
         for (int i = 0; i < kOwn; ++i) acc_own[m][i] = Op::mfma(w[q][m], own[i], acc_own[m][i]);
@@ -332,10 +352,8 @@ __device__ __forceinline__ void conv_fc1_block(
       read_filters(nq, fa, fb);
       get_swap(buf, oth);
       own_group(0);
-      w[fq][0] = load_one(fP, fq, 0);
       __builtin_amdgcn_sched_barrier(0);
       own_group(1);
-      w[fq][1] = load_one(fP, fq, 1);
       __builtin_amdgcn_sched_barrier(0);
       // g2, g3: conv of the next K-step
 #pragma unroll
@@ -345,39 +363,47 @@ __device__ __forceinline__ void conv_fc1_block(
       for (int i = 0; i < kOwn; ++i) cb[i] = Op::mfma(fb, (q == 2) ? win_next[i] : win[i], z);
       __builtin_amdgcn_sched_barrier(0);
       own_group(2);
-      w[fq][2] = load_one(fP, fq, 2);
       if (q == 1) read_win_raw(P + kKGroups, win_next);
       __builtin_amdgcn_sched_barrier(0);
       own_group(3);
-      w[fq][3] = load_one(fP, fq, 3);
       nxt[0] = convert1(ca[0], cb[0]);
       __builtin_amdgcn_sched_barrier(0);
       oth_group(0);
+      w[q][0] = load_one(P + kKGroups, q, 0);
       if constexpr (kOwn > 1) nxt[1] = convert1(ca[1], cb[1]);
       put1(buf ^ 1, 0, nxt[0]);
       __builtin_amdgcn_sched_barrier(0);
       oth_group(1);
+      w[q][1] = load_one(P + kKGroups, q, 1);
       if constexpr (kOwn > 2) nxt[2] = convert1(ca[2], cb[2]);
       if constexpr (kOwn > 1) put1(buf ^ 1, 1, nxt[1]);
       if (q == 1) fix_win(win_next);
       __builtin_amdgcn_sched_barrier(0);
       oth_group(2);
+      w[q][2] = load_one(P + kKGroups, q, 2);
       if constexpr (kOwn > 2) put1(buf ^ 1, 2, nxt[2]);
       __builtin_amdgcn_sched_barrier(0);
       oth_group(3);
+      w[q][3] = load_one(P + kKGroups, q, 3);
       __builtin_amdgcn_sched_barrier(0);
+      if (q == 0) {
+        // Patch rows.  Loads return in order, and a row comes from further
+        // away than the weights: its loads follow a K-step's weight loads, the
+        // next weight loads come half a K-step later and are used two and a
+        // half K-steps after that, and the row goes into the ring three K-steps
+        // later, so that nothing waits for a row that takes less than 2 us.
+        // The slot it overwrites held a row below every row that any wave
+        // still reads; the barriers publish it before the step that first
+        // needs it.  Block-uniform conditions.
+        if (row_pending) rv.template store<kFp16>(lds, ++loaded_hi);
+        row_pending = top_row(step + kAhead) > loaded_hi;
+        if (row_pending) rv.load(patches, n, p_base, loaded_hi + 1);
+      }
 #pragma unroll
       for (int i = 0; i < kOwn; ++i) own[i] = nxt[i];
       if (q == 2) {
 #pragma unroll
         for (int i = 0; i < kOwn; ++i) win[i] = win_next[i];
-        // The slot a new row overwrites held a row below every row that any
-        // wave still reads; the barrier below publishes it before the step
-        // that first needs it (two steps later).
-        if (new_row) {
-          row_store<kBt>(lds, want_hi, rmain, extra, rv);
-          loaded_hi = want_hi;
-        }
       }
       buf ^= 1;
       // publishes the next K-step's swap fragments (and a new row); the
@@ -386,67 +412,116 @@ __device__ __forceinline__ void conv_fc1_block(
     }
   }
 
-  // ---- fixed-order reduction over position groups, per output half:
-  //      (g0 + g2) + (g1 + g3), finished by one wave per accumulator tile.
-  // The four waves of an output half hold the same tiles (they share the
-  // own/partner tile order); position group g finishes the g-th quarter of
-  // them, so after one barrier every wave adds and stores its own quarter.
-  // One 16 B accumulator tile per lane and access (conflict-free b128).
-  constexpr int kSlots = kMT * kTiles;         // accumulator tiles of a wave
-  constexpr int kPer = kSlots / kKGroups;      // tiles a wave finishes
-  static_assert(kSlots % kKGroups == 0, "whole quarters");
-  floatx4* red = reinterpret_cast<floatx4*>(lds);
-  // slot q of output half nh, written by the src-th of the other three groups
-  auto entry = [&](int q, int src) { return ((nh * kSlots + q) * (kKGroups - 1) + src) * 64 + lane; };
-  auto tile = [&](auto qc) -> floatx4& {
-    constexpr int q = decltype(qc)::value, m = q / kTiles, j = q % kTiles;
-    if constexpr (j < kOwn) return acc_own[m][j];
-    else return acc_oth[m][j - kOwn];
-  };
-  static_for<kSlots>([&](auto qc) {
-    constexpr int o = decltype(qc)::value / kPer;     // the group that finishes it
-    if (kg != o) red[entry(decltype(qc)::value, kg - (kg > o ? 1 : 0))] = tile(qc);
-  });
-  __syncthreads();
-
-  // tile q = m * kTiles + j: outputs 16(nh*kMT + m) + 4*grp + e for patch
-  // 16*(block tile) + col, the block tile nh*kOwn + j (own) or
-  // (1-nh)*kOwn + j - kOwn (partner's)
-  float* dst = part + ((int64_t)split * n_total + row0 + p_base) * kFc1Out;
-  static_for<kSlots>([&](auto qc) {
-    constexpr int q = decltype(qc)::value, o = q / kPer, m = q / kTiles, j = q % kTiles;
-    if (kg == o) {
-      floatx4 v[kKGroups];
+    // ---- fixed-order reduction over position groups, per output half:
+    //      (g0 + g2) + (g1 + g3), finished by one wave per accumulator tile.
+    // The four waves of an output half hold the same tiles (they share the
+    // own/partner tile order); position group g finishes the g-th quarter of
+    // them: with one range per block in one pass through the whole LDS, else
+    // half of the quarter in each of two passes through the swap buffers and
+    // the LDS behind them, so that the ring stays as it is for the next range.
+    // 16 B per lane and access (conflict-free b128).
+    auto tile = [&](auto qc) -> floatx4& {
+      constexpr int q = decltype(qc)::value, m = q / kTiles, j = q % kTiles;
+      if constexpr (j < kOwn) return acc_own[m][j];
+      else return acc_oth[m][j - kOwn];
+    };
+    // the lane index anew: addresses derived from it stay out of the K loop's registers
+    int rl = lane;
+    asm volatile("" : "+v"(rl));
+    float* dst = part + ((int64_t)split * n + p_base) * kFc1Out;
+    // tiles o * kPer + j0 .. o * kPer + j0 + kN - 1 of every group o; the
+    // src-th other group writes entry(o, j, src)
+    auto reduce = [&](auto j0c, auto nc, floatx4* red) {
+      constexpr int j0 = decltype(j0c)::value, kN = decltype(nc)::value;
+      auto entry = [&](int o, int j, int src) {
+        return (((nh * kKGroups + o) * kN + j) * (kKGroups - 1) + src) * 64 + rl;
+      };
+      static_for<kKGroups * kN>([&](auto ic) {
+        constexpr int o = decltype(ic)::value / kN, j = decltype(ic)::value % kN;
+        if (kg != o)
+          red[entry(o, j, kg - (kg > o ? 1 : 0))] = tile(std::integral_constant<int, o * kPer + j0 + j>{});
+      });
+      __syncthreads();
+      // tile q = m * kTiles + t: outputs 16(nh*kMT + m) + 4*grp + e for patch
+      // 16*(block tile) + col, the block tile nh*kOwn + t (own) or
+      // (1-nh)*kOwn + t - kOwn (partner's)
+      static_for<kKGroups * kN>([&](auto ic) {
+        constexpr int o = decltype(ic)::value / kN, j = decltype(ic)::value % kN;
+        constexpr int q = o * kPer + j0 + j, m = q / kTiles, t = q % kTiles;
+        if (kg == o) {
+          floatx4 v[kKGroups];
 #pragma unroll
-      for (int g = 0; g < kKGroups; ++g)
-        v[g] = (g == o) ? tile(qc) : red[entry(q, g - (g > o ? 1 : 0))];
-      const floatx4 sum = (v[0] + v[2]) + (v[1] + v[3]);
-      const int64_t pt = (int64_t)((j < kOwn) ? nh * kOwn + j : (1 - nh) * kOwn + (j - kOwn)) * 16 + col;
-      const int out = 16 * (nh * kMT + m) + 4 * grp;
-      // the partials are read once, by the tail kernel: non-temporal stores keep
-      // them from evicting the FC1 weight slices from L2
-      if (p_base + pt < n) __builtin_nontemporal_store(sum, reinterpret_cast<floatx4*>(dst + pt * kFc1Out + out));
-    }
-  });
+          for (int g = 0; g < kKGroups; ++g)
+            v[g] = (g == o) ? tile(std::integral_constant<int, q>{}) : red[entry(o, j, g - (g > o ? 1 : 0))];
+          const floatx4 sum = (v[0] + v[2]) + (v[1] + v[3]);
+          const int pt = ((t < kOwn) ? nh * kOwn + t : (1 - nh) * kOwn + (t - kOwn)) * 16 + (rl & 15);
+          const int out = 16 * (nh * kMT + m) + 4 * (rl >> 4);
+          // the partials are read once, by the tail kernel: non-temporal stores keep
+          // them from evicting the FC1 weights from L2
+          if (p_base + pt < n) __builtin_nontemporal_store(sum, reinterpret_cast<floatx4*>(dst + pt * kFc1Out + out));
+        }
+      });
+    };
+    constexpr int kPass = T::kRedTiles;
+    floatx4* red = reinterpret_cast<floatx4*>(lds + T::kSwapOff);
+    reduce(std::integral_constant<int, 0>{}, std::integral_constant<int, kPass>{}, red);
+    // (one range per block: the second pass through LDS that the first leaves alone)
+    if constexpr (kMulti) __syncthreads();
+    reduce(std::integral_constant<int, kPass>{}, std::integral_constant<int, kPer - kPass>{},
+           kMulti ? red : reinterpret_cast<floatx4*>(lds));
+    if (split + 1 < split0 + ranges) __syncthreads();
+  }
 }
 
-// Tiles t < n_big hold kBigTile patches, the ones after them kMidTile.  A
-// patch's sums do not depend on the size of the tile it is in: every MFMA
-// column and every reduction step is per patch.
-template <bool kFp16, int kSplits, class In>
+// Blocks of a launch.  Most of a block's time outside its loop goes to its
+// first patch rows, so a block takes 4 or 2 consecutive position ranges where
+// whole rounds of those can be filled (fused kernel on the event, fp16 patches:
+// 1.152 -> 1.146 ms; with fp32 patches, whose rows are twice as long, one
+// range per block would cost the gain of rounding them here).  A patch's sums
+// do not depend on the size of the tile it is in (every MFMA column and every
+// reduction step is per patch) nor on how many ranges a block takes.  In launch
+// order: big tiles with 4, 2 and 1 ranges per block, then mid tiles with 2 and 1.
+struct Blocks16 {
+  int64_t big4, big2, big1, mid2, mid1;      // tiles
+};
+
+template <bool kFp16, class In, bool kMulti>
 __global__ __launch_bounds__(kThreads, 1) void conv_fc1_16_kernel(
-    const In* __restrict__ patches, int64_t n, int64_t n_big, const uint4* __restrict__ w1p,
-    const uint4* __restrict__ convp, float* __restrict__ part, int64_t row0, int64_t n_total) {
+    const In* __restrict__ patches, int64_t n, Blocks16 bl, const uint4* __restrict__ w1p, const uint4* __restrict__ convp,
+    float* __restrict__ part) {
   __shared__ __attribute__((aligned(16))) uint32_t lds[Tile<kBigTile>::kLdsDwords];
-  const int split = blockIdx.x % kSplits;
-  const int64_t t = blockIdx.x / kSplits;
-  if (t < n_big)
-    conv_fc1_block<kFp16, kSplits, kBigTile, In>(lds, split, t * kBigTile, patches, n, w1p, convp,
-                                                 part, row0, n_total);
+  int64_t b = blockIdx.x, first = 0, tiles = bl.big4;
+  int ranges = 4;
+  bool mid = false;
+  // segment of block b: 8 blocks (one per XCD) hold `ranges` tiles
+  auto blocks = [&] { return (tiles + ranges - 1) / ranges * 8; };
+  auto next = [&](int64_t t, int r) {
+    b -= blocks();
+    first += tiles;
+    tiles = t;
+    ranges = r;
+  };
+  if (b >= blocks()) next(bl.big2, 2);
+  if (ranges == 2 && b >= blocks()) next(bl.big1, 1);
+  if (ranges == 1 && b >= blocks()) {
+    next(bl.mid2, 2);
+    first = 0;
+    mid = true;
+    if (b >= blocks()) next(bl.mid1, 1);
+  }
+  // XCD x = b % 8 takes range group x % (8 / ranges): the blocks that run on
+  // one XCD at a time stream the same weights through its L2
+  const int groups = kSplits16 / ranges, x = (int)(b % 8);
+  const int64_t t = b / 8 * ranges + x / groups;
+  if (t >= tiles) return;
+  const int split = x % groups * ranges;
+  if (!mid)
+    conv_fc1_block<kFp16, kBigTile, In, kMulti>(lds, split, ranges, (first + t) * kBigTile, patches, n, w1p, convp,
+                                    part);
   else
-    conv_fc1_block<kFp16, kSplits, kMidTile, In>(lds, split,
-                                                 n_big * kBigTile + (t - n_big) * kMidTile,
-                                                 patches, n, w1p, convp, part, row0, n_total);
+    conv_fc1_block<kFp16, kMidTile, In, kMulti>(
+        lds, split, ranges, (bl.big4 + bl.big2 + bl.big1) * kBigTile + (first + t) * kMidTile, patches,
+        n, w1p, convp, part);
 }
 
 
@@ -477,9 +552,11 @@ struct Thin {
   // one row slot more than a range needs: the loop reads the window of the
   // pair after its last one (the result is never used), which may lie one row lower
   static constexpr int kRowsDw = (kThinRows + 1) * kSlot;
-  static constexpr int kLdsDwords = kRowsDw > kRed ? kRowsDw : kRed;
-  static constexpr int kRowChunks = kBt * 6;               // 16 B chunks per staged row
-  static constexpr int kPer = (kThinRows * kRowChunks + kThreads - 1) / kThreads;
+  static constexpr int kDescOff = kRowsDw;                 // the block's row descriptors
+  static constexpr int kMain = kDescOff + kBt * 4;
+  static constexpr int kLdsDwords = kMain > kRed ? kMain : kRed;
+  static constexpr int kRowAll = kBt * kRowChunks;         // 4-pixel chunks per staged row
+  static constexpr int kPer = (kThinRows * kRowAll + kThreads - 1) / kThreads;
   static_assert(kTiles >= 1 && kTiles <= 2, "1 or 2 patch tiles");
   static_assert(kParts == 1 || kParts == 2 || kParts == 4, "whole, half or quarter of the outputs");
 };
@@ -496,11 +573,10 @@ constexpr int thin_rows_needed(int splits) {
   return most;
 }
 
-template <bool kFp16, int kSplits, int kBt, int kParts, class In>
+template <bool kFp16, int kSplits, int kBt, int kParts>
 __device__ __forceinline__ void thin_block(
-    uint32_t* lds, int split, int opart, int64_t p_base, const In* __restrict__ patches,
-    int64_t n, const uint4* __restrict__ w1p, const uint4* __restrict__ convp,
-    float* __restrict__ part, int64_t row0, int64_t n_total) {
+    uint32_t* lds, int split, int opart, int64_t p_base, const HitSource& src,
+    const uint4* __restrict__ w1p, const uint4* __restrict__ convp, float* __restrict__ part) {
   using T = Thin<kBt, kParts>;
   constexpr int kTiles = T::kTiles, kSlot = T::kSlot, kMTw = T::kMTw;
   const int tid = threadIdx.x;
@@ -516,37 +592,66 @@ __device__ __forceinline__ void thin_block(
   const int P0 = kKGroups * G0;
   const int r0 = P0 / kPairsPerRow;                        // first input row of the range
   const int nrows = (P0 + kKGroups * steps - 1) / kPairsPerRow + kK - r0;
+  const int64_t n = src.n;
   using Op = Op16<kFp16>;
 
-  // ---- every input row of the range, all loads in flight together
-  {
-    const int total = nrows * T::kRowChunks;
-    uint4 v[T::kPer];
+  // the weights and filters first: they do not wait for the hits
+  const __amdgpu_buffer_rsrc_t w1r = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint4*>(w1p), (short)0, (int)(kFc1Frags * 16), 0x00020000);
+  const int ot0 = (opart * kNHalves + nh) * kMTw;           // the wave's first output tile
+  const int voff = lane * 16 + ot0 * 1024;
+  auto load_one = [&](int P, int q, int m) {
+    return __builtin_bit_cast(
+        uint4, __builtin_amdgcn_raw_buffer_load_b128(w1r, voff + m * 1024, (P * 3 + q) * 8 * 1024, 0));
+  };
+  // FC1 weights: 3 register sets, set q for K-step q of a pair, each reloaded
+  // for the next pair as soon as its MFMAs have issued (three K-steps ahead:
+  // with one or two patch tiles a K-step is short)
+  uint4 w[3][kMTw];
 #pragma unroll
-    for (int k = 0; k < T::kPer; ++k) {
-      const int c = tid + k * kThreads;
-      if (c < total) {
-        const int j = c / T::kRowChunks;
-        v[k] = row_chunk_load<kBt, kFp16, In>(patches, n, p_base, r0 + j, c - j * T::kRowChunks);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < T::kPer; ++k) {
-      const int c = tid + k * kThreads;
-      if (c < total) {
-        const int j = c / T::kRowChunks, cc = c - j * T::kRowChunks;
-        const int p = cc / 6, h = cc - (cc / 6) * 6;
-        uint32_t* d = lds + j * kSlot + p * kRP + h * 4;
-        *reinterpret_cast<uint2*>(d) = make_uint2(v[k].x, v[k].y);
-        *reinterpret_cast<uint2*>(d + 2) = make_uint2(v[k].z, v[k].w);
-      }
-    }
+  for (int m = 0; m < kMTw; ++m) {
+    w[0][m] = load_one(P0 + kg, 0, m);
+    w[1][m] = load_one(P0 + kg, 1, m);
+    w[2][m] = load_one(P0 + kg, 2, m);
   }
   // the six conv filter fragments [shift][channel tile], kept in registers:
   // K-step q uses fragments 2q and 2q + 1
   uint4 filt[6];
 #pragma unroll
   for (int k = 0; k < 6; ++k) filt[k] = convp[k * 64 + lane];
+
+  // ---- every input row of the range, all loads in flight together
+  {
+    uint4* desc = reinterpret_cast<uint4*>(lds + T::kDescOff);
+    if (tid < kBt) desc[tid] = src.get(p_base + tid);
+    __syncthreads();
+    const int total = nrows * T::kRowAll;
+    rowx4 v[T::kPer];
+    uint32_t kinds = 0;                      // 2 bits per chunk
+    static_assert(2 * T::kPer <= 32, "kinds");
+#pragma unroll
+    for (int k = 0; k < T::kPer; ++k) {
+      const int c = tid + k * kThreads;
+      if (c < total) {
+        const int j = c / T::kRowAll, cc = c - j * T::kRowAll;
+        uint32_t kind;
+        v[k] = row_chunk_load(desc_from_lds(desc + cc / kRowChunks), r0 + j,
+                              cc - (cc / kRowChunks) * kRowChunks, w1p, &kind);
+        kinds |= kind << 2 * k;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < T::kPer; ++k) {
+      const int c = tid + k * kThreads;
+      if (c < total) {
+        const int j = c / T::kRowAll, cc = c - j * T::kRowAll;
+        const int p = cc / kRowChunks, h = cc - (cc / kRowChunks) * kRowChunks;
+        const rowx4 x = row_chunk_finish(desc + p, r0 + j, h, v[k], (kinds >> 2 * k) & 3);
+        *reinterpret_cast<uint2*>(lds + j * kSlot + p * kRP + h * 2) =
+            make_uint2(Op::pack(x[0], x[1]), Op::pack(x[2], x[3]));
+      }
+    }
+  }
 
   int woff[4], wrow[4];
 #pragma unroll
@@ -576,30 +681,12 @@ __device__ __forceinline__ void thin_block(
     return make_uint4(relu2(Op::pack(ca[0], ca[1])), relu2(Op::pack(ca[2], ca[3])),
                       relu2(Op::pack(cb[0], cb[1])), relu2(Op::pack(cb[2], cb[3])));
   };
-  const __amdgpu_buffer_rsrc_t w1r = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint4*>(w1p), (short)0, (int)(kFc1Frags * 16), 0x00020000);
-  const int ot0 = (opart * kNHalves + nh) * kMTw;           // the wave's first output tile
-  const int voff = lane * 16 + ot0 * 1024;
-  auto load_one = [&](int P, int q, int m) {
-    return __builtin_bit_cast(
-        uint4, __builtin_amdgcn_raw_buffer_load_b128(w1r, voff + m * 1024, (P * 3 + q) * 8 * 1024, 0));
-  };
-
   floatx4 acc[kMTw][kTiles];
 #pragma unroll
   for (int m = 0; m < kMTw; ++m)
 #pragma unroll
     for (int i = 0; i < kTiles; ++i) acc[m][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
-  // FC1 weights: 3 register sets, set q for K-step q of a pair, each reloaded
-  // for the next pair as soon as its MFMAs have issued (three K-steps ahead:
-  // with one or two patch tiles a K-step is short)
-  uint4 w[3][kMTw], win[kTiles], own[kTiles];
-#pragma unroll
-  for (int m = 0; m < kMTw; ++m) {
-    w[0][m] = load_one(P0 + kg, 0, m);
-    w[1][m] = load_one(P0 + kg, 1, m);
-    w[2][m] = load_one(P0 + kg, 2, m);
-  }
+  uint4 win[kTiles], own[kTiles];
   __syncthreads();                           // the staged rows
   const floatx4 z = {0.f, 0.f, 0.f, 0.f};
   read_win(P0 + kg, win);
@@ -658,7 +745,7 @@ __device__ __forceinline__ void thin_block(
   });
   __syncthreads();
 
-  float* dst = part + ((int64_t)split * n_total + row0 + p_base) * kFc1Out;
+  float* dst = part + ((int64_t)split * n + p_base) * kFc1Out;
   static_for<kSlots>([&](auto qc) {
     constexpr int q = decltype(qc)::value, o = owner(q), m = q / kTiles, i = q % kTiles;
     if (kg == o) {
@@ -676,21 +763,18 @@ __device__ __forceinline__ void thin_block(
 }
 
 // Block b: split b % kSplits, then output part, then patch tile.
-template <bool kFp16, int kSplits, int kBt, int kParts, class In>
+template <bool kFp16, int kSplits, int kBt, int kParts>
 __global__ __launch_bounds__(kThreads, 1) void conv_fc1_16_thin_kernel(
-    const In* __restrict__ patches, int64_t n, const uint4* __restrict__ w1p,
-    const uint4* __restrict__ convp, float* __restrict__ part, int64_t row0, int64_t n_total) {
+    HitSource src, const uint4* __restrict__ w1p, const uint4* __restrict__ convp,
+    float* __restrict__ part) {
   static_assert(thin_rows_needed(kSplits) <= kThinRows, "a position range's rows fit the stage");
   __shared__ __attribute__((aligned(16))) uint32_t lds[Thin<kBt, kParts>::kLdsDwords];
   const int split = blockIdx.x % kSplits;
   const int64_t r = blockIdx.x / kSplits;
   const int opart = (int)(r % kParts);
   const int64_t t = r / kParts;
-  thin_block<kFp16, kSplits, kBt, kParts, In>(lds, split, opart, t * kBt, patches, n, w1p, convp,
-                                              part, row0, n_total);
+  thin_block<kFp16, kSplits, kBt, kParts>(lds, split, opart, t * kBt, src, w1p, convp, part);
 }
-
-constexpr int kSplits16 = 8;
 
 }  // namespace
 
@@ -750,45 +834,51 @@ int conv_fc1_16_thin_parts(int64_t n, int cus, int thin) {
   return 2 * blocks <= cus ? 2 : 1;
 }
 
-template <bool kFp16, class In>
-hipError_t launch_typed(const In* patches, int64_t n, int64_t row0, int64_t n_total,
-                        const uint4* w1p, const uint4* convp, float* part, hipStream_t stream) {
-  int dev = 0, cus = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return e;
+template <bool kFp16>
+hipError_t launch_typed(const RowInput& in, int64_t n, const uint4* w1p, const uint4* convp,
+                        float* part, int cus, hipStream_t stream) {
   const int thin = conv_fc1_16_thin_tile(n, cus);
   if (thin) {
     const int parts = conv_fc1_16_thin_parts(n, cus, thin);
     const dim3 grid((unsigned)((n + thin - 1) / thin * kSplits16 * parts));
+    const HitSource src = hit_source(in, n);
     auto go = [&](auto kernel) {
-      return launch_kernel(kernel, grid, dim3(kThreads), 0, stream, patches, n, w1p, convp, part,
-                           row0, n_total);
+      return launch_kernel(kernel, grid, dim3(kThreads), 0, stream, src, w1p, convp, part);
     };
-    if (thin == 32) return go(conv_fc1_16_thin_kernel<kFp16, kSplits16, 32, 1, In>);
-    if (parts == 4) return go(conv_fc1_16_thin_kernel<kFp16, kSplits16, 16, 4, In>);
-    return parts == 2 ? go(conv_fc1_16_thin_kernel<kFp16, kSplits16, 16, 2, In>)
-                      : go(conv_fc1_16_thin_kernel<kFp16, kSplits16, 16, 1, In>);
+    if (thin == 32) return go(conv_fc1_16_thin_kernel<kFp16, kSplits16, 32, 1>);
+    if (parts == 4) return go(conv_fc1_16_thin_kernel<kFp16, kSplits16, 16, 4>);
+    return parts == 2 ? go(conv_fc1_16_thin_kernel<kFp16, kSplits16, 16, 2>)
+                      : go(conv_fc1_16_thin_kernel<kFp16, kSplits16, 16, 1>);
   }
   int64_t n_big = 0, n_mid = 0;
   conv_fc1_16_tiles(n, cus, &n_big, &n_mid);
-  const dim3 grid((unsigned)((n_big + n_mid) * kSplits16));
-  return launch_kernel(conv_fc1_16_kernel<kFp16, kSplits16, In>, grid, dim3(kThreads), 0, stream,
-                       patches, n, n_big, w1p, convp, part, row0, n_total);
+  // blocks of several ranges for the whole rounds of tiles there are
+  const int64_t round = cus >= kSplits16 ? cus / kSplits16 : 1;
+  Blocks16 bl = {};
+  bl.big4 = n_big / (4 * round) * (4 * round);
+  bl.big2 = (n_big - bl.big4) / (2 * round) * (2 * round);
+  bl.big1 = n_big - bl.big4 - bl.big2;
+  bl.mid2 = n_mid / (2 * round) * (2 * round);
+  if (n_mid - bl.mid2 > round) bl.mid2 = n_mid;
+  bl.mid1 = n_mid - bl.mid2;
+  const int64_t blocks = bl.big4 * 2 + bl.big2 * 4 + bl.big1 * 8 + (bl.mid2 + 1) / 2 * 8 + bl.mid1 * 8;
+  auto go = [&](auto kernel, auto* patches) {
+    return launch_kernel(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, patches, n, bl, w1p,
+                         convp, part);
+  };
+  const bool multi = bl.big4 + bl.big2 + bl.mid2 > 0;
+  if (in.patches)
+    return multi ? go(conv_fc1_16_kernel<kFp16, float, true>, in.patches)
+                 : go(conv_fc1_16_kernel<kFp16, float, false>, in.patches);
+  return multi ? go(conv_fc1_16_kernel<kFp16, uint16_t, true>, in.patches16)
+               : go(conv_fc1_16_kernel<kFp16, uint16_t, false>, in.patches16);
 }
 
-hipError_t launch_conv_fc1_16(bool fp16, const void* patches, bool f32_in, int64_t n, int64_t row0,
-                              int64_t n_total, const uint4* w1p, const uint4* convp,
-                              float* part, hipStream_t stream) {
+hipError_t launch_conv_fc1_16(bool fp16, const RowInput& in, int64_t n, const uint4* w1p,
+                              const uint4* convp, float* part, int cus, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
-  if (f32_in) {
-    const float* p = static_cast<const float*>(patches);
-    return fp16 ? launch_typed<true>(p, n, row0, n_total, w1p, convp, part, stream)
-                : launch_typed<false>(p, n, row0, n_total, w1p, convp, part, stream);
-  }
-  const uint16_t* p = static_cast<const uint16_t*>(patches);
-  return fp16 ? launch_typed<true>(p, n, row0, n_total, w1p, convp, part, stream)
-              : launch_typed<false>(p, n, row0, n_total, w1p, convp, part, stream);
+  return fp16 ? launch_typed<true>(in, n, w1p, convp, part, cus, stream)
+              : launch_typed<false>(in, n, w1p, convp, part, cus, stream);
 }
 
 }  // namespace pointid

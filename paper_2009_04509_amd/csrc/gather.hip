@@ -282,6 +282,13 @@ hipError_t launch_bin_ticks(const PlaneTable& in, const PlaneTable& out, int tic
   return launch_kernel(bin_ticks_kernel<false>, grid, dim3(256), 0, stream, in, out, ticks_per_column);
 }
 
+hipError_t device_cus(int* cus) {
+  int dev = 0;
+  const hipError_t e = hipGetDevice(&dev);
+  return e != hipSuccess ? e
+                         : hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+}
+
 hipError_t launch_patches_to_16(bool fp16, const float* in, int64_t n, uint16_t* out,
                                 hipStream_t stream) {
   if (n <= 0) return hipSuccess;

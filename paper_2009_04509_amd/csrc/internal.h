@@ -170,9 +170,14 @@ int set_error(int code, const std::string& msg);
 // Device ordinal of a handle.
 int handle_device(pointid_handle h);
 
-// Fused conv + ReLU + FC1 on 16-bit MFMA: patches [n][2304] (bf16 or fp16
-// bits, or fp32 when f32_in: rounded in the kernel) -> part[s][row0 + i][128]
-// for s < conv_fc1_16_splits().
+// The patches of a launch: pre-cut, gathered, or hits on planes (rows.h).
+struct RowInput;
+// Compute units of the current device.
+hipError_t device_cus(int* cus);
+
+// Fused conv + ReLU + FC1 on 16-bit MFMA: fp32 patches (rounded to bf16 or
+// fp16 in the kernel), 16-bit patches, or hits (batches that run thin tiles
+// only) -> part[s][i][128] for s < conv_fc1_16_splits().
 int conv_fc1_16_splits();
 // Tiles of the launch over n patches on `cus` CUs: n_big tiles of 96 patches,
 // then n_mid of 64 (a batch that fits one round of thin tiles of 16 or 32
@@ -180,9 +185,8 @@ int conv_fc1_16_splits();
 void conv_fc1_16_tiles(int64_t n, int cus, int64_t* n_big, int64_t* n_mid);
 int conv_fc1_16_thin_tile(int64_t n, int cus);
 int conv_fc1_16_thin_parts(int64_t n, int cus, int thin);
-hipError_t launch_conv_fc1_16(bool fp16, const void* patches, bool f32_in, int64_t n, int64_t row0,
-                              int64_t n_total, const uint4* w1p, const uint4* convp,
-                              float* part, hipStream_t stream);
+hipError_t launch_conv_fc1_16(bool fp16, const RowInput& in, int64_t n, const uint4* w1p,
+                              const uint4* convp, float* part, int cus, hipStream_t stream);
 
 // Fused conv (fp16 MFMA) + ReLU + FC1 on e4m3 MFMA operands: fp16 patches
 // [n][2304] -> part[s][row0 + i][128] for s < conv_fc1_8_splits(), the sums
