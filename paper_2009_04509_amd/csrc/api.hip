@@ -341,73 +341,61 @@ class EndsCall {
   bool on_;
 };
 
-// Scratch bytes of one call: 16-bit or fp32 patches (when the call makes
-// them) and the FC1 split-K partials.
-size_t patch_bytes(int precision, int64_t n) {
-  return (precision == POINTID_FP32 ? 4 : 2) * (size_t)n * kPatchPix;
-}
-size_t scratch_bytes(int precision, int64_t n, bool makes_patches) {
-  size_t b = makes_patches ? pad256(patch_bytes(precision, n)) : 0;
-  const int S = precision == POINTID_FP8 ? conv_fc1_8_splits()
-                : precision != POINTID_FP32 ? conv_fc1_16_splits() : conv_fc1_f32_splits();
-  b += pad256(sizeof(float) * (size_t)S * n * kFc1Out);
-  return b;
+// Scratch bytes of one call: the 16-bit patches (when the call makes them) and
+// the FC1 split-K partials.
+size_t patch_bytes(int64_t n) { return 2 * (size_t)n * kPatchPix; }
+size_t part_bytes(int precision, int64_t n, int cus) {
+  const int S = precision == POINTID_FP8    ? conv_fc1_8_splits()
+                : precision != POINTID_FP32 ? conv_fc1_16_splits()
+                                            : conv_fc1_f32_splits() * conv_fc1_f32_groups(n, cus);
+  return sizeof(float) * (size_t)S * n * kFc1Out;
 }
 
-// fp32 handles: patches (fp32 [n][2304]) -> scores, or into the outputs of the
-// requests of `reqs` when it is given.
-int run_network_fp32(pointid_handle h, const float* patches, int64_t n, float* scores,
+// The end of every call: split-K partials -> scores, or into the outputs of
+// the requests of `reqs` when it is given.
+int run_tail(pointid_handle h, const float* part, int splits, int groups, int64_t n, float* scores,
+             hipStream_t stream, Workspace& ws, const RequestTable* reqs) {
+  KernelTimer kt("tail", stream);
+  EndsCall end(ws);
+  const hipError_t e = reqs ? launch_tail_requests(part, splits, groups, h->w, *reqs, stream)
+                            : launch_tail(part, splits, groups, n, h->w, scores, stream);
+  end.launched(e);
+  return e == hipSuccess ? POINTID_OK : hip_fail(e, "tail launch");
+}
+
+// fp32 handles: patches or hits -> scores.
+int run_network_fp32(pointid_handle h, const RowInput& in, int64_t n, float* scores, int cus,
                      hipStream_t stream, Workspace& ws, const RequestTable* reqs = nullptr) {
-  const int S = conv_fc1_f32_splits();
   float* part = nullptr;
-  hipError_t e = ws.get(sizeof(float) * (size_t)S * n * kFc1Out, (void**)&part);
+  hipError_t e = ws.get(part_bytes(h->precision, n, cus), (void**)&part);
   if (e != hipSuccess) return hip_fail(e, "workspace (FC1 partials)");
   {
     KernelTimer kt("conv_fc1_f32", stream);
-    e = launch_conv_fc1_f32(patches, n, 0, n, h->w.conv_w, h->w.conv_b, h->w.fc1_wt, part, stream);
+    e = launch_conv_fc1_f32(in, n, h->w.conv_w, h->w.conv_b, h->w.fc1_frag32, part, cus, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "conv_fc1_f32 launch");
-  {
-    KernelTimer kt("tail", stream);
-    EndsCall end(ws);
-    e = reqs ? launch_tail_requests(part, S, h->w, *reqs, stream)
-             : launch_tail(part, S, n, h->w, scores, stream);
-    end.launched(e);
-  }
-  if (e != hipSuccess) return hip_fail(e, "tail launch");
-  return POINTID_OK;
+  return run_tail(h, part, conv_fc1_f32_splits(), conv_fc1_f32_groups(n, cus), n, scores, stream, ws, reqs);
 }
 
 // 8-bit handles: fp16 patches [n][2304] -> scores.
-int run_network_8(pointid_handle h, const uint16_t* patches, int64_t n, float* scores,
+int run_network_8(pointid_handle h, const uint16_t* patches, int64_t n, float* scores, int cus,
                   hipStream_t stream, Workspace& ws, const RequestTable* reqs = nullptr) {
-  const int S = conv_fc1_8_splits();
   float* part = nullptr;
-  hipError_t e = ws.get(sizeof(float) * (size_t)S * n * kFc1Out, (void**)&part);
+  hipError_t e = ws.get(part_bytes(h->precision, n, cus), (void**)&part);
   if (e != hipSuccess) return hip_fail(e, "workspace (FC1 partials)");
   {
     KernelTimer kt("conv_fc1_8", stream);
     e = launch_conv_fc1_8(patches, n, 0, n, h->w.fc1_frag8, h->w.conv_frag, part, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "conv_fc1 launch");
-  {
-    KernelTimer kt("tail", stream);
-    EndsCall end(ws);
-    e = reqs ? launch_tail_requests(part, S, h->w, *reqs, stream)
-             : launch_tail(part, S, n, h->w, scores, stream);
-    end.launched(e);
-  }
-  if (e != hipSuccess) return hip_fail(e, "tail launch");
-  return POINTID_OK;
+  return run_tail(h, part, conv_fc1_8_splits(), 1, n, scores, stream, ws, reqs);
 }
 
 // 16-bit handles: patches or hits -> scores.
 int run_network_16(pointid_handle h, const RowInput& in, int64_t n, float* scores, int cus,
                    hipStream_t stream, Workspace& ws, const RequestTable* reqs = nullptr) {
-  const int S = conv_fc1_16_splits();
-  hipError_t e;
   float* part = nullptr;
-  e = ws.get(sizeof(float) * (size_t)S * n * kFc1Out, (void**)&part);
+  hipError_t e = ws.get(part_bytes(h->precision, n, cus), (void**)&part);
   if (e != hipSuccess) return hip_fail(e, "workspace (FC1 partials)");
   {
     KernelTimer kt("conv_fc1_16", stream);
@@ -415,15 +403,7 @@ int run_network_16(pointid_handle h, const RowInput& in, int64_t n, float* score
                            cus, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "conv_fc1 launch");
-  {
-    KernelTimer kt("tail", stream);
-    EndsCall end(ws);
-    e = reqs ? launch_tail_requests(part, S, h->w, *reqs, stream)
-             : launch_tail(part, S, n, h->w, scores, stream);
-    end.launched(e);
-  }
-  if (e != hipSuccess) return hip_fail(e, "tail launch");
-  return POINTID_OK;
+  return run_tail(h, part, conv_fc1_16_splits(), 1, n, scores, stream, ws, reqs);
 }
 
 // An empty request table (unused starts past every patch index).
@@ -446,38 +426,38 @@ int classify_table(pointid_handle h, const PlaneTable& planes, const RequestTabl
                    int tick_div, float* scores, hipStream_t stream, Workspace& ws) {
   const int64_t n = reqs.start[reqs.n];
   const RequestTable* out = scores ? nullptr : &reqs;
-  hipError_t e = ws.reserve(scratch_bytes(h->precision, n, true));
+  const bool fp8 = h->precision == POINTID_FP8, fp32 = h->precision == POINTID_FP32;
+  int cus = 0;
+  hipError_t e = device_cus(&cus);
+  if (e != hipSuccess) return hip_fail(e, "device attribute");
+  // The fp32 kernel, and the 16-bit kernel for batches that fill at most one
+  // round of thin tiles, take the hits themselves.  The 16-bit kernel's larger
+  // tiles read 16-bit patches from the gather: at the card's power limit the
+  // image reads cost them as much as the gather takes.
+  const bool direct = fp32 || (!fp8 && conv_fc1_16_thin_tile(n, cus));
+  e = ws.reserve((direct ? 0 : pad256(patch_bytes(n))) + pad256(part_bytes(h->precision, n, cus)));
   if (e != hipSuccess) return hip_fail(e, "scratch buffer");
   RowInput in;
   in.planes = &planes;
   in.reqs = &reqs;
   in.div = tick_div;
-  const bool fp8 = h->precision == POINTID_FP8, half = !fp8 && h->precision != POINTID_FP32;
-  int cus = 0;
-  e = device_cus(&cus);
-  if (e != hipSuccess) return hip_fail(e, "device attribute");
-  // batches that fill at most one round of thin tiles: the fused kernel takes
-  // the hits itself, which saves the gather's launch (128 hits, fp16: 27.3 ->
-  // 26.0 us per call with the same fused kernel)
-  if (half && conv_fc1_16_thin_tile(n, cus))
-    return run_network_16(h, in, n, scores, cus, stream, ws, out);
-  void* patches = nullptr;
-  e = ws.get(patch_bytes(h->precision, n), &patches);
-  if (e != hipSuccess) return hip_fail(e, "workspace (patches)");
-  {
-    KernelTimer kt("gather", stream);
-    const int dt = fp8 ? POINTID_FP16 : h->precision;
-    e = scores ? launch_gather(planes, reqs.hits[0], reqs.plane[0] < 0 ? 3 : 2, n, patches, dt, stream,
-                               tick_div)
-               : launch_gather_requests(planes, reqs, patches, dt, stream);
-  }
-  if (e != hipSuccess) return hip_fail(e, "gather launch");
-  if (half) {
+  if (!direct) {
+    void* patches = nullptr;
+    e = ws.get(patch_bytes(n), &patches);
+    if (e != hipSuccess) return hip_fail(e, "workspace (patches)");
+    {
+      KernelTimer kt("gather", stream);
+      const int dt = fp8 ? POINTID_FP16 : h->precision;
+      e = scores ? launch_gather(planes, reqs.hits[0], reqs.plane[0] < 0 ? 3 : 2, n, patches, dt, stream,
+                                 tick_div)
+                 : launch_gather_requests(planes, reqs, patches, dt, stream);
+    }
+    if (e != hipSuccess) return hip_fail(e, "gather launch");
     in.patches16 = static_cast<const uint16_t*>(patches);
-    return run_network_16(h, in, n, scores, cus, stream, ws, out);
   }
-  if (fp8) return run_network_8(h, static_cast<const uint16_t*>(patches), n, scores, stream, ws, out);
-  return run_network_fp32(h, static_cast<const float*>(patches), n, scores, stream, ws, out);
+  if (fp8) return run_network_8(h, in.patches16, n, scores, cus, stream, ws, out);
+  return fp32 ? run_network_fp32(h, in, n, scores, cus, stream, ws, out)
+              : run_network_16(h, in, n, scores, cus, stream, ws, out);
 }
 
 // One array of hits (stride 2: (wire, tick) on plane 0; 3: (plane, wire,
@@ -524,14 +504,15 @@ int classify_request_batch(pointid_handle h, const PlaneTable& planes, const Req
 }
 
 // ---- scratch for pointid_classify_planes_noalloc: a fixed device array,
-// sized for kNoAllocMaxHits hits at any precision (fp32 patches and the
-// split-K partials of both fused kernels, 8 splits each).  Every GPU the
+// sized for kNoAllocMaxHits hits at any precision (16-bit patches and the
+// split-K partials, 8 splits; 32 groups of partials at up to 1,024 patches take
+// no more).  Every GPU the
 // library runs on holds its own copy until the process ends.  In host code
 // the array's name is no device address: the address comes from
 // hipGetSymbolAddress, once per device, and only that address is used.
 constexpr int64_t kNoAllocMaxHits = 8192;
 constexpr size_t kNoAllocBytes =
-    ((size_t)kNoAllocMaxHits * kPatchPix * 4 + kScratchAlign - 1) / kScratchAlign * kScratchAlign +
+    ((size_t)kNoAllocMaxHits * kPatchPix * 2 + kScratchAlign - 1) / kScratchAlign * kScratchAlign +
     ((size_t)8 * kNoAllocMaxHits * kFc1Out * 4 + kScratchAlign - 1) / kScratchAlign * kScratchAlign;
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
@@ -689,7 +670,7 @@ int pointid_create(const pointid_weights* w, int precision, int device,
     pieces.push_back({nullptr, (size_t)kConvFrags * 16, (const void**)&hnd->w.conv_frag});
     pieces.push_back({nullptr, (size_t)kFc1Frags * 16, (const void**)&hnd->w.fc1_frag});
   } else {
-    pieces.push_back({nullptr, sizeof(float) * kFc1In * kFc1Out, (const void**)&hnd->w.fc1_wt});
+    pieces.push_back({nullptr, sizeof(float) * kFc1In * kFc1Out, (const void**)&hnd->w.fc1_frag32});
   }
   size_t total = 0;
   std::vector<size_t> offs;
@@ -715,7 +696,7 @@ int pointid_create(const pointid_weights* w, int precision, int device,
   }
   {
     // FC1 is rearranged on the device from a temporary fp32 copy: 16-bit
-    // fragments for the MFMA kernel, or the transposed fp32 matrix
+    // or 8-bit fragments for the MFMA kernels, or fp32 ones
     float* w1 = nullptr;
     e = hipMalloc(&w1, sizeof(float) * kFc1In * kFc1Out);
     if (e == hipSuccess)
@@ -731,7 +712,7 @@ int pointid_create(const pointid_weights* w, int precision, int device,
                          const_cast<uint4*>(hnd->w.conv_frag), const_cast<uint4*>(hnd->w.fc1_frag),
                          nullptr);
     if (e == hipSuccess && !half)
-      e = launch_transpose_w1(w1, const_cast<float*>(hnd->w.fc1_wt), nullptr);
+      e = launch_pack_fc1_f32(w1, const_cast<float*>(hnd->w.fc1_frag32), nullptr);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (w1) (void)hipFree(w1);
     if (e != hipSuccess) {
@@ -961,27 +942,27 @@ int pointid_classify_patches(pointid_handle h, const float* patches, int64_t n,
   DeviceScope dev(h->device);
   if (dev.error() != hipSuccess) return hip_fail(dev.error(), "hipSetDevice");
   const bool fp8 = h->precision == POINTID_FP8;
+  int cus = 0;
+  hipError_t e = device_cus(&cus);
+  if (e != hipSuccess) return hip_fail(e, "device attribute");
   Workspace ws(h->scratch, stream);
-  hipError_t e = ws.reserve(scratch_bytes(h->precision, n, fp8));
+  e = ws.reserve((fp8 ? pad256(patch_bytes(n)) : 0) + pad256(part_bytes(h->precision, n, cus)));
   if (e != hipSuccess) return hip_fail(e, "scratch buffer");
-  if (h->precision == POINTID_FP32) return run_network_fp32(h, patches, n, scores, stream, ws);
   if (!fp8) {
     RowInput in;
     in.patches = patches;
-    int cus = 0;
-    e = device_cus(&cus);
-    if (e != hipSuccess) return hip_fail(e, "device attribute");
-    return run_network_16(h, in, n, scores, cus, stream, ws);
+    return h->precision == POINTID_FP32 ? run_network_fp32(h, in, n, scores, cus, stream, ws)
+                                        : run_network_16(h, in, n, scores, cus, stream, ws);
   }
   uint16_t* pb = nullptr;
-  e = ws.get(patch_bytes(h->precision, n), (void**)&pb);
+  e = ws.get(patch_bytes(n), (void**)&pb);
   if (e != hipSuccess) return hip_fail(e, "workspace (16-bit patches)");
   {
     KernelTimer kt("patches_to_16", stream);
     e = launch_patches_to_16(true, patches, n, pb, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "16-bit cast launch");
-  return run_network_8(h, pb, n, scores, stream, ws);
+  return run_network_8(h, pb, n, scores, cus, stream, ws);
 }
 
 int pointid_gather(const float* image, int32_t n_wires, int32_t n_ticks,

@@ -92,7 +92,7 @@ struct DeviceWeights {
   int precision;             // POINTID_FP32 / POINTID_BF16 / POINTID_FP16 / POINTID_FP8
   const float* conv_w;       // [48][25] fp32
   const float* conv_b;       // [48]
-  const float* fc1_wt;       // [128][92928] fp32, FC1 transposed (fp32 handles)
+  const float* fc1_frag32;   // fp32 handles: [968 pairs][6 K-steps][8 output tiles][64 lanes] x 4
   const float* fc1_b;        // [128]
   const float* fc2_w;        // [128][32]
   const float* fc2_b;        // [32]
@@ -197,26 +197,29 @@ void conv_fc1_8_tiles(int64_t n, int cus, int64_t* n_big, int64_t* n_small);
 hipError_t launch_conv_fc1_8(const uint16_t* patches, int64_t n, int64_t row0, int64_t n_total,
                              const uint8_t* w1p, const uint4* convp, float* part, hipStream_t stream);
 
-// Fused fp32 conv + ReLU + FC1 on fp32 MFMA: patches [n][2304] fp32 ->
-// part[s][row0 + i][128] for s < conv_fc1_f32_splits(), from the conv filters
-// and biases and the transposed FC1 weights w1t[o][k].
+// Fused fp32 conv + ReLU + FC1 on fp32 MFMA: fp32 patches or hits ->
+// part[s][i][128] for s < conv_fc1_f32_splits() x groups, from the conv filters
+// and biases and the packed FC1 weights.  groups = conv_fc1_f32_groups(n, cus):
+// 4 where the tail has to add the sums of each range's 4 position groups.
 int conv_fc1_f32_splits();
-// Tiles of the fused fp32 launch for n patches on `cus` CUs (64 and 32 patches).
+int conv_fc1_f32_groups(int64_t n, int cus);
+// Tiles of the fused fp32 launch for n patches on `cus` CUs (32 and 16 patches).
 void conv_fc1_f32_tiles(int64_t n, int cus, int64_t* n_big, int64_t* n_small);
-hipError_t launch_conv_fc1_f32(const float* patches, int64_t n, int64_t row0, int64_t n_total,
-                               const float* conv_w, const float* conv_b, const float* w1t,
-                               float* part, hipStream_t stream);
+hipError_t launch_conv_fc1_f32(const RowInput& in, int64_t n, const float* conv_w, const float* conv_b,
+                               const float* w1f, float* part, int cus, hipStream_t stream);
 
-// w1t[o][k] = w1[k][o] for the FC1 weights.
-hipError_t launch_transpose_w1(const float* w1, float* w1t, hipStream_t stream);
+// The fp32 FC1 weights in the order of that kernel.
+hipError_t launch_pack_fc1_f32(const float* w1, float* w1f, hipStream_t stream);
 
 // Reduce the split-K partials in fixed order, then bias+ReLU, FC2+ReLU, the
-// softmax and sigmoid heads: scores [n][4].
-hipError_t launch_tail(const float* part, int splits, int64_t n,
+// softmax and sigmoid heads: scores [n][4].  groups (1 or 4): the partials are
+// those of each split's position groups, part[4 s + g], added as
+// (g0 + g2) + (g1 + g3) first.
+hipError_t launch_tail(const float* part, int splits, int groups, int64_t n,
                        const DeviceWeights& w, float* scores,
                        hipStream_t stream);
 // The same, with patch p's scores written to its request's output.
-hipError_t launch_tail_requests(const float* part, int splits, const DeviceWeights& w,
+hipError_t launch_tail_requests(const float* part, int splits, int groups, const DeviceWeights& w,
                                 const RequestTable& reqs, hipStream_t stream);
 
 // Hit finding (hits.hip).  The waveforms of all planes are cut into steps of
