@@ -1034,32 +1034,28 @@ int pointid_find_hits(pointid_handle h, const pointid_plane* planes, int32_t n_p
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   DeviceScope dev(h->device);
   if (dev.error() != hipSuccess) return hip_fail(dev.error(), "hipSetDevice");
-  const size_t mask_bytes = 4 * sizeof(uint64_t) * (size_t)st.step0[st.n];
+  const size_t mask_bytes = 8 * sizeof(uint32_t) * (size_t)st.step0[st.n];
   const size_t count_bytes = sizeof(int32_t) * (size_t)st.workers;
-  const size_t off_bytes = sizeof(int64_t) * (size_t)st.workers;
+  const size_t block_bytes = sizeof(int32_t) * (size_t)hit_blocks(st);
   Workspace ws(h->scratch, stream);
-  hipError_t e = ws.reserve(pad256(mask_bytes) + pad256(count_bytes) + pad256(off_bytes));
+  hipError_t e = ws.reserve(pad256(mask_bytes) + pad256(count_bytes) + pad256(block_bytes));
   if (e != hipSuccess) return hip_fail(e, "scratch buffer");
-  uint64_t* mask = nullptr;
-  int32_t* counts = nullptr;
-  int64_t* offsets = nullptr;
+  uint32_t* mask = nullptr;
+  int32_t *counts = nullptr, *block_counts = nullptr;
   e = ws.get(mask_bytes, (void**)&mask);
   if (e == hipSuccess) e = ws.get(count_bytes, (void**)&counts);
-  if (e == hipSuccess) e = ws.get(off_bytes, (void**)&offsets);
+  if (e == hipSuccess) e = ws.get(block_bytes, (void**)&block_counts);
   if (e != hipSuccess) return hip_fail(e, "workspace (hit finding)");
   {
     KernelTimer kt("hits_mask", stream);
-    e = launch_hits_mask(t, st, threshold, mask, counts, stream);
+    e = launch_hits_mask(t, st, threshold, mask, counts, block_counts, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "hit mask launch");
   {
-    KernelTimer kt("hits_scan", stream);
-    e = launch_hits_scan(counts, st.workers, offsets, n_found, stream);
-  }
-  if (e != hipSuccess) return hip_fail(e, "hit scan launch");
-  {
     KernelTimer kt("hits_emit", stream);
-    e = launch_hits_emit(t, st, mask, counts, offsets, hits_out, capacity, stream);
+    EndsCall end(ws);
+    e = launch_hits_emit(t, st, mask, counts, block_counts, hits_out, capacity, n_found, stream);
+    end.launched(e);
   }
   if (e != hipSuccess) return hip_fail(e, "hit emit launch");
   return POINTID_OK;

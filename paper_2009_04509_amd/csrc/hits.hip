@@ -10,19 +10,19 @@
 // The waveforms are cut into steps of 256 ticks (one wire each), numbered in
 // output order, and every wave ("worker") owns one contiguous range of steps,
 // so all workers have the same amount of image to read whatever the plane
-// shapes.  Three launches, each a plain pass (no atomics, no waits between
+// shapes.  Two launches, each a plain pass (no atomics, no waits between
 // blocks):
 //   mask   per step, 4 consecutive ticks per lane (one 16-byte load), the
 //          neighbours from the adjacent lanes and, at the step's two ends,
-//          one extra value; the step's hit bits are stored as 4 ballots
-//          (32 B) and the worker's hit count at the end;
-//   scan   one block: exclusive prefix sum of the worker counts -> each
-//          worker's first output index, and the total;
-//   emit   one block per worker with hits, its waves splitting the worker's
-//          steps: each step's output index comes from a prefix sum of the
-//          steps' hit counts across lanes; a hit is ranked within its step by
-//          the set bits of the lanes below it, and the step's (plane, wire,
-//          tick) rows are staged in LDS and stored as contiguous dwords.
+//          one extra value; the step's hit bits are packed in tick order (8
+//          words, 32 B), the worker's and the block's hit counts stored at the end;
+//   emit   a block of the same 4 workers: its first output index is the sum of
+//          the counts of the blocks before it (at most 2,048 words, a few loads
+//          per thread; a scan launch of its own took 8.9 us).  A lane takes one
+//          hit: the step from a binary search in the steps' prefix sums, the
+//          word and the bit from bit counts, and consecutive lanes store
+//          consecutive rows.  (A pass with one step per wave at a time, whatever
+//          its few hits, was bound by instruction issue: 39.6 us on the event.)
 // The image is read once (the bits are 1/32 of it), so the whole call is bound
 // by HBM reads of the image.
 #include "pointid.h"
@@ -33,7 +33,6 @@ namespace {
 
 constexpr int kMaskWaves = 4;             // workers per mask block
 constexpr int kUnroll = 8;                // steps whose loads are in flight together
-constexpr int kEmitWaves = 4;             // waves sharing one worker's steps in the emit
 
 // Position of a step: plane p, wire `row`, step s along the wire, with plane
 // p's sizes and the wire's first tick cached (reloaded only when the cursor
@@ -83,18 +82,21 @@ __device__ __forceinline__ void advance(const PlaneTable& planes, const HitSteps
 template <bool kVec>
 __global__ __launch_bounds__(64 * kMaskWaves) void hits_mask_kernel(PlaneTable planes, HitSteps st,
                                                                     float thr,
-                                                                    uint64_t* __restrict__ mask,
-                                                                    int32_t* __restrict__ counts) {
+                                                                    uint32_t* __restrict__ mask,
+                                                                    int32_t* __restrict__ counts,
+                                                                    int32_t* __restrict__ block_counts) {
+  __shared__ int32_t wave_counts[kMaskWaves];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int64_t w = (int64_t)blockIdx.x * kMaskWaves + wave;
-  if (w >= st.workers) return;                           // wave-uniform
   const float ninf = -__builtin_huge_valf();
   const int64_t total = st.step0[st.n];
   int64_t g = w * st.per;
-  const int64_t end = g + st.per < total ? g + st.per : total;
-  Cursor c = locate(planes, st, g);
-  int32_t count = 0;
+  // (a wave past the last worker has no steps)
+  const int64_t end = w >= st.workers ? g : g + st.per < total ? g + st.per : total;
+  Cursor c = {};
+  if (g < end) c = locate(planes, st, g);
+  int32_t count = 0;                                     // this lane's hits
   for (; g < end; g += kUnroll) {
     float v[kUnroll][4], edge[kUnroll];
 #pragma unroll
@@ -130,65 +132,31 @@ __global__ __launch_bounds__(64 * kMaskWaves) void hits_mask_kernel(PlaneTable p
       if (lane == 0) before = edge[u];
       if (lane == 63) after = edge[u];
       const float* a = v[u];
-      const uint64_t b0 = __ballot(a[0] > thr && a[0] > before && a[0] >= a[1]);
-      const uint64_t b1 = __ballot(a[1] > thr && a[1] > a[0] && a[1] >= a[2]);
-      const uint64_t b2 = __ballot(a[2] > thr && a[2] > a[1] && a[2] >= a[3]);
-      const uint64_t b3 = __ballot(a[3] > thr && a[3] > a[2] && a[3] >= after);
-      count += __popcll(b0) + __popcll(b1) + __popcll(b2) + __popcll(b3);
-      if (lane < 4) mask[(g + u) * 4 + lane] = lane == 0 ? b0 : lane == 1 ? b1 : lane == 2 ? b2 : b3;
+      uint32_t x = (a[0] > thr && a[0] > before && a[0] >= a[1] ? 1u : 0u) |
+                   (a[1] > thr && a[1] > a[0] && a[1] >= a[2] ? 2u : 0u) |
+                   (a[2] > thr && a[2] > a[1] && a[2] >= a[3] ? 4u : 0u) |
+                   (a[3] > thr && a[3] > a[2] && a[3] >= after ? 8u : 0u);
+      count += __popc(x);
+      // the 4 bits of 8 lanes into one word: lanes 1, 2, then 4 further on
+      // (row_shl: within rows of 16 lanes)
+      x |= __builtin_amdgcn_update_dpp(0, x, 0x101, 0xf, 0xf, true) << 4;
+      x |= __builtin_amdgcn_update_dpp(0, x, 0x102, 0xf, 0xf, true) << 8;
+      x |= __builtin_amdgcn_update_dpp(0, x, 0x104, 0xf, 0xf, true) << 16;
+      if ((lane & 7) == 0) mask[(g + u) * 8 + (lane >> 3)] = x;
     }
   }
-  if (lane == 0) counts[w] = count;
-}
-
-constexpr int kScanThreads = 1024;
-constexpr int kScanPer = kHitMaxWorkers / kScanThreads;   // counts per thread
-
-__global__ __launch_bounds__(kScanThreads) void hits_scan_kernel(const int32_t* __restrict__ counts,
-                                                                 int32_t n,
-                                                                 int64_t* __restrict__ offsets,
-                                                                 int64_t* __restrict__ total) {
-  __shared__ int64_t wsum[kScanThreads / 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int i0 = tid * kScanPer;
-  int64_t v[kScanPer];
-  int64_t s = 0;
 #pragma unroll
-  for (int k = 0; k < kScanPer; ++k) {
-    v[k] = i0 + k < n ? counts[i0 + k] : 0;
-    s += v[k];
-  }
-  int64_t x = s;                                          // inclusive scan over the wave
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int64_t y = __shfl_up(x, d);
-    if (lane >= d) x += y;
-  }
-  if (lane == 63) wsum[wave] = x;
-  __syncthreads();
-  if (wave == 0) {                                        // inclusive scan of the wave sums
-    int64_t y = lane < kScanThreads / 64 ? wsum[lane] : 0;
-#pragma unroll
-    for (int d = 1; d < kScanThreads / 64; d <<= 1) {
-      const int64_t z = __shfl_up(y, d);
-      if (lane >= d) y += z;
-    }
-    if (lane < kScanThreads / 64) wsum[lane] = y;
+  for (int d = 32; d > 0; d >>= 1) count += __shfl_xor(count, d);
+  if (lane == 0) {
+    wave_counts[wave] = count;
+    if (w < st.workers) counts[w] = count;
   }
   __syncthreads();
-  int64_t run = x - s + (wave > 0 ? wsum[wave - 1] : 0);
-#pragma unroll
-  for (int k = 0; k < kScanPer; ++k) {
-    if (i0 + k < n) offsets[i0 + k] = run;
-    run += v[k];
+  if (threadIdx.x == 0) {
+    int32_t sum = 0;
+    for (int k = 0; k < kMaskWaves; ++k) sum += wave_counts[k];
+    block_counts[blockIdx.x] = sum;
   }
-  if (tid == 0) *total = wsum[kScanThreads / 64 - 1];
-}
-
-__device__ __forceinline__ uint64_t lane_word(uint64_t v, int l) {
-  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, l);
-  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
-  return ((uint64_t)hi << 32) | lo;
 }
 
 // Inclusive prefix sum over the 64 lanes.
@@ -204,97 +172,133 @@ __device__ __forceinline__ int wave_incl_scan(int x, int lane) {
 // Keeps the compiler from moving LDS accesses across this point.  A wave's
 // LDS instructions execute in issue order, so a lane reading what another lane
 // of the same wave wrote earlier needs no wait (the waves of an emit block
-// never share LDS).
+// share no staging).
 __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_wave_barrier();
   asm volatile("" ::: "memory");
 }
 
-// One block per worker; its kEmitWaves waves split the worker's steps into
-// consecutive ranges.  A wave takes its first output index from the worker's
-// offset plus the hits of the worker's steps before its range, and each
-// step's from a prefix sum of the steps' counts across lanes (64 steps per
-// pass), so the steps do not wait on each other.
-__global__ __launch_bounds__(64 * kEmitWaves) void hits_emit_kernel(PlaneTable planes, HitSteps st,
-                                                                    const uint64_t* __restrict__ mask,
-                                                                    const int32_t* __restrict__ counts,
-                                                                    const int64_t* __restrict__ offsets,
-                                                                    int32_t* __restrict__ hits,
-                                                                    int64_t capacity) {
-  __shared__ int32_t stage_all[kEmitWaves][3 * kHitStep];
+// Position of the r-th set bit (r from 0) of x.
+__device__ __forceinline__ int nth_bit(uint32_t x, int r) {
+  int pos = 0;
+#pragma unroll
+  for (int width = 16; width > 0; width >>= 1) {
+    const int below = __popc(x & ((1u << width) - 1));
+    const bool up = r >= below;
+    r -= up ? below : 0;
+    x >>= up ? width : 0;
+    pos += up ? width : 0;
+  }
+  return pos;
+}
+
+// 64 steps of one wave: their first hit, bits, plane, wire and first tick.
+struct EmitStage {
+  int32_t start[64];
+  uint32_t bits[64][8];
+  int32_t plane[64], row[64], tick[64];
+};
+
+__global__ __launch_bounds__(64 * kMaskWaves) void hits_emit_kernel(
+    PlaneTable planes, HitSteps st, const uint32_t* __restrict__ mask,
+    const int32_t* __restrict__ counts, const int32_t* __restrict__ block_counts,
+    int32_t* __restrict__ hits, int64_t capacity, int64_t* __restrict__ n_found) {
+  __shared__ EmitStage stages[kMaskWaves];
+  __shared__ int64_t wave_sums[kMaskWaves];
+  constexpr int kPer = kHitMaxWorkers / kMaskWaves / (64 * kMaskWaves);   // block counts per thread
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int64_t w = blockIdx.x;
-  int32_t* stage = stage_all[wave];
-  if (counts[w] == 0) return;
-  int64_t base = offsets[w];
-  if (base >= capacity) return;
+  const int64_t w = (int64_t)blockIdx.x * kMaskWaves + wave;
+  // hits of the blocks before this one
+  const bool last = blockIdx.x + 1 == gridDim.x;
+  const int32_t own = block_counts[blockIdx.x];
+  if (own == 0 && !last) return;                         // block-uniform
+  int64_t sum = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = threadIdx.x + k * 64 * kMaskWaves;
+    sum += i < (int)blockIdx.x ? block_counts[i] : 0;
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+  if (lane == 0) wave_sums[wave] = sum;
+  __syncthreads();
+  int64_t base = 0;
+#pragma unroll
+  for (int k = 0; k < kMaskWaves; ++k) base += wave_sums[k];
+  if (last && threadIdx.x == 0) *n_found = base + own;
+  if (w >= st.workers) return;                           // wave-uniform; no barrier below
+  for (int k = 0; k < wave; ++k) base += counts[w - wave + k];
+  if (counts[w] == 0 || base >= capacity) return;
+
+  EmitStage& sg = stages[wave];
   const int64_t total = st.step0[st.n];
   const int64_t g0 = w * st.per;
   const int64_t g1 = g0 + st.per < total ? g0 + st.per : total;
-  const int64_t share = (g1 - g0 + kEmitWaves - 1) / kEmitWaves;
-  const int64_t a = g0 + wave * share;
-  const int64_t b = a + share < g1 ? a + share : g1;
-  if (a >= b) return;                                    // wave-uniform
-  const uint4* m4 = reinterpret_cast<const uint4*>(mask);   // 2 per step
-  auto step_hits = [&](int64_t g, uint4& lo, uint4& hi) {
-    lo = m4[2 * g];
-    hi = m4[2 * g + 1];
-    return __popc(lo.x) + __popc(lo.y) + __popc(lo.z) + __popc(lo.w) + __popc(hi.x) +
-           __popc(hi.y) + __popc(hi.z) + __popc(hi.w);
-  };
-  for (int64_t c = g0; c < a; c += 64) {                 // hits of the steps before the range
-    uint4 lo, hi;
-    const int n = c + lane < a ? step_hits(c + lane, lo, hi) : 0;
-    base += __builtin_amdgcn_readlane(wave_incl_scan(n, lane), 63);
+  int p0 = 0, hi = st.n - 1;                             // the plane of step g0
+  while (p0 < hi) {
+    const int mid = (p0 + hi + 1) >> 1;
+    if (st.step0[mid] <= g0) p0 = mid;
+    else hi = mid - 1;
   }
-  Cursor cur = locate(planes, st, a);
-  for (int64_t c = a; c < b && base < capacity; c += 64) {
-    const int nst = (int)(b - c < 64 ? b - c : 64);
-    uint4 lo = make_uint4(0, 0, 0, 0), hi = lo;
-    const int n = lane < nst ? step_hits(c + lane, lo, hi) : 0;
-    const int incl = wave_incl_scan(n, lane);
-    const uint64_t mw[4] = {((uint64_t)lo.y << 32) | lo.x, ((uint64_t)lo.w << 32) | lo.z,
-                            ((uint64_t)hi.y << 32) | hi.x, ((uint64_t)hi.w << 32) | hi.z};
-    for (int k = 0; k < nst; ++k) {
-      const int nk = __builtin_amdgcn_readlane(n, k);
-      const int64_t bk = base + __builtin_amdgcn_readlane(incl, k) - nk;
-      if (bk >= capacity) break;                         // wave-uniform
-      if (nk > 0) {
-        const uint64_t ws[4] = {lane_word(mw[0], k), lane_word(mw[1], k), lane_word(mw[2], k),
-                                lane_word(mw[3], k)};
-        // hits of the lanes below this one come first (their ticks are lower)
-        uint32_t pos = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          pos = __builtin_amdgcn_mbcnt_lo((uint32_t)ws[j], pos);
-          pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(ws[j] >> 32), pos);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if ((ws[j] >> lane) & 1) {
-            stage[3 * pos] = cur.p;
-            stage[3 * pos + 1] = cur.row;
-            stage[3 * pos + 2] = cur.s * kHitStep + 4 * lane + j;
-            ++pos;
-          }
-        }
-        wave_lds_order();
-        const int lim = 3 * (int)(nk < capacity - bk ? nk : capacity - bk);
-        int32_t* o = hits + 3 * bk;
-        for (int i = lane; i < lim; i += 256) {          // 4 LDS reads in flight
-          int32_t v[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) v[u] = i + 64 * u < lim ? stage[i + 64 * u] : 0;
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (i + 64 * u < lim) o[i + 64 * u] = v[u];
-        }
-        wave_lds_order();
-      }
-      advance(planes, st, cur);
+  for (int64_t c = g0; c < g1 && base < capacity; c += 64) {
+    const int64_t g = c + lane;
+    // lane k: step c + k
+    uint4 lo = make_uint4(0, 0, 0, 0), up = lo;
+    if (g < g1) {
+      lo = reinterpret_cast<const uint4*>(mask)[2 * g];
+      up = reinterpret_cast<const uint4*>(mask)[2 * g + 1];
     }
-    base += __builtin_amdgcn_readlane(incl, nst - 1);
+    const int n = __popc(lo.x) + __popc(lo.y) + __popc(lo.z) + __popc(lo.w) + __popc(up.x) +
+                  __popc(up.y) + __popc(up.z) + __popc(up.w);
+    const int incl = wave_incl_scan(n, lane);
+    const int found = __builtin_amdgcn_readlane(incl, 63);
+    int p = p0;
+    int64_t first = st.step0[p0];
+    int per_row = st.per_row[p0];
+    for (int q = p0 + 1; q < st.n && st.step0[q] <= c + 63; ++q) {   // planes that start in the chunk
+      if (g >= st.step0[q]) {
+        p = q;
+        first = st.step0[q];
+        per_row = st.per_row[q];
+      }
+    }
+    const int64_t local = g - first;
+    const int row = (int)(local / per_row);
+    sg.start[lane] = incl - n;
+    reinterpret_cast<uint4*>(sg.bits[lane])[0] = lo;
+    reinterpret_cast<uint4*>(sg.bits[lane])[1] = up;
+    sg.plane[lane] = p;
+    sg.row[lane] = row;
+    sg.tick[lane] = (int)(local - (int64_t)row * per_row) * kHitStep;
+    p0 = __builtin_amdgcn_readlane(p, 63);
+    wave_lds_order();
+    const int lim = (int)(found < capacity - base ? found : capacity - base);
+    for (int i = lane; i < lim; i += 64) {
+      int k = 0;                                         // the last step that starts at or before hit i
+#pragma unroll
+      for (int d = 32; d > 0; d >>= 1) k += sg.start[k + d] <= i ? d : 0;
+      int r = i - sg.start[k];
+      uint32_t x = 0;
+      int word = 0;
+      bool open = true;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {                      // the word holding its r-th hit
+        const uint32_t v = sg.bits[k][j];
+        const int m = __popc(v);
+        const bool here = open && r < m;
+        x = here ? v : x;
+        word = here ? j : word;
+        open = open && !here;
+        r -= open ? m : 0;
+      }
+      int32_t* o = hits + 3 * (base + i);
+      o[0] = sg.plane[k];
+      o[1] = sg.row[k];
+      o[2] = sg.tick[k] + 32 * word + nth_bit(x, r);
+    }
+    wave_lds_order();
+    base += found;
   }
 }
 
@@ -312,34 +316,28 @@ void hit_steps(const PlaneTable& planes, HitSteps* st) {
   st->workers = (int32_t)((total + st->per - 1) / st->per);
 }
 
+int hit_blocks(const HitSteps& st) { return (st.workers + kMaskWaves - 1) / kMaskWaves; }
+
 hipError_t launch_hits_mask(const PlaneTable& planes, const HitSteps& st, float threshold,
-                            uint64_t* mask, int32_t* counts, hipStream_t stream) {
-  if (st.workers <= 0) return hipSuccess;
+                            uint32_t* mask, int32_t* counts, int32_t* block_counts,
+                            hipStream_t stream) {
   bool vec = true;
   for (int i = 0; i < planes.n; ++i)
     vec = vec && (reinterpret_cast<uintptr_t>(planes.p[i].image) & 15) == 0 &&
           planes.p[i].n_ticks % 4 == 0;
-  const dim3 grid((unsigned)((st.workers + kMaskWaves - 1) / kMaskWaves));
+  const dim3 grid((unsigned)hit_blocks(st));
   if (vec)
     return launch_kernel(hits_mask_kernel<true>, grid, dim3(64 * kMaskWaves), 0, stream, planes, st,
-                         threshold, mask, counts);
+                         threshold, mask, counts, block_counts);
   return launch_kernel(hits_mask_kernel<false>, grid, dim3(64 * kMaskWaves), 0, stream, planes, st,
-                       threshold, mask, counts);
+                       threshold, mask, counts, block_counts);
 }
 
-hipError_t launch_hits_scan(const int32_t* counts, int32_t n, int64_t* offsets, int64_t* total,
-                            hipStream_t stream) {
-  if (n > kHitMaxWorkers) return hipErrorInvalidValue;
-  return launch_kernel(hits_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, counts, n, offsets,
-                       total);
-}
-
-hipError_t launch_hits_emit(const PlaneTable& planes, const HitSteps& st, const uint64_t* mask,
-                            const int32_t* counts, const int64_t* offsets, int32_t* hits,
-                            int64_t capacity, hipStream_t stream) {
-  if (st.workers <= 0 || capacity <= 0) return hipSuccess;
-  return launch_kernel(hits_emit_kernel, dim3((unsigned)st.workers), dim3(64 * kEmitWaves), 0, stream,
-                       planes, st, mask, counts, offsets, hits, capacity);
+hipError_t launch_hits_emit(const PlaneTable& planes, const HitSteps& st, const uint32_t* mask,
+                            const int32_t* counts, const int32_t* block_counts, int32_t* hits,
+                            int64_t capacity, int64_t* n_found, hipStream_t stream) {
+  return launch_kernel(hits_emit_kernel, dim3((unsigned)hit_blocks(st)), dim3(64 * kMaskWaves), 0, stream,
+                       planes, st, mask, counts, block_counts, hits, capacity, n_found);
 }
 
 }  // namespace pointid

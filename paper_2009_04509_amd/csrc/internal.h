@@ -236,18 +236,18 @@ struct HitSteps {
   int32_t n;
 };
 void hit_steps(const PlaneTable& planes, HitSteps* st);
-// Every step's hit bits (4 uint64 words: bit l of word j = tick 4l + j of the
-// step) into mask[4g ...]; each worker's hit count into counts[w].  kVec
-// (every image 16-byte aligned, every n_ticks a multiple of 4) allows 16-byte
-// loads.
+// Blocks of both launches (each takes a few consecutive workers).
+int hit_blocks(const HitSteps& st);
+// Every step's hit bits (bit t % 32 of word 8g + t / 32 for tick t of step g)
+// into mask; each worker's and each block's hit count.  Images that are all
+// 16-byte aligned with every n_ticks a multiple of 4 are read in 16-byte loads.
 hipError_t launch_hits_mask(const PlaneTable& planes, const HitSteps& st, float threshold,
-                            uint64_t* mask, int32_t* counts, hipStream_t stream);
-// offsets[w] = sum of counts[0 .. w-1]; *total = sum of all counts.
-hipError_t launch_hits_scan(const int32_t* counts, int32_t n, int64_t* offsets, int64_t* total,
+                            uint32_t* mask, int32_t* counts, int32_t* block_counts,
                             hipStream_t stream);
-// (plane, wire, tick) of every hit with output index below `capacity`.
-hipError_t launch_hits_emit(const PlaneTable& planes, const HitSteps& st, const uint64_t* mask,
-                            const int32_t* counts, const int64_t* offsets, int32_t* hits,
-                            int64_t capacity, hipStream_t stream);
+// (plane, wire, tick) of every hit with output index below `capacity`, and the
+// number of hits.
+hipError_t launch_hits_emit(const PlaneTable& planes, const HitSteps& st, const uint32_t* mask,
+                            const int32_t* counts, const int32_t* block_counts, int32_t* hits,
+                            int64_t capacity, int64_t* n_found, hipStream_t stream);
 
 }  // namespace pointid

@@ -167,3 +167,38 @@ def test_found_hits_classify_like_given_hits(pid, handle):
     P = oracle.gather_patches_planes(imgs, ref[idx])
     want = oracle.forward(P, synth.he_normal_weights())
     assert np.abs(s_found.cpu().numpy()[idx] - want).max() <= 2e-2
+
+
+@pytest.mark.parametrize("shapes", [[(8300, 16500)], [(1, 7), (3, 256), (2, 257), (700, 1000), (1, 1)]])
+def test_planted_peaks(pid, shapes):
+    """Peaks planted on flat planes come back in order: a plane so large that a
+    worker has more than 64 steps (two passes of the emit), and small planes
+    whose steps share one, with dense and empty steps among them."""
+    rng = np.random.default_rng(len(shapes))
+    imgs, want = [], []
+    for p, (W, T) in enumerate(shapes):
+        im = torch.zeros((W, T), device=DEV)
+        n = min(W * T // 3 + 1, 200_000)
+        at = np.unique(rng.integers(0, W * T, n))
+        if W * T > 5000:                                 # a dense stretch: every second tick
+            at = np.unique(np.concatenate([at, W * T // 2 + 2 * np.arange(600)]))
+        w, t = at // T, at % T
+        keep = np.ones(len(at), bool)                    # no peak next to another on its wire
+        for i in range(1, len(at)):
+            if keep[i - 1] and w[i] == w[i - 1] and t[i] == t[i - 1] + 1:
+                keep[i] = False
+        w, t = w[keep], t[keep]
+        im[torch.from_numpy(w).to(DEV), torch.from_numpy(t).to(DEV)] = 5.0
+        imgs.append(im)
+        want.append(np.stack([np.full(len(w), p), w, t], 1))
+    want = np.concatenate(want).astype(np.int32)
+    h = pid.pointid_create(synth.he_normal_weights(), "fp16", 0)
+    for cap in (len(want) + 5, len(want) // 2):
+        say(f"planted peaks {shapes}, capacity {cap}")
+        out = torch.full((cap + 3, 3), -7, dtype=torch.int32, device=DEV)
+        got, n = pid.pointid_find_hits(h, imgs, 1.0, capacity=cap, hits_out=out)
+        assert int(n.item()) == len(want)
+        m = min(cap, len(want))
+        assert np.array_equal(got.cpu().numpy()[:m], want[:m])
+        assert (got.cpu().numpy()[m:] == -7).all()
+    h.close()
