@@ -344,21 +344,21 @@ class EndsCall {
 // Scratch bytes of one call: the 16-bit patches (when the call makes them) and
 // the FC1 split-K partials.
 size_t patch_bytes(int64_t n) { return 2 * (size_t)n * kPatchPix; }
-size_t part_bytes(int precision, int64_t n, int cus) {
+size_t part_bytes(int precision, int64_t n) {
   const int S = precision == POINTID_FP8    ? conv_fc1_8_splits()
                 : precision != POINTID_FP32 ? conv_fc1_16_splits()
-                                            : conv_fc1_f32_splits() * conv_fc1_f32_groups(n, cus);
+                                            : conv_fc1_f32_splits();
   return sizeof(float) * (size_t)S * n * kFc1Out;
 }
 
 // The end of every call: split-K partials -> scores, or into the outputs of
 // the requests of `reqs` when it is given.
-int run_tail(pointid_handle h, const float* part, int splits, int groups, int64_t n, float* scores,
+int run_tail(pointid_handle h, const float* part, int splits, int64_t n, float* scores,
              hipStream_t stream, Workspace& ws, const RequestTable* reqs) {
   KernelTimer kt("tail", stream);
   EndsCall end(ws);
-  const hipError_t e = reqs ? launch_tail_requests(part, splits, groups, h->w, *reqs, stream)
-                            : launch_tail(part, splits, groups, n, h->w, scores, stream);
+  const hipError_t e = reqs ? launch_tail_requests(part, splits, h->w, *reqs, stream)
+                            : launch_tail(part, splits, n, h->w, scores, stream);
   end.launched(e);
   return e == hipSuccess ? POINTID_OK : hip_fail(e, "tail launch");
 }
@@ -367,35 +367,35 @@ int run_tail(pointid_handle h, const float* part, int splits, int groups, int64_
 int run_network_fp32(pointid_handle h, const RowInput& in, int64_t n, float* scores, int cus,
                      hipStream_t stream, Workspace& ws, const RequestTable* reqs = nullptr) {
   float* part = nullptr;
-  hipError_t e = ws.get(part_bytes(h->precision, n, cus), (void**)&part);
+  hipError_t e = ws.get(part_bytes(h->precision, n), (void**)&part);
   if (e != hipSuccess) return hip_fail(e, "workspace (FC1 partials)");
   {
     KernelTimer kt("conv_fc1_f32", stream);
-    e = launch_conv_fc1_f32(in, n, h->w.conv_w, h->w.conv_b, h->w.fc1_frag32, part, cus, stream);
+    e = launch_conv_fc1_f32(in, n, h->w.fc1_frag, h->w.conv_frag, part, cus, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "conv_fc1_f32 launch");
-  return run_tail(h, part, conv_fc1_f32_splits(), conv_fc1_f32_groups(n, cus), n, scores, stream, ws, reqs);
+  return run_tail(h, part, conv_fc1_f32_splits(), n, scores, stream, ws, reqs);
 }
 
 // 8-bit handles: fp16 patches [n][2304] -> scores.
 int run_network_8(pointid_handle h, const uint16_t* patches, int64_t n, float* scores, int cus,
                   hipStream_t stream, Workspace& ws, const RequestTable* reqs = nullptr) {
   float* part = nullptr;
-  hipError_t e = ws.get(part_bytes(h->precision, n, cus), (void**)&part);
+  hipError_t e = ws.get(part_bytes(h->precision, n), (void**)&part);
   if (e != hipSuccess) return hip_fail(e, "workspace (FC1 partials)");
   {
     KernelTimer kt("conv_fc1_8", stream);
     e = launch_conv_fc1_8(patches, n, 0, n, h->w.fc1_frag8, h->w.conv_frag, part, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "conv_fc1 launch");
-  return run_tail(h, part, conv_fc1_8_splits(), 1, n, scores, stream, ws, reqs);
+  return run_tail(h, part, conv_fc1_8_splits(), n, scores, stream, ws, reqs);
 }
 
 // 16-bit handles: patches or hits -> scores.
 int run_network_16(pointid_handle h, const RowInput& in, int64_t n, float* scores, int cus,
                    hipStream_t stream, Workspace& ws, const RequestTable* reqs = nullptr) {
   float* part = nullptr;
-  hipError_t e = ws.get(part_bytes(h->precision, n, cus), (void**)&part);
+  hipError_t e = ws.get(part_bytes(h->precision, n), (void**)&part);
   if (e != hipSuccess) return hip_fail(e, "workspace (FC1 partials)");
   {
     KernelTimer kt("conv_fc1_16", stream);
@@ -403,7 +403,7 @@ int run_network_16(pointid_handle h, const RowInput& in, int64_t n, float* score
                            cus, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "conv_fc1 launch");
-  return run_tail(h, part, conv_fc1_16_splits(), 1, n, scores, stream, ws, reqs);
+  return run_tail(h, part, conv_fc1_16_splits(), n, scores, stream, ws, reqs);
 }
 
 // An empty request table (unused starts past every patch index).
@@ -435,7 +435,7 @@ int classify_table(pointid_handle h, const PlaneTable& planes, const RequestTabl
   // tiles read 16-bit patches from the gather: at the card's power limit the
   // image reads cost them as much as the gather takes.
   const bool direct = fp32 || (!fp8 && conv_fc1_16_thin_tile(n, cus));
-  e = ws.reserve((direct ? 0 : pad256(patch_bytes(n))) + pad256(part_bytes(h->precision, n, cus)));
+  e = ws.reserve((direct ? 0 : pad256(patch_bytes(n))) + pad256(part_bytes(h->precision, n)));
   if (e != hipSuccess) return hip_fail(e, "scratch buffer");
   RowInput in;
   in.planes = &planes;
@@ -505,8 +505,7 @@ int classify_request_batch(pointid_handle h, const PlaneTable& planes, const Req
 
 // ---- scratch for pointid_classify_planes_noalloc: a fixed device array,
 // sized for kNoAllocMaxHits hits at any precision (16-bit patches and the
-// split-K partials, 8 splits; 32 groups of partials at up to 1,024 patches take
-// no more).  Every GPU the
+// split-K partials, 8 splits).  Every GPU the
 // library runs on holds its own copy until the process ends.  In host code
 // the array's name is no device address: the address comes from
 // hipGetSymbolAddress, once per device, and only that address is used.
@@ -670,7 +669,8 @@ int pointid_create(const pointid_weights* w, int precision, int device,
     pieces.push_back({nullptr, (size_t)kConvFrags * 16, (const void**)&hnd->w.conv_frag});
     pieces.push_back({nullptr, (size_t)kFc1Frags * 16, (const void**)&hnd->w.fc1_frag});
   } else {
-    pieces.push_back({nullptr, sizeof(float) * kFc1In * kFc1Out, (const void**)&hnd->w.fc1_frag32});
+    pieces.push_back({nullptr, (size_t)kF32Parts * kConvFrags * 16, (const void**)&hnd->w.conv_frag});
+    pieces.push_back({nullptr, (size_t)kF32Parts * kFc1Frags * 16, (const void**)&hnd->w.fc1_frag});
   }
   size_t total = 0;
   std::vector<size_t> offs;
@@ -696,7 +696,7 @@ int pointid_create(const pointid_weights* w, int precision, int device,
   }
   {
     // FC1 is rearranged on the device from a temporary fp32 copy: 16-bit
-    // or 8-bit fragments for the MFMA kernels, or fp32 ones
+    // or 8-bit fragments for the MFMA kernels, or fp32 in three bf16 parts
     float* w1 = nullptr;
     e = hipMalloc(&w1, sizeof(float) * kFc1In * kFc1Out);
     if (e == hipSuccess)
@@ -712,7 +712,8 @@ int pointid_create(const pointid_weights* w, int precision, int device,
                          const_cast<uint4*>(hnd->w.conv_frag), const_cast<uint4*>(hnd->w.fc1_frag),
                          nullptr);
     if (e == hipSuccess && !half)
-      e = launch_pack_fc1_f32(w1, const_cast<float*>(hnd->w.fc1_frag32), nullptr);
+      e = launch_pack_f32(hnd->w.conv_w, hnd->w.conv_b, w1, const_cast<uint4*>(hnd->w.conv_frag),
+                          const_cast<uint4*>(hnd->w.fc1_frag), nullptr);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (w1) (void)hipFree(w1);
     if (e != hipSuccess) {
@@ -946,7 +947,7 @@ int pointid_classify_patches(pointid_handle h, const float* patches, int64_t n,
   hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return hip_fail(e, "device attribute");
   Workspace ws(h->scratch, stream);
-  e = ws.reserve((fp8 ? pad256(patch_bytes(n)) : 0) + pad256(part_bytes(h->precision, n, cus)));
+  e = ws.reserve((fp8 ? pad256(patch_bytes(n)) : 0) + pad256(part_bytes(h->precision, n)));
   if (e != hipSuccess) return hip_fail(e, "scratch buffer");
   if (!fp8) {
     RowInput in;

@@ -1,407 +1,494 @@
-// Fused conv 5x5 (1->48) + ReLU + FC1 (92928->128) in fp32 on the fp32 MFMA
-// (v_mfma_f32_16x16x4_f32), paper §2.2: the fp32 path.  The conv maps exist
-// only in registers and LDS, and the patch rows are read from the plane images
-// or the pre-cut patches themselves (rows.h): no patch is written and read back.
+// Fused conv 5x5 (1->48) + ReLU + FC1 (92928->128) of the fp32 path, paper §2.2,
+// on bf16 MFMAs (v_mfma_f32_16x16x32_bf16).  The conv maps exist only in
+// registers, and the patch rows are read from the plane images or the pre-cut
+// patches themselves (rows.h): no patch is written and read back.
 //
-// Arithmetic.  Map positions go in pairs (x, x+1), x even, in 8 contiguous
-// ranges (split-K) of 4 interleaved position groups (group g takes the pairs
-// 4k + g of a range).  The 5x6 window of a pair (30 pixels), a constant 1.0 for
-// the bias and a zero fill the K = 32 conv operand, taken as 8 MFMAs of K = 4
-// (slot f = 4i + g for MFMA i and lane group g).  Its 6 conv tiles (2 shifts x
-// 3 channel tiles of 16) are the pair's 6 K-steps.  Per K-step q (shift s,
-// channel tile t) and 16-patch tile:
-//   conv:  C[ch][patch] = sum_f Kc[ch][f] * Win[f][patch] (8 MFMAs); lane
-//          (col, g) ends with channels 16t + 4g + e, e = 0..3, of patch col;
-//   FC1:   chunk e uses that value as B operand K-slot g, so K-slot g of chunk
-//          e is FC1 input (y*44 + x + s)*48 + 16t + 4g + e; the weights are
-//          packed in that order, one 1 KiB fragment per (pair, K-step, 16 outputs).
-// A patch's sums are one chain of MFMAs per range and group, added as
-// (g0 + g2) + (g1 + g3): they do not depend on the shape of the block.
+// Arithmetic.  Every fp32 operand (pixel, filter, map value, FC1 weight) is
+// taken as the exact sum of three bf16 values, high + middle + low (3 x 8
+// significand bits), and a product as the six of its nine partial products
+// that reach fp32's precision: hh, hm, mh, mm, hl, lh.  Each partial product is
+// exact and all are added in fp32 MFMA accumulators; what is left out is below
+// 2^-22 of a product at most (2^-25 on average).  The bf16 MFMA runs at 16 times
+// the rate of the fp32 one, so six of them take 3/8 of its time (event of 50,000
+// hits: 11.7 ms per call with fp32 MFMAs, 6.26 here).  It is no less precise:
+// against the network in 64 bits the event's scores are off by a relative 1.6e-6
+// (fp32 MFMAs: 1.8e-6), those of pre-cut patches by 5.7e-7 (6.4e-7), because a
+// K = 32 MFMA rounds its accumulator once per 32 inputs.
 //
-// Work split.  8 waves share a position group, one per 16 outputs: the wave
-// holds one accumulator tile per patch tile and streams the FC1 weights of its
-// outputs.  The conv tiles of a pair are shared out over the 8 waves (so that
-// every SIMD computes as many), which read each other's through LDS: the conv
-// is computed once per block and there is one barrier per pair.  The input rows
-// of the range (at most 11) are staged in LDS at the start.  A block takes
-//   2 patch tiles (32 patches) and all 4 groups, two at a time by two sets of
-//     8 waves (16 waves, 4 per SIMD; 139 KB of LDS), in whole rounds;
-//   1 patch tile and all 4 groups, for a last round that is at most half full;
-//   1 patch tile and one group (8 waves, two such blocks fit a CU), for batches
-//     that would leave CUs idle otherwise: the groups' sums go to the tail.
-// Bound by the fp32 MFMA: 240 MFMAs per pair and patch tile against 48 weight
-// loads, 48 fragment reads and 48 window reads.
+// Map positions go in pairs (x, x+1), x even, in 8 contiguous ranges (split-K)
+// of 8 interleaved position groups, one per wave (wave g takes the pairs
+// 8k + g of a range).  The 5x6 window of a pair (30 pixels; slot 30 is 1.0 for
+// the bias) is one K = 32 conv operand per part; operand layouts, the two conv
+// tiles that feed a K-step and the 3 K-steps of a pair are those of
+// conv_fc1_16.hip.  Per K-step a wave computes the conv of each 16-patch tile
+// (2 x 6 MFMAs), splits the ReLU'd maps into three FC1 operands in place, and
+// runs 6 MFMAs per output tile and patch tile, each accumulator's six back to
+// back.  The FC1 weights are packed at create, [pair][K-step][16 outputs][part]:
+// a fragment feeds 2 MFMAs per patch tile, and a ring of register sets holds
+// the next few output tiles' fragments, each set reloaded as soon as its MFMAs
+// have issued.
+//
+// A wave needs no other wave's results before the final reduction, so the two
+// waves of a SIMD run freely, one's conversions behind the other's MFMAs; the
+// block meets only where a new patch row goes into the LDS ring (6 rows, the
+// most that one step of 8 pairs needs, in three bf16 planes).  The row's loads
+// are issued a K-step before that.
+//
+// A block takes 64 or 32 patches and one range; a patch's sums are one chain of
+// MFMAs per range and group and a fixed tree over the groups, whatever the shape
+// of the block.  Small batches share the 128 outputs over 2 or 4 blocks
+// (`kParts`; each computes the conv).
 #include "internal.h"
+#include "op16.h"
 #include "rows.h"
 
 namespace pointid {
 namespace {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-constexpr int kGroups = 4;                    // position groups
+constexpr int kWaves = 8;                     // position groups
+constexpr int kThreads = kWaves * 64;
 constexpr int kSplits = 8;                    // position ranges
-constexpr int kMTiles = kFc1Out / 16;         // 16-output tiles: the waves of a group
-constexpr int kSet = kMTiles * 64;            // threads of a group
-constexpr int kRP = 52;                       // LDS row pitch (dwords; 48 used)
+constexpr int kMTiles = kFc1Out / 16;         // 16-output tiles
 constexpr int kPairsPerRow = kFm / 2;         // 22
 constexpr int kPairs = kPos / 2;              // 968
-constexpr int kQ = 6;                         // K-steps per pair (2 shifts x 3 channel tiles)
-constexpr int kRows = 11;                     // input rows of one range, at most
-static_assert(kPairs % kGroups == 0, "whole steps");
+constexpr int kQ = 3;                         // K-steps per pair
+constexpr int kParts3 = kF32Parts;            // bf16 parts of an fp32 value: high, middle, low
+constexpr int kRing = 6;                      // patch rows in LDS
+constexpr int kRP = 26;                       // LDS row pitch of one part, dwords (24 used)
+static_assert((kWaves - 2) / kPairsPerRow + 1 + kK <= kRing, "rows of one step of 8 pairs");
+static_assert(kWaves < kPairsPerRow, "at most one new row per step");
 
-// first step (kGroups pairs) of range s, of 242 in all
-__host__ __device__ constexpr int range_begin(int s) { return kPairs / kGroups * s / kSplits; }
-constexpr int rows_needed() {
-  int most = 0;
-  for (int s = 0; s < kSplits; ++s) {
-    const int p0 = kGroups * range_begin(s), p1 = kGroups * range_begin(s + 1) - 1;
-    const int rows = p1 / kPairsPerRow + kK - p0 / kPairsPerRow;
-    most = rows > most ? rows : most;
-  }
-  return most;
-}
-static_assert(rows_needed() <= kRows, "a range's rows fit the stage");
+// first pair of range s (whole groups of 4 pairs: 120 or 124 pairs each)
+__host__ __device__ constexpr int range_begin(int s) { return 4 * (kPairs / 4 * s / kSplits); }
 
-// LDS of a block (dwords): rows | conv tiles [2 buffers][sets][6][patch tiles]
-// [64 lanes] x 4 | row descriptors.
-template <int kTiles, int kSets>
+// Block of 16 kTiles patches and 128 / kParts outputs.  LDS (dwords): ring
+// [part][row][patch] | conv filters | row descriptors | infinity flags; the
+// reduction reuses it from the start.
+template <int kTiles, int kParts>
 struct Block {
   static constexpr int kBt = 16 * kTiles;
-  static constexpr int kThreads = kSet * kSets;
-  static constexpr int kSlot = kBt * kRP;                  // dwords per staged row
-  static constexpr int kMapOff = kRows * kSlot;
-  static constexpr int kMapBuf = kQ * kTiles * 256;        // one set's buffer
-  static constexpr int kDescOff = kMapOff + 2 * kSets * kMapBuf;
-  static constexpr int kLds = kDescOff + kBt * 4;
-  static constexpr int kRowAll = kBt * kRowChunks;         // chunks per staged row
-  static constexpr int kPer = (kRows * kRowAll + kThreads - 1) / kThreads;
-  static_assert(kLds * 4 <= 160 * 1024 && 2 * kPer <= 32 && kBt <= kThreads, "block");
+  static constexpr int kMT = kMTiles / kParts;             // output tiles per wave
+  static constexpr int kSlot = kBt * kRP;                  // dwords per row and part
+  static constexpr int kPart = kRing * kSlot;
+  static constexpr int kConvOff = kParts3 * kPart;
+  static constexpr int kDescOff = kConvOff + kParts3 * 6 * 64 * 4;
+  // the reduction, at most 16 accumulator tiles a pass, of each one from each
+  // of the other 7 waves
+  static constexpr int kSlots = kMT * kTiles;
+  static constexpr int kPer = kSlots >= kWaves ? kSlots / kWaves : 1;   // tiles a wave finishes
+  static constexpr int kPass = kPer < 2 ? kPer : 2;        // of them per pass
+  static constexpr int kOwners = kSlots / kPer;
+  static constexpr int kRed = kOwners * kPass * (kWaves - 1) * 256;
+  static constexpr int kDesc = kBt * 4;
+  static constexpr int kMain = kDescOff + kDesc;
+  static constexpr int kFlagOff = kMain > kRed ? kMain : kRed;
+  static constexpr int kLds = kFlagOff + kBt;
+  // register sets of weights: one wave's L2 latency is behind as many output tiles
+  static constexpr int kSets = kTiles == 4 ? 3 : 6;
+  static constexpr int kRowAll = kBt * kRowChunks;         // chunks per row
+  static constexpr int kRowPer = (kRowAll + kThreads - 1) / kThreads;
+  static_assert(kLds * 4 <= 160 * 1024 && kPer % kPass == 0 && kQ * kMT % kSets == 0 && kRowAll % 64 == 0, "block");
 };
 
-__device__ __forceinline__ floatx4 mfma4(float a, float b, const floatx4& c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+// a == high + middle + low exactly, each a bf16 value in the upper half of its
+// word: the significand cut after 8 and 16 bits.  (Infinity gives NaN parts.)
+__device__ __forceinline__ void cut3(float a, uint32_t& h, uint32_t& m, uint32_t& l) {
+  h = __float_as_uint(a) & 0xFFFF0000u;
+  const float r = a - __uint_as_float(h);
+  m = __float_as_uint(r) & 0xFFFF0000u;
+  l = __float_as_uint(r - __uint_as_float(m));
+}
+// the upper halves of a and b, a's in the low half
+__device__ __forceinline__ uint32_t uppers(uint32_t a, uint32_t b) {
+  return __builtin_amdgcn_perm(b, a, 0x07060302u);
+}
+__device__ __forceinline__ floatx4 mfma(const uint4& a, const uint4& b, const floatx4& c) {
+  return Op16<false>::mfma(a, b, c);
+}
+// c += a x b, the smallest products first
+__device__ __forceinline__ floatx4 mfma6(const uint4 (&a)[kParts3], const uint4 (&b)[kParts3], floatx4 c) {
+  c = mfma(a[2], b[0], c);
+  c = mfma(a[0], b[2], c);
+  c = mfma(a[1], b[1], c);
+  c = mfma(a[1], b[0], c);
+  c = mfma(a[0], b[1], c);
+  return mfma(a[0], b[0], c);
 }
 
-// One block: patches p_base .. p_base + 16 kTiles - 1 (those past the batch
-// hold zeros and are not stored), range `split`; kSets sets of 8 waves take
-// the groups set + g0, set + g0 + 2, ... (kSeq of them) one after the other.
-// `out` points at the sums of the block's first patch.
-template <int kTiles, int kSets, int kSeq>
-__device__ __forceinline__ void conv_fc1_f32_block(float* lds, int split, int g0, int64_t p_base,
-                                                   const HitSource& src,
-                                                   const float* __restrict__ conv_w,
-                                                   const float* __restrict__ conv_b,
-                                                   const float* __restrict__ w1f,
-                                                   float* __restrict__ out) {
-  using B = Block<kTiles, kSets>;
-  constexpr int kSlot = B::kSlot;
+// One block: patches p_base .. p_base + kBt - 1 (those past the batch hold
+// zeros and are not stored), range `split`, output part `opart`.
+template <int kTiles, int kParts>
+__device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int opart, int64_t p_base,
+                                                   const HitSource& src, const uint4* __restrict__ w1p,
+                                                   const uint4* __restrict__ convp, float* __restrict__ part) {
+  using B = Block<kTiles, kParts>;
+  constexpr int kSlot = B::kSlot, kMT = B::kMT, kSets = B::kSets, kBt = B::kBt;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int set = wave / kMTiles, m = wave % kMTiles;
   const int col = lane & 15, grp = lane >> 4;
-  const int P0 = kGroups * range_begin(split);
-  const int steps = range_begin(split + 1) - range_begin(split);
-  const int r0 = P0 / kPairsPerRow;                        // first input row of the range
-  const int nrows = (P0 + kGroups * steps - 1) / kPairsPerRow + kK - r0;
-  const int total = kSeq * steps;
-  // pair i of this wave's sequence
-  auto pair = [&](int i) {
-    const int ph = kSeq > 1 && i >= steps ? 1 : 0;
-    return P0 + kGroups * (i - ph * steps) + g0 + set + 2 * ph;
-  };
+  const int P0 = range_begin(split), P_end = range_begin(split + 1);
+  const int steps = (P_end - P0 + kWaves - 1) / kWaves;
 
-  // FC1 weights of this wave's outputs: one fragment per pair and K-step,
-  // reloaded for the next pair as soon as its MFMAs have issued (reads past the
-  // end return 0)
-  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<float*>(w1f), (short)0, (int)(sizeof(float) * kFc1Out * kFc1In), 0x00020000);
-  auto load_w = [&](int P, int q) {
-    return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
-                                           wr, lane * 16, ((P * kQ + q) * kMTiles + m) * 1024, 0));
-  };
-  floatx4 w[kQ];
+  // FC1 fragments through a buffer resource (reads past the end return 0):
+  // group G of a pair is K-step G / kMT, output tile G % kMT
+  const __amdgpu_buffer_rsrc_t w1r = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint4*>(w1p), (short)0, (int)(kParts3 * kFc1Frags * 16), 0x00020000);
+  const int voff = lane * 16 + opart * kMT * kParts3 * 1024;
+  auto load_set = [&](int P, int G, uint4 (&w)[kParts3]) {
 #pragma unroll
-  for (int q = 0; q < kQ; ++q) w[q] = load_w(pair(0), q);
+    for (int k = 0; k < kParts3; ++k)
+      w[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                           w1r, voff + k * 1024,
+                                           ((P * kQ + G / kMT) * kMTiles + G % kMT) * kParts3 * 1024, 0));
+  };
+  uint4 w[kSets][kParts3];
+#pragma unroll
+  for (int s = 0; s < kSets; ++s) load_set(P0 + wave, s, w[s]);
 
-  // The conv tiles (jobs) this wave computes of a pair, job = K-step * kTiles +
-  // patch tile.  2 patch tiles: job m always, and of jobs 8-11 one in every
-  // other pair (waves 0-3 and 4-7 in turn); 1 patch tile: waves 0-5 and 7-2 in
-  // turn.  Waves w and w + 4 share a SIMD: each SIMD computes as many.
-  auto job_of = [&](int odd, int k) {        // k-th job of an even / odd pair, or -1
-    if (kTiles == 2) {
-      if (k == 0) return m;
-      return (m < 4) == (odd == 0) ? 8 + m % 4 : -1;
-    }
-    if (k == 1) return -1;
-    return odd == 0 ? (m < kQ ? m : -1) : (m >= kMTiles - kQ ? kMTiles - 1 - m : -1);
-  };
-  // Their filters, lane (channel 16t + col, K-slot group grp), MFMA i.  Two
-  // sets: 2 patch tiles, the first and the second job; 1, even and odd pairs.
-  float filt[2][8];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int job = kTiles == 2 ? (k == 0 ? m : 8 + m % 4) : job_of(k, 0);
-    const int q = job < 0 ? 0 : job / kTiles, s = q / 3, ch = 16 * (q % 3) + col;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int f = 4 * i + grp, u = f / 6, c = f - 6 * (f / 6) - s;
-      float v = 0.f;
-      if (f < 30 && c >= 0 && c < kK) v = conv_w[ch * kK * kK + u * kK + c];
-      if (f == 30) v = conv_b[ch];
-      filt[k][i] = v;
-    }
+  // ---- patch rows
+  uint4* desc = reinterpret_cast<uint4*>(lds + B::kDescOff);
+  uint32_t* flags = lds + B::kFlagOff;       // patches with an infinite pixel
+  if (tid < kBt) {
+    desc[tid] = src.get(p_base + tid);
+    flags[tid] = 0;
   }
-
-  // ---- every input row of the range, all loads in flight together
-  {
-    uint4* desc = reinterpret_cast<uint4*>(lds + B::kDescOff);
-    if (tid < B::kBt) desc[tid] = src.get(p_base + tid);
-    __syncthreads();
-    const int chunks = nrows * B::kRowAll;
-    rowx4 v[B::kPer];
-    uint32_t kinds = 0;                      // 2 bits per chunk
+  uint4* filters = reinterpret_cast<uint4*>(lds + B::kConvOff);
+  for (int i = tid; i < kParts3 * 6 * 64; i += kThreads) filters[i] = convp[i];
+  __syncthreads();
+  struct Row {
+    rowx4 v[B::kRowPer];
+    uint32_t kinds;
+  };
+  auto load_row = [&](int r, Row& row) {
+    row.kinds = 0;
 #pragma unroll
-    for (int k = 0; k < B::kPer; ++k) {
-      const int c = tid + k * B::kThreads;
-      if (c < chunks) {
-        const int j = c / B::kRowAll, cc = c - j * B::kRowAll;
+    for (int k = 0; k < B::kRowPer; ++k) {
+      const int c = tid + k * kThreads;
+      if (c < B::kRowAll) {
         uint32_t kind;
-        v[k] = row_chunk_load(desc_from_lds(desc + cc / kRowChunks), r0 + j,
-                              cc - (cc / kRowChunks) * kRowChunks, w1f, &kind);
-        kinds |= kind << 2 * k;
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < B::kPer; ++k) {
-      const int c = tid + k * B::kThreads;
-      if (c < chunks) {
-        const int j = c / B::kRowAll, cc = c - j * B::kRowAll;
-        const int p = cc / kRowChunks, h = cc - (cc / kRowChunks) * kRowChunks;
-        const rowx4 x = row_chunk_finish(desc + p, r0 + j, h, v[k], (kinds >> 2 * k) & 3);
-        *reinterpret_cast<rowx4*>(lds + j * kSlot + p * kRP + 4 * h) = x;
-      }
-    }
-  }
-  __syncthreads();
-
-  // this lane's window pixels: slot f = 4i + grp of patch col
-  int woff[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    int f = 4 * i + grp;
-    if (f > 29) f = 29;                      // slots 30-31 are constants (set below)
-    woff[i] = f / 6 * kSlot + f % 6 + col * kRP;
-  }
-  auto read_win = [&](int P, int tile, float (&win)[8]) {
-    const int y = P / kPairsPerRow;
-    const int base = (y - r0) * kSlot + 2 * (P - y * kPairsPerRow) + tile * 16 * kRP;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) win[i] = lds[base + woff[i]];
-    if (grp >= 2) win[7] = grp == 2 ? 1.f : 0.f;
-  };
-  auto conv = [&](const float (&fr)[8], const float (&win)[8]) {
-    floatx4 c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < 8; ++i) c = mfma4(fr[i], win[i], c);
-    return (floatx4){fmaxf(c[0], 0.f), fmaxf(c[1], 0.f), fmaxf(c[2], 0.f), fmaxf(c[3], 0.f)};
-  };
-  floatx4* maps = reinterpret_cast<floatx4*>(lds + B::kMapOff) + set * 2 * (B::kMapBuf / 4) + lane;
-  auto map_at = [&](int buf, int job) { return maps + (buf * kQ * kTiles + job) * 64; };
-
-  // the jobs of the first pair
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int job = job_of(0, k);
-    if (job >= 0) {
-      float win[8];
-      read_win(pair(0), job % kTiles, win);
-      *map_at(0, job) = conv(filt[kTiles == 2 ? k : 0], win);
-    }
-  }
-  __syncthreads();
-
-  floatx4 acc[kTiles], sum[kTiles];
-#pragma unroll
-  for (int j = 0; j < kTiles; ++j) acc[j] = sum[j] = (floatx4){0.f, 0.f, 0.f, 0.f};
-
-  // One pair: its FC1, and the jobs of the next pair (`odd`: the next pair's
-  // parity) into the other buffer.
-  auto step = [&](int i, auto oddc) {
-    constexpr int odd = decltype(oddc)::value;
-    const int Pn = pair(i + 1);
-    const int job0 = job_of(odd, 0), job1 = job_of(odd, 1);
-    const bool more = i + 1 < total;
-    const bool do0 = more && job0 >= 0, do1 = more && job1 >= 0;   // wave-uniform
-    floatx4 b[kTiles][kQ];
-    auto get = [&](int q) {
-#pragma unroll
-      for (int j = 0; j < kTiles; ++j) b[j][q] = *map_at(odd ^ 1, q * kTiles + j);
-    };
-    auto fc1 = [&](int q) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int j = 0; j < kTiles; ++j) acc[j] = mfma4(w[q][e], b[j][q][e], acc[j]);
-      w[q] = load_w(Pn, q);
-    };
-    float win[8];
-    get(0);
-    get(1);
-    if (do0) read_win(Pn, job0 % kTiles, win);
-    fc1(0);
-    get(2);
-    get(3);
-    if (do0) *map_at(odd, job0) = conv(filt[kTiles == 2 ? 0 : odd], win);
-    fc1(1);
-    if (kTiles == 2 && do1) read_win(Pn, job1 % kTiles, win);
-    fc1(2);
-    get(4);
-    get(5);
-    if (kTiles == 2 && do1) *map_at(odd, job1) = conv(filt[1], win);
-    fc1(3);
-    fc1(4);
-    fc1(5);
-    __syncthreads();
-  };
-  // the second group of a set starts with fresh accumulators
-  auto next_group = [&](int i) {
-    if (kSeq > 1 && i == steps) {
-#pragma unroll
-      for (int j = 0; j < kTiles; ++j) {
-        sum[j] = acc[j];
-        acc[j] = (floatx4){0.f, 0.f, 0.f, 0.f};
+        row.v[k] = row_chunk_load(desc_from_lds(desc + c / kRowChunks), r, c - (c / kRowChunks) * kRowChunks,
+                                  w1p, &kind);
+        row.kinds |= kind << 2 * k;
       }
     }
   };
-  int i = 0;
+  auto store_row = [&](int r, const Row& row) {
+#pragma unroll
+    for (int k = 0; k < B::kRowPer; ++k) {
+      const int c = tid + k * kThreads;
+      if (c < B::kRowAll) {
+        const int p = c / kRowChunks, h = c - (c / kRowChunks) * kRowChunks;
+        const rowx4 x = row_chunk_finish(desc + p, r, h, row.v[k], (row.kinds >> 2 * k) & 3);
+        uint32_t hi[4], mi[4], lo[4];
+        bool inf = false;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          cut3(x[j], hi[j], mi[j], lo[j]);
+          inf |= (__float_as_uint(x[j]) << 1) == 0xFF000000u;
+        }
+        if (inf) flags[p] = 1;
+        uint32_t* d = lds + r % kRing * kSlot + p * kRP + h * 2;
+        *reinterpret_cast<uint2*>(d) = make_uint2(uppers(hi[0], hi[1]), uppers(hi[2], hi[3]));
+        *reinterpret_cast<uint2*>(d + B::kPart) = make_uint2(uppers(mi[0], mi[1]), uppers(mi[2], mi[3]));
+        *reinterpret_cast<uint2*>(d + 2 * B::kPart) = make_uint2(uppers(lo[0], lo[1]), uppers(lo[2], lo[3]));
+      }
+    }
+  };
+  auto top_row = [&](int step) {             // highest input row a step needs
+    const int pl = P0 + kWaves * step + kWaves - 1;
+    return (pl < P_end ? pl : P_end - 1) / kPairsPerRow + kK - 1;
+  };
+  int loaded = top_row(0);
+  {
+    const int r0 = P0 / kPairsPerRow;
+    Row row[kRing];
+#pragma unroll
+    for (int j = 0; j < kRing; ++j)
+      if (r0 + j <= loaded) load_row(r0 + j, row[j]);
+#pragma unroll
+    for (int j = 0; j < kRing; ++j)
+      if (r0 + j <= loaded) store_row(r0 + j, row[j]);
+  }
+
+  // this lane's 4 window dwords: slots f, f + 1 (f = 8 grp + 2d) are pixels
+  // (u, c), (u, c + 1); a place in the ring from row y % kRing on
+  int woff[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    int f = 8 * grp + 2 * d;
+    if (f > 28) f = 28;                      // slots 30-31 are constants (set below)
+    woff[d] = f / 6 * kSlot + (f % 6) / 2 + col * kRP;
+  }
+  const bool const_slot = grp == 3;
+
+  floatx4 acc[kMT][kTiles];
+#pragma unroll
+  for (int m = 0; m < kMT; ++m)
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i) acc[m][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+  __syncthreads();                           // the first rows and the filters
+
 #pragma unroll 1
-  for (; i + 1 < total; i += 2) {
-    next_group(i);
-    step(i, std::integral_constant<int, 1>{});
-    next_group(i + 1);
-    step(i + 1, std::integral_constant<int, 0>{});
-  }
-  if (i < total) {
-    next_group(i);
-    step(i, std::integral_constant<int, 1>{});
+  for (int step = 0; step < steps; ++step) {
+    const int P = P0 + kWaves * step + wave;
+    const bool new_row = step + 1 < steps && top_row(step + 1) > loaded;   // block-uniform
+    Row row;
+    if (P < P_end) {                         // (the last step of a range can be half a step)
+      const int y = P / kPairsPerRow;
+      const uint32_t at = (uint32_t)(y % kRing * kSlot), xh = (uint32_t)(P - y * kPairsPerRow);
+      uint32_t base[4];
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const uint32_t t = (uint32_t)woff[d] + at;
+        base[d] = min(t, t - (uint32_t)(kRing * kSlot)) + xh;   // wrapped
+      }
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) {
+        // conv tiles (shift, channel tile) of K-step q, see conv_fc1_16.hip
+        const int ta = (q == 2) ? 3 + 1 : (q == 1 ? 2 : 0), tb = (q == 0) ? 1 : (q == 1 ? 3 : 3 + 2);
+        uint4 b[kTiles][kParts3];
+#pragma unroll
+        for (int i = 0; i < kTiles; ++i) {
+          // (the fences keep the compiler from holding filters and windows of
+          // several tiles at a time: there are no registers for them)
+          asm volatile("" ::: "memory");
+          uint4 win[kParts3], f[kParts3];
+#pragma unroll
+          for (int k = 0; k < kParts3; ++k) {
+            const uint32_t* s = lds + k * B::kPart + i * 16 * kRP;
+            f[k] = filters[(k * 6 + ta) * 64 + lane];
+            win[k].x = s[base[0]];
+            win[k].y = s[base[1]];
+            win[k].z = s[base[2]];
+            win[k].w = s[base[3]];
+            asm volatile("" : "+v"(win[k].w));   // read by every lane: a select, not a branch
+            win[k].w = const_slot ? (k == 0 ? 0x00003F80u : 0u) : win[k].w;
+          }
+          const floatx4 z = {0.f, 0.f, 0.f, 0.f};
+          const floatx4 ca = mfma6(f, win, z);
+          asm volatile("" ::: "memory");
+#pragma unroll
+          for (int k = 0; k < kParts3; ++k) f[k] = filters[(k * 6 + tb) * 64 + lane];
+          const floatx4 cb = mfma6(f, win, z);
+          uint32_t h[8], m[8], l[8];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            cut3(fmaxf(ca[e], 0.f), h[e], m[e], l[e]);
+            cut3(fmaxf(cb[e], 0.f), h[4 + e], m[4 + e], l[4 + e]);
+          }
+          b[i][0] = make_uint4(uppers(h[0], h[1]), uppers(h[2], h[3]), uppers(h[4], h[5]), uppers(h[6], h[7]));
+          b[i][1] = make_uint4(uppers(m[0], m[1]), uppers(m[2], m[3]), uppers(m[4], m[5]), uppers(m[6], m[7]));
+          b[i][2] = make_uint4(uppers(l[0], l[1]), uppers(l[2], l[3]), uppers(l[4], l[5]), uppers(l[6], l[7]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // the next row's loads: behind this K-step's FC1
+        if (q == kQ - 1 && new_row) load_row(loaded + 1, row);
+#pragma unroll
+        for (int m = 0; m < kMT; ++m) {
+          constexpr int kAll = kQ * kMT;
+          const int G = q * kMT + m, s = G % kSets;
+#pragma unroll
+          for (int i = 0; i < kTiles; ++i) acc[m][i] = mfma6(w[s], b[i], acc[m][i]);
+          load_set(G + kSets < kAll ? P : P + kWaves, (G + kSets) % kAll, w[s]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    if (new_row) {
+      // the slot that the row takes held a row of this step
+      __syncthreads();
+      store_row(++loaded, row);
+      __syncthreads();
+    }
   }
 
-  // ---- fixed-order sum of the groups: (g0 + g2) + (g1 + g3)
+  // ---- fixed-order sum over the waves, each finishing its share of the tiles:
+  //      ((g0 + g4) + (g1 + g5)) + ((g2 + g6) + (g3 + g7))
+  constexpr int kPer = B::kPer, kPass = B::kPass, kOwners = B::kOwners;
+  constexpr int kStride = kWaves / kOwners;                // owner o is wave o * kStride
+  floatx4* red = reinterpret_cast<floatx4*>(lds);
+  float* dst = part + ((int64_t)split * src.n + p_base) * kFc1Out;
+  auto entry = [&](int o, int j, int from) { return ((o * kPass + j) * (kWaves - 1) + from) * 64 + lane; };
 #pragma unroll
-  for (int j = 0; j < kTiles; ++j) acc[j] = kSeq > 1 ? sum[j] + acc[j] : acc[j];
-  if constexpr (kSets > 1) {
-    floatx4* red = reinterpret_cast<floatx4*>(lds);        // the rows are dead
-    if (set == 1)
+  for (int j0 = 0; j0 < kPer; j0 += kPass) {
+    __syncthreads();                         // the ring, or the last pass, is dead
 #pragma unroll
-      for (int j = 0; j < kTiles; ++j) red[(m * kTiles + j) * 64 + lane] = acc[j];
+    for (int k = 0; k < kOwners * kPass; ++k) {
+      const int o = k / kPass, j = k % kPass, q = o * kPer + j0 + j, g = o * kStride;
+      if (wave != g) red[entry(o, j, wave - (wave > g ? 1 : 0))] = acc[q / kTiles][q % kTiles];
+    }
     __syncthreads();
-    if (set == 1) return;
 #pragma unroll
-    for (int j = 0; j < kTiles; ++j) acc[j] = acc[j] + red[(m * kTiles + j) * 64 + lane];
-  }
-  // outputs 16m + 4 grp + e of patch 16 j + col
+    for (int k = 0; k < kOwners * kPass; ++k) {
+      const int o = k / kPass, j = k % kPass, q = o * kPer + j0 + j, g0 = o * kStride;
+      if (wave == g0) {
+        floatx4 v[kWaves];
 #pragma unroll
-  for (int j = 0; j < kTiles; ++j) {
-    const int p = 16 * j + col;
-    if (p_base + p < src.n)
-      __builtin_nontemporal_store(acc[j], reinterpret_cast<floatx4*>(out + p * kFc1Out + 16 * m + 4 * grp));
+        for (int g = 0; g < kWaves; ++g)
+          v[g] = g == g0 ? acc[q / kTiles][q % kTiles] : red[entry(o, j, g - (g > g0 ? 1 : 0))];
+        floatx4 sum = ((v[0] + v[4]) + (v[1] + v[5])) + ((v[2] + v[6]) + (v[3] + v[7]));
+        const int p = 16 * (q % kTiles) + col, out = 16 * (opart * kMT + q / kTiles) + 4 * grp;
+        // an infinite pixel: its maps are infinite, and their FC1 sums NaN (the
+        // parts of an infinity would leave no trace behind the ReLU)
+        if (flags[p]) sum = (floatx4){__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+        if (p_base + p < src.n) __builtin_nontemporal_store(sum, reinterpret_cast<floatx4*>(dst + p * kFc1Out + out));
+      }
+    }
   }
 }
 
-// Tiles t < n_big hold 32 patches, the ones after them 16; block b takes range
-// b % 8 (one per XCD, whose L2 the blocks that run on it share for the weights).
-__global__ __launch_bounds__(2 * kSet, 1) void conv_fc1_f32_kernel(
-    HitSource src, int64_t n_big, const float* __restrict__ conv_w, const float* __restrict__ conv_b,
-    const float* __restrict__ w1f, float* __restrict__ part) {
-  __shared__ __attribute__((aligned(16))) float lds[Block<2, 2>::kLds];
-  const int split = blockIdx.x % kSplits;
+// Tiles t < n_big hold 64 patches, the ones after them 32.  Block b runs on XCD
+// b % 8, whose L2 the blocks there share for their range's weights; the ranges
+// move on by one XCD every 32 tiles (a round of 256 CUs), because two of the
+// eight are 3 % longer.
+__global__ __launch_bounds__(kThreads, 1) void conv_fc1_f32_kernel(HitSource src, int64_t n_big,
+                                                                   const uint4* __restrict__ w1p,
+                                                                   const uint4* __restrict__ convp,
+                                                                   float* __restrict__ part) {
+  __shared__ __attribute__((aligned(16))) uint32_t lds[Block<4, 1>::kLds];
   const int64_t t = blockIdx.x / kSplits;
-  const int64_t p = t < n_big ? t * 32 : n_big * 32 + (t - n_big) * 16;
-  float* out = part + ((int64_t)split * src.n + p) * kFc1Out;
+  const int split = (int)((blockIdx.x + t / 32) % kSplits);
   if (t < n_big)
-    conv_fc1_f32_block<2, 2, 2>(lds, split, 0, p, src, conv_w, conv_b, w1f, out);
+    conv_fc1_f32_block<4, 1>(lds, split, 0, t * 64, src, w1p, convp, part);
   else
-    conv_fc1_f32_block<1, 2, 2>(lds, split, 0, p, src, conv_w, conv_b, w1f, out);
+    conv_fc1_f32_block<2, 1>(lds, split, 0, n_big * 64 + (t - n_big) * 32, src, w1p, convp, part);
 }
 
-// Small batches: a block per 16 patches, range and group; the sums of range s
-// and group g go to part[4 s + g].
-__global__ __launch_bounds__(kSet, 2) void conv_fc1_f32_small_kernel(
-    HitSource src, const float* __restrict__ conv_w, const float* __restrict__ conv_b,
-    const float* __restrict__ w1f, float* __restrict__ part) {
-  __shared__ __attribute__((aligned(16))) float lds[Block<1, 1>::kLds];
-  const int split = blockIdx.x % kSplits, g = blockIdx.x / kSplits % kGroups;
-  const int64_t p = (int64_t)(blockIdx.x / (kSplits * kGroups)) * 16;
-  conv_fc1_f32_block<1, 1, 1>(lds, split, g, p, src, conv_w, conv_b, w1f,
-                              part + ((int64_t)(split * kGroups + g) * src.n + p) * kFc1Out);
+// Block b: split b % kSplits, then output part, then patch tile.
+template <int kTiles, int kParts>
+__global__ __launch_bounds__(kThreads, 1) void conv_fc1_f32_small_kernel(HitSource src,
+                                                                         const uint4* __restrict__ w1p,
+                                                                         const uint4* __restrict__ convp,
+                                                                         float* __restrict__ part) {
+  __shared__ __attribute__((aligned(16))) uint32_t lds[Block<kTiles, kParts>::kLds];
+  const int split = blockIdx.x % kSplits;
+  const int64_t r = blockIdx.x / kSplits;
+  conv_fc1_f32_block<kTiles, kParts>(lds, split, (int)(r % kParts), r / kParts * (16 * kTiles), src, w1p, convp,
+                                     part);
+}
+
+// The parts of a weight: rounded to nearest (their products' rest is then of
+// either sign), cut where that would round a finite weight to infinity.
+__device__ __forceinline__ void round3(float v, float (&out)[kParts3]) {
+#pragma unroll
+  for (int k = 0; k < kParts3; ++k) {
+    float h = Op16<false>::value((uint16_t)Op16<false>::pack(v, 0.f));
+    if (isinf(h)) h = __uint_as_float(__float_as_uint(v) & 0xFFFF0000u);
+    out[k] = h;
+    v = isfinite(v) ? v - h : 0.f;
+  }
+}
+__device__ __forceinline__ void store3(const float (&v)[8], uint4* out, int stride) {
+  float p[8][kParts3];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) round3(v[j], p[j]);
+  using Op = Op16<false>;
+#pragma unroll
+  for (int k = 0; k < kParts3; ++k)          // (every part is a bf16 value: packing is exact)
+    out[k * stride] = make_uint4(Op::pack(p[0][k], p[1][k]), Op::pack(p[2][k], p[3][k]),
+                                 Op::pack(p[4][k], p[5][k]), Op::pack(p[6][k], p[7][k]));
 }
 
 // FC1 weights in the order the kernel reads them, once at create: one thread
 // per (pair, K-step, 16 outputs, lane (output i, K-slot group g)).
-__global__ __launch_bounds__(256) void pack_fc1_f32_kernel(const float* __restrict__ w1,
-                                                           floatx4* __restrict__ out) {
+__global__ __launch_bounds__(256) void pack_fc1_f32_kernel(const float* __restrict__ w1, uint4* __restrict__ out) {
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (int64_t)kPairs * kQ * kMTiles * 64) return;
-  const int lane = (int)(idx & 63), m = (int)(idx >> 6) % kMTiles;
-  const int64_t pq = idx >> 9;
-  const int q = (int)(pq % kQ);
-  const int64_t k = (2 * (pq / kQ) + q / 3) * kCh + 16 * (q % 3) + 4 * (lane >> 4);
-  const int o = 16 * m + (lane & 15);
-  out[idx] = (floatx4){w1[k * kFc1Out + o], w1[(k + 1) * kFc1Out + o], w1[(k + 2) * kFc1Out + o],
-                       w1[(k + 3) * kFc1Out + o]};
+  if (idx >= kFc1Frags) return;
+  const int lane = (int)(idx & 63);
+  const int64_t f = idx >> 6;
+  const int m = (int)(f % kMTiles), q = (int)(f / kMTiles % kQ);
+  const int64_t P = f / (kMTiles * kQ);
+  float v[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int st = 2 * q + (j >> 2);         // conv tile: shift st / 3, channel tile st % 3
+    const int64_t k = (2 * P + st / 3) * kCh + 16 * (st % 3) + 4 * (lane >> 4) + (j & 3);
+    v[j] = w1[k * kFc1Out + 16 * m + (lane & 15)];
+  }
+  store3(v, out + f * kParts3 * 64 + lane, 64);
+}
+
+// The conv filters [part][shift][channel tile][64 lanes], slot 30 the bias.
+__global__ __launch_bounds__(64) void pack_conv_f32_kernel(const float* __restrict__ K, const float* __restrict__ b,
+                                                           uint4* __restrict__ out) {
+  const int st = blockIdx.x, s = st / 3, lane = threadIdx.x;
+  const int ch = 16 * (st % 3) + (lane & 15);
+  float v[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int f = 8 * (lane >> 4) + j, u = f / 6, c = f % 6 - s;
+    v[j] = f == 30 ? b[ch] : (f < 30 && c >= 0 && c < kK) ? K[ch * kK * kK + u * kK + c] : 0.f;
+  }
+  store3(v, out + st * 64 + lane, 6 * 64);
 }
 
 }  // namespace
 
-// Position groups whose sums a launch over n patches leaves to the tail: 4 for
-// small batches, 1 else.  In units of one group of one 16-patch tile on a CU,
-// the small kernel takes a unit per block, the others 4 (16 patches) and 8
-// (32 patches) per round of the CUs, one block each.
-int conv_fc1_f32_groups(int64_t n, int cus) {
-  const int64_t tiles = (n + 15) / 16;
-  if (tiles > 64) return 1;
-  auto rounds = [&](int64_t blocks) { return (blocks + cus - 1) / cus; };
-  const int64_t small = rounds(tiles * kSplits * kGroups);
-  const int64_t one = 4 * rounds(tiles * kSplits), two = 8 * rounds((tiles + 1) / 2 * kSplits);
-  return small < (one < two ? one : two) ? kGroups : 1;
-}
 int conv_fc1_f32_splits() { return kSplits; }
 
-// Tiles of 32 patches fill whole rounds of the CUs (one block per CU); the
-// rest is cut into tiles of 16 when those fit in one round.
+// Small batches: patches per block and output parts, (0, 0) past 512 patches
+// on 256 CUs.  The shapes whose blocks fit one round of the CUs, by the time of
+// a K-step in the block (two waves per SIMD, 16 cycles per MFMA; 3 KiB of
+// weights per wave and output tile at 64 B per clock and CU, whichever is
+// longer): 16 patches, a quarter of the outputs 770 cycles; 32 patches, a
+// quarter 1,540, half 2,300; 32 patches and all outputs 3,840 (the blocks of
+// the other kernel).
+void conv_fc1_f32_small(int64_t n, int cus, int* tiles, int* parts) {
+  const int64_t per_round = cus >= kSplits ? cus / kSplits : 1;
+  *tiles = *parts = 0;
+  if ((n + 15) / 16 * 4 <= per_round) {
+    *tiles = 1;
+    *parts = 4;
+  } else if ((n + 31) / 32 * 4 <= per_round) {
+    *tiles = 2;
+    *parts = 4;
+  } else if ((n + 31) / 32 * 2 <= per_round) {
+    *tiles = 2;
+    *parts = 2;
+  }
+}
+
+// Tiles of 64 patches fill whole rounds of the CUs (one block per CU); the
+// rest is cut into tiles of 32 when those fit in one round, which then takes
+// about half as long.
 void conv_fc1_f32_tiles(int64_t n, int cus, int64_t* n_big, int64_t* n_small) {
   const int64_t per_round = cus >= kSplits ? cus / kSplits : 1;     // tiles per round
-  int64_t big = n / (32 * per_round) * per_round;
-  const int64_t rest = n - big * 32;
-  int64_t small = (rest + 15) / 16;
+  int64_t big = n / (64 * per_round) * per_round;
+  const int64_t rest = n - big * 64;
+  int64_t small = (rest + 31) / 32;
   if (small > per_round) {
-    big += (rest + 31) / 32;
+    big += (rest + 63) / 64;
     small = 0;
   }
   *n_big = big;
   *n_small = small;
 }
 
-hipError_t launch_pack_fc1_f32(const float* w1, float* w1f, hipStream_t stream) {
-  const int64_t threads = (int64_t)kPairs * kQ * kMTiles * 64;
-  static_assert(kPairs * kQ * kMTiles * 64 * 4 == kFc1In * kFc1Out, "every weight once");
-  return launch_kernel(pack_fc1_f32_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream,
-                       w1, reinterpret_cast<floatx4*>(w1f));
+hipError_t launch_pack_f32(const float* conv_w, const float* conv_b, const float* fc1_w, uint4* conv_frag,
+                           uint4* fc1_frag, hipStream_t stream) {
+  const hipError_t e = launch_kernel(pack_conv_f32_kernel, dim3(6), dim3(64), 0, stream, conv_w, conv_b, conv_frag);
+  if (e != hipSuccess) return e;
+  return launch_kernel(pack_fc1_f32_kernel, dim3((unsigned)((kFc1Frags + 255) / 256)), dim3(256), 0, stream, fc1_w,
+                       fc1_frag);
 }
 
-hipError_t launch_conv_fc1_f32(const RowInput& in, int64_t n, const float* conv_w, const float* conv_b,
-                               const float* w1f, float* part, int cus, hipStream_t stream) {
+hipError_t launch_conv_fc1_f32(const RowInput& in, int64_t n, const uint4* w1p, const uint4* convp, float* part,
+                               int cus, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
   const HitSource src = hit_source(in, n);
-  if (conv_fc1_f32_groups(n, cus) > 1)
-    return launch_kernel(conv_fc1_f32_small_kernel, dim3((unsigned)((n + 15) / 16 * kSplits * kGroups)),
-                         dim3(kSet), 0, stream, src, conv_w, conv_b, w1f, part);
+  int tiles = 0, parts = 0;
+  conv_fc1_f32_small(n, cus, &tiles, &parts);
+  if (tiles) {
+    const dim3 grid((unsigned)((n + 16 * tiles - 1) / (16 * tiles) * parts * kSplits));
+    auto go = [&](auto kernel) { return launch_kernel(kernel, grid, dim3(kThreads), 0, stream, src, w1p, convp, part); };
+    if (tiles == 1) return go(conv_fc1_f32_small_kernel<1, 4>);
+    return parts == 4 ? go(conv_fc1_f32_small_kernel<2, 4>) : go(conv_fc1_f32_small_kernel<2, 2>);
+  }
   int64_t n_big = 0, n_small = 0;
   conv_fc1_f32_tiles(n, cus, &n_big, &n_small);
-  return launch_kernel(conv_fc1_f32_kernel, dim3((unsigned)((n_big + n_small) * kSplits)), dim3(2 * kSet), 0,
-                       stream, src, n_big, conv_w, conv_b, w1f, part);
+  return launch_kernel(conv_fc1_f32_kernel, dim3((unsigned)((n_big + n_small) * kSplits)), dim3(kThreads), 0, stream,
+                       src, n_big, w1p, convp, part);
 }
 
 }  // namespace pointid

@@ -92,7 +92,6 @@ struct DeviceWeights {
   int precision;             // POINTID_FP32 / POINTID_BF16 / POINTID_FP16 / POINTID_FP8
   const float* conv_w;       // [48][25] fp32
   const float* conv_b;       // [48]
-  const float* fc1_frag32;   // fp32 handles: [968 pairs][6 K-steps][8 output tiles][64 lanes] x 4
   const float* fc1_b;        // [128]
   const float* fc2_w;        // [128][32]
   const float* fc2_b;        // [32]
@@ -103,6 +102,8 @@ struct DeviceWeights {
   // 16-bit handles: MFMA operand fragments (see conv_fc1_16.hip)
   const uint4* conv_frag;    // [2 shifts][3 channel tiles][64 lanes] x 8 halves
   const uint4* fc1_frag;     // [968 pairs][3 K-steps][8 output tiles][64 lanes] x 8 halves
+  // fp32 handles (see conv_fc1_f32.hip): the same in three bf16 parts,
+  // conv_frag [part][shift][channel tile], fc1_frag [pair][K-step][output tile][part]
   // 8-bit handles (see conv_fc1_8.hip): e4m3 fragments [968 pairs][8 output
   // tiles] x (64 lanes x 16 B, then 64 lanes x 8 B), and the factor 2^-k_n
   // the tail multiplies FC1 output n's sums by (nullptr on other handles)
@@ -197,29 +198,29 @@ void conv_fc1_8_tiles(int64_t n, int cus, int64_t* n_big, int64_t* n_small);
 hipError_t launch_conv_fc1_8(const uint16_t* patches, int64_t n, int64_t row0, int64_t n_total,
                              const uint8_t* w1p, const uint4* convp, float* part, hipStream_t stream);
 
-// Fused fp32 conv + ReLU + FC1 on fp32 MFMA: fp32 patches or hits ->
-// part[s][i][128] for s < conv_fc1_f32_splits() x groups, from the conv filters
-// and biases and the packed FC1 weights.  groups = conv_fc1_f32_groups(n, cus):
-// 4 where the tail has to add the sums of each range's 4 position groups.
+// Fused conv + ReLU + FC1 of the fp32 path: fp32 patches or hits -> part[s][i][128]
+// for s < conv_fc1_f32_splits(), from the conv filters and FC1 weights in three
+// bf16 parts each (launch_pack_f32).
+constexpr int kF32Parts = 3;
 int conv_fc1_f32_splits();
-int conv_fc1_f32_groups(int64_t n, int cus);
-// Tiles of the fused fp32 launch for n patches on `cus` CUs (32 and 16 patches).
+// Tiles of the launch over n patches on `cus` CUs: n_big of 64 patches, then
+// n_small of 32; small batches instead run blocks of 16 * tiles patches and
+// 128 / parts outputs (tiles = 0: not a small batch).
 void conv_fc1_f32_tiles(int64_t n, int cus, int64_t* n_big, int64_t* n_small);
-hipError_t launch_conv_fc1_f32(const RowInput& in, int64_t n, const float* conv_w, const float* conv_b,
-                               const float* w1f, float* part, int cus, hipStream_t stream);
+void conv_fc1_f32_small(int64_t n, int cus, int* tiles, int* parts);
+hipError_t launch_conv_fc1_f32(const RowInput& in, int64_t n, const uint4* w1p, const uint4* convp, float* part,
+                               int cus, hipStream_t stream);
 
-// The fp32 FC1 weights in the order of that kernel.
-hipError_t launch_pack_fc1_f32(const float* w1, float* w1f, hipStream_t stream);
+hipError_t launch_pack_f32(const float* conv_w, const float* conv_b, const float* fc1_w, uint4* conv_frag,
+                           uint4* fc1_frag, hipStream_t stream);
 
 // Reduce the split-K partials in fixed order, then bias+ReLU, FC2+ReLU, the
-// softmax and sigmoid heads: scores [n][4].  groups (1 or 4): the partials are
-// those of each split's position groups, part[4 s + g], added as
-// (g0 + g2) + (g1 + g3) first.
-hipError_t launch_tail(const float* part, int splits, int groups, int64_t n,
+// softmax and sigmoid heads: scores [n][4].
+hipError_t launch_tail(const float* part, int splits, int64_t n,
                        const DeviceWeights& w, float* scores,
                        hipStream_t stream);
 // The same, with patch p's scores written to its request's output.
-hipError_t launch_tail_requests(const float* part, int splits, int groups, const DeviceWeights& w,
+hipError_t launch_tail_requests(const float* part, int splits, const DeviceWeights& w,
                                 const RequestTable& reqs, hipStream_t stream);
 
 // Hit finding (hits.hip).  The waveforms of all planes are cut into steps of

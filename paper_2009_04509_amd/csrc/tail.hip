@@ -56,8 +56,7 @@ struct RequestOut {
   }
 };
 
-// kGroups = 4: the partials of each split's position groups (small batches).
-template <class Out, int kGroups>
+template <class Out>
 __global__ __launch_bounds__(256) void tail_kernel(const float* __restrict__ part, int splits,
                                                    int64_t n, DeviceWeights w, Out out) {
   constexpr int kBlockRows = kRows;
@@ -81,29 +80,7 @@ __global__ __launch_bounds__(256) void tail_kernel(const float* __restrict__ par
     float4 acc[kBlockRows / 8];
 #pragma unroll
     for (int k = 0; k < kBlockRows / 8; ++k) acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if constexpr (kGroups > 1) {
-      // two splits' groups at a time: (g0 + g2) + (g1 + g3), then in split order
-      static_assert(kMaxSplits == 2 * kGroups && kBlockRows == 8, "8 loads in flight");
-      const bool live = p0 + r0 < n;
-      for (int s0 = 0; s0 < splits; s0 += 2) {
-        float4 v[kMaxSplits];
-#pragma unroll
-        for (int k = 0; k < kMaxSplits; ++k) {
-          const int64_t row = (int64_t)(s0 * kGroups + k) * n + p0 + r0;
-          v[k] = live && s0 + k / kGroups < splits
-                     ? reinterpret_cast<const float4*>(part + row * kFc1Out)[c4]
-                     : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-#pragma unroll
-        for (int k = 0; k < kMaxSplits; k += kGroups) {
-          add4(v[k], v[k + 2]);
-          add4(v[k + 1], v[k + 3]);
-          add4(v[k], v[k + 1]);
-          add4(acc[0], v[k]);
-        }
-      }
-    }
-    for (int s0 = 0; kGroups == 1 && s0 < splits; s0 += kMaxSplits) {
+    for (int s0 = 0; s0 < splits; s0 += kMaxSplits) {
       float4 v[kMaxSplits][kBlockRows / 8];
 #pragma unroll
       for (int s = 0; s < kMaxSplits; ++s) {
@@ -179,26 +156,22 @@ __global__ __launch_bounds__(256) void tail_kernel(const float* __restrict__ par
 
 }  // namespace
 
-template <class Out>
-hipError_t launch_tail_to(const float* part, int splits, int groups, int64_t n, const DeviceWeights& w,
-                          const Out& out, hipStream_t stream) {
-  if (n <= 0) return hipSuccess;
-  if (splits < 1 || (groups != 1 && groups != 4)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((n + kRows - 1) / kRows));
-  return groups == 1
-             ? launch_kernel(tail_kernel<Out, 1>, grid, dim3(256), 0, stream, part, splits, n, w, out)
-             : launch_kernel(tail_kernel<Out, 4>, grid, dim3(256), 0, stream, part, splits, n, w, out);
-}
-
-hipError_t launch_tail(const float* part, int splits, int groups, int64_t n, const DeviceWeights& w,
+hipError_t launch_tail(const float* part, int splits, int64_t n, const DeviceWeights& w,
                        float* scores, hipStream_t stream) {
-  return launch_tail_to(part, splits, groups, n, w, PlainOut{scores}, stream);
+  if (n <= 0) return hipSuccess;
+  if (splits < 1) return hipErrorInvalidValue;
+  return launch_kernel(tail_kernel<PlainOut>, dim3((unsigned)((n + kRows - 1) / kRows)), dim3(256), 0,
+                       stream, part, splits, n, w, PlainOut{scores});
 }
 
-hipError_t launch_tail_requests(const float* part, int splits, int groups, const DeviceWeights& w,
+hipError_t launch_tail_requests(const float* part, int splits, const DeviceWeights& w,
                                 const RequestTable& reqs, hipStream_t stream) {
   if (reqs.n < 1 || reqs.n > kMaxRequests) return hipErrorInvalidValue;
-  return launch_tail_to(part, splits, groups, reqs.start[reqs.n], w, RequestOut{reqs}, stream);
+  const int64_t n = reqs.start[reqs.n];
+  if (n <= 0) return hipSuccess;
+  if (splits < 1) return hipErrorInvalidValue;
+  return launch_kernel(tail_kernel<RequestOut>, dim3((unsigned)((n + kRows - 1) / kRows)), dim3(256), 0,
+                       stream, part, splits, n, w, RequestOut{reqs});
 }
 
 }  // namespace pointid

@@ -101,7 +101,8 @@ def test_large_batches_give_the_bits_of_small_ones(pid, handles, prec):
     """On a 256-CU device the 16-bit path runs 20,641 patches in blocks of four,
     two and one ranges of 96 patches and of 64, 7,000 in blocks of two and one,
     5,100 and 3,973 in blocks of two ranges of 64; the fp32 path runs batches
-    past 1,024 in tiles of 32 and 16 and smaller ones by position group."""
+    past 512 in tiles of 64 and 32 and smaller ones in tiles of 32 and 16 whose
+    outputs are shared out over 2 or 4 blocks."""
     h = handles[prec]
     P = t(synth.config4_patches(20641, seed=5))
     full = bits(pid.pointid_classify_patches(h, P))
@@ -109,3 +110,53 @@ def test_large_batches_give_the_bits_of_small_ones(pid, handles, prec):
                    (20000, 20641), (13000, 20000), (100, 5200), (16668, 20641), (500, 1900)]:
         say(f"{prec} patches {lo}:{hi}")
         assert np.array_equal(bits(pid.pointid_classify_patches(h, P[lo:hi].contiguous())), full[lo:hi]), (lo, hi)
+
+
+def test_fp32_block_shapes_at_their_edges(pid, handles):
+    """Batches on both sides of every change of the fp32 path's block shape on a
+    256-CU device (16 patches, a quarter of the outputs up to 128; 32 patches, a
+    quarter up to 256, half up to 512, all up to 1,024; then 64) give one set of bits."""
+    h = handles["fp32"]
+    P = t(synth.config4_patches(4200, seed=6))
+    full = bits(pid.pointid_classify_patches(h, P))
+    for n in (1, 15, 16, 17, 127, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 3072, 3073, 4096, 4097):
+        say(f"fp32 {n} patches")
+        for lo in (0, 4200 - n):
+            got = bits(pid.pointid_classify_patches(h, P[lo:lo + n].contiguous()))
+            assert np.array_equal(got, full[lo:lo + n]), (n, lo)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.0e38, 1e-30])
+def test_fp32_extreme_pixels(pid, handles, value):
+    """One extreme pixel per patch: an infinite one makes every FC1 sum NaN, which
+    the ReLU takes to 0 as it takes a NaN map value to 0; a finite one is an fp32
+    number like any other, to the last bit of its bf16 parts.  Against the
+    network in 64 bits, the tolerance that of the other fp32 tests."""
+    h = handles["fp32"]
+    w = {k: np.asarray(v, np.float64) for k, v in synth.he_normal_weights().items()}
+    P = synth.config4_patches(40, seed=7).astype(np.float32)
+    rng = np.random.default_rng(3)
+    for i in range(1, 40, 2):                            # every other patch keeps its own pixels
+        P[i, rng.integers(0, 48), rng.integers(0, 48)] = value
+    got = pid.pointid_classify_patches(h, t(P)).cpu().numpy()
+    X = P.astype(np.float64)
+    with np.errstate(all="ignore"):
+        cols = np.stack([X[:, u:u + 44, v:v + 44] for u in range(5) for v in range(5)], -1)
+        maps = np.fmax(cols @ w["conv_w"].reshape(48, 25).T + w["conv_b"], 0)
+        # (a pair of positions x, x + 1 shares a window of six columns, whose sixth
+        # pixel meets a tap of 0: 0 times NaN takes the other position with it)
+        pair = np.isnan(cols).any(-1).reshape(40, 44, 22, 2).any(-1).repeat(2, -1)
+        maps[pair] = 0
+        h1 = np.fmax(maps.reshape(40, -1) @ w["fc1_w"] + w["fc1_b"], 0)
+    if not np.isfinite(value):
+        assert np.isfinite(h1).all()
+    if np.isinf(value):
+        assert (h1[1::2] == 0).all()
+    if value == 3.0e38:                                  # past fp32's range further on: only the others
+        got, h1 = got[::2], h1[::2]
+    h2 = np.maximum(h1 @ w["fc2_w"] + w["fc2_b"], 0)
+    z = h2 @ w["cls_w"] + w["cls_b"].reshape(-1)
+    e = np.exp(z - z.max(1, keepdims=True))
+    q = h2 @ w["mic_w"].reshape(32, 1) + w["mic_b"].reshape(-1)
+    want = np.concatenate([e / e.sum(1, keepdims=True), 1 / (1 + np.exp(-q))], 1)
+    assert np.abs(got - want).max() <= 1e-4
