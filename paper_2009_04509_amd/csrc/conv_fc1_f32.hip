@@ -22,8 +22,7 @@
 // tiles that feed a K-step and the 3 K-steps of a pair are those of
 // conv_fc1_16.hip.  Per K-step a wave computes the conv of each 16-patch tile
 // (2 x 6 MFMAs), splits the ReLU'd maps into three FC1 operands in place, and
-// runs 6 MFMAs per output tile and patch tile, each accumulator's six back to
-// back.  The FC1 weights are packed at create, [pair][K-step][16 outputs][part]:
+// runs 6 MFMAs per output tile and patch tile, two accumulators' six in turn.  The FC1 weights are packed at create, [pair][K-step][16 outputs][part]:
 // a fragment feeds 2 MFMAs per patch tile, and a ring of register sets holds
 // the next few output tiles' fragments, each set reloaded as soon as its MFMAs
 // have issued.
@@ -105,14 +104,21 @@ __device__ __forceinline__ uint32_t uppers(uint32_t a, uint32_t b) {
 __device__ __forceinline__ floatx4 mfma(const uint4& a, const uint4& b, const floatx4& c) {
   return Op16<false>::mfma(a, b, c);
 }
-// c += a x b, the smallest products first
+// c += a x b, the smallest products first.  Two patch tiles take turns: an MFMA
+// would wait a few cycles for an accumulator written by the one just before.
+constexpr int kPartA[6] = {2, 0, 1, 1, 0, 0}, kPartB[6] = {0, 2, 1, 0, 1, 0};
 __device__ __forceinline__ floatx4 mfma6(const uint4 (&a)[kParts3], const uint4 (&b)[kParts3], floatx4 c) {
-  c = mfma(a[2], b[0], c);
-  c = mfma(a[0], b[2], c);
-  c = mfma(a[1], b[1], c);
-  c = mfma(a[1], b[0], c);
-  c = mfma(a[0], b[1], c);
-  return mfma(a[0], b[0], c);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) c = mfma(a[kPartA[k]], b[kPartB[k]], c);
+  return c;
+}
+__device__ __forceinline__ void mfma6x2(const uint4 (&a)[kParts3], const uint4 (&b0)[kParts3],
+                                        const uint4 (&b1)[kParts3], floatx4& c0, floatx4& c1) {
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    c0 = mfma(a[kPartA[k]], b0[kPartB[k]], c0);
+    c1 = mfma(a[kPartA[k]], b1[kPartB[k]], c1);
+  }
 }
 
 // One block: patches p_base .. p_base + kBt - 1 (those past the batch hold
@@ -247,12 +253,13 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
       for (int q = 0; q < kQ; ++q) {
         // conv tiles (shift, channel tile) of K-step q, see conv_fc1_16.hip
         const int ta = (q == 2) ? 3 + 1 : (q == 1 ? 2 : 0), tb = (q == 0) ? 1 : (q == 1 ? 3 : 3 + 2);
+        // The conv is a chain of LDS reads, MFMAs and conversions; a wave in it
+        // goes first, and the other wave of the SIMD fills its gaps with FC1
+        // (event, one box: 6.18 -> 6.01 ms, with the two chains in turn 5.96)
+        __builtin_amdgcn_s_setprio(2);
         uint4 b[kTiles][kParts3];
 #pragma unroll
         for (int i = 0; i < kTiles; ++i) {
-          // (the fences keep the compiler from holding filters and windows of
-          // several tiles at a time: there are no registers for them)
-          asm volatile("" ::: "memory");
           uint4 win[kParts3], f[kParts3];
 #pragma unroll
           for (int k = 0; k < kParts3; ++k) {
@@ -267,7 +274,6 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
           }
           const floatx4 z = {0.f, 0.f, 0.f, 0.f};
           const floatx4 ca = mfma6(f, win, z);
-          asm volatile("" ::: "memory");
 #pragma unroll
           for (int k = 0; k < kParts3; ++k) f[k] = filters[(k * 6 + tb) * 64 + lane];
           const floatx4 cb = mfma6(f, win, z);
@@ -282,6 +288,7 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
           b[i][2] = make_uint4(uppers(l[0], l[1]), uppers(l[2], l[3]), uppers(l[4], l[5]), uppers(l[6], l[7]));
         }
         __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(0);
         // the next row's loads: behind this K-step's FC1
         if (q == kQ - 1 && new_row) load_row(loaded + 1, row);
 #pragma unroll
@@ -289,7 +296,8 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
           constexpr int kAll = kQ * kMT;
           const int G = q * kMT + m, s = G % kSets;
 #pragma unroll
-          for (int i = 0; i < kTiles; ++i) acc[m][i] = mfma6(w[s], b[i], acc[m][i]);
+          for (int i = 0; i + 1 < kTiles; i += 2) mfma6x2(w[s], b[i], b[i + 1], acc[m][i], acc[m][i + 1]);
+          if constexpr (kTiles == 1) acc[m][0] = mfma6(w[s], b[0], acc[m][0]);
           load_set(G + kSets < kAll ? P : P + kWaves, (G + kSets) % kAll, w[s]);
           __builtin_amdgcn_sched_barrier(0);
         }
