@@ -377,15 +377,15 @@ int run_network_fp32(pointid_handle h, const RowInput& in, int64_t n, float* sco
   return run_tail(h, part, conv_fc1_f32_splits(), n, scores, stream, ws, reqs);
 }
 
-// 8-bit handles: fp16 patches [n][2304] -> scores.
-int run_network_8(pointid_handle h, const uint16_t* patches, int64_t n, float* scores, int cus,
+// 8-bit handles: patches or hits -> scores.
+int run_network_8(pointid_handle h, const RowInput& in, int64_t n, float* scores, int cus,
                   hipStream_t stream, Workspace& ws, const RequestTable* reqs = nullptr) {
   float* part = nullptr;
   hipError_t e = ws.get(part_bytes(h->precision, n), (void**)&part);
   if (e != hipSuccess) return hip_fail(e, "workspace (FC1 partials)");
   {
     KernelTimer kt("conv_fc1_8", stream);
-    e = launch_conv_fc1_8(patches, n, 0, n, h->w.fc1_frag8, h->w.conv_frag, part, stream);
+    e = launch_conv_fc1_8(in, n, h->w.fc1_frag8, h->w.conv_frag, part, cus, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "conv_fc1 launch");
   return run_tail(h, part, conv_fc1_8_splits(), n, scores, stream, ws, reqs);
@@ -430,11 +430,11 @@ int classify_table(pointid_handle h, const PlaneTable& planes, const RequestTabl
   int cus = 0;
   hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return hip_fail(e, "device attribute");
-  // The fp32 kernel, and the 16-bit kernel for batches that fill at most one
-  // round of thin tiles, take the hits themselves.  The 16-bit kernel's larger
-  // tiles read 16-bit patches from the gather: at the card's power limit the
-  // image reads cost them as much as the gather takes.
-  const bool direct = fp32 || (!fp8 && conv_fc1_16_thin_tile(n, cus));
+  // The fp32 kernel, and the others for batches that fill at most one round
+  // of thin tiles, take the hits themselves.  The larger tiles read 16-bit
+  // patches from the gather: at the card's power limit the image reads cost
+  // the 16-bit kernel as much as the gather takes.
+  const bool direct = fp32 || (fp8 ? conv_fc1_8_thin(n, cus) : conv_fc1_16_thin_tile(n, cus) != 0);
   e = ws.reserve((direct ? 0 : pad256(patch_bytes(n))) + pad256(part_bytes(h->precision, n)));
   if (e != hipSuccess) return hip_fail(e, "scratch buffer");
   RowInput in;
@@ -455,7 +455,7 @@ int classify_table(pointid_handle h, const PlaneTable& planes, const RequestTabl
     if (e != hipSuccess) return hip_fail(e, "gather launch");
     in.patches16 = static_cast<const uint16_t*>(patches);
   }
-  if (fp8) return run_network_8(h, in.patches16, n, scores, cus, stream, ws, out);
+  if (fp8) return run_network_8(h, in, n, scores, cus, stream, ws, out);
   return fp32 ? run_network_fp32(h, in, n, scores, cus, stream, ws, out)
               : run_network_16(h, in, n, scores, cus, stream, ws, out);
 }
@@ -942,16 +942,18 @@ int pointid_classify_patches(pointid_handle h, const float* patches, int64_t n,
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   DeviceScope dev(h->device);
   if (dev.error() != hipSuccess) return hip_fail(dev.error(), "hipSetDevice");
-  const bool fp8 = h->precision == POINTID_FP8;
   int cus = 0;
   hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return hip_fail(e, "device attribute");
+  // the 8-bit kernel's larger tiles take fp16 patches
+  const bool fp8 = h->precision == POINTID_FP8, cast = fp8 && !conv_fc1_8_thin(n, cus);
   Workspace ws(h->scratch, stream);
-  e = ws.reserve((fp8 ? pad256(patch_bytes(n)) : 0) + pad256(part_bytes(h->precision, n)));
+  e = ws.reserve((cast ? pad256(patch_bytes(n)) : 0) + pad256(part_bytes(h->precision, n)));
   if (e != hipSuccess) return hip_fail(e, "scratch buffer");
-  if (!fp8) {
-    RowInput in;
+  RowInput in;
+  if (!cast) {
     in.patches = patches;
+    if (fp8) return run_network_8(h, in, n, scores, cus, stream, ws);
     return h->precision == POINTID_FP32 ? run_network_fp32(h, in, n, scores, cus, stream, ws)
                                         : run_network_16(h, in, n, scores, cus, stream, ws);
   }
@@ -963,7 +965,8 @@ int pointid_classify_patches(pointid_handle h, const float* patches, int64_t n,
     e = launch_patches_to_16(true, patches, n, pb, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "16-bit cast launch");
-  return run_network_8(h, pb, n, scores, cus, stream, ws);
+  in.patches16 = pb;
+  return run_network_8(h, in, n, scores, cus, stream, ws);
 }
 
 int pointid_gather(const float* image, int32_t n_wires, int32_t n_ticks,

@@ -43,22 +43,16 @@
 #include "internal.h"
 #include "op16.h"
 #include "rows.h"
+#include "thin.h"
 
 namespace pointid {
 namespace {
 
-constexpr int kKGroups = 4;                   // position groups (interleaved pairs)
-constexpr int kNHalves = 2;                   // output halves
-constexpr int kWaves = kKGroups * kNHalves;   // 8
-constexpr int kThreads = kWaves * 64;         // 512
-constexpr int kMT = 8 / kNHalves;             // 16-output tiles per wave
 constexpr int kSplits16 = 8;                  // position ranges (split-K), one per XCD
-constexpr int kPairsPerRow = kFm / 2;         // 22
 constexpr int kRing = 8;                      // patch-row ring slots
 // rows the first steps of a range need: their pairs span at most two map rows,
 // plus the filter height
 constexpr int kPrologueRows = 2 + 5 - 1;
-constexpr int kRP = 26;                       // LDS row pitch, dwords (24 used)
 constexpr int kBigTile = 96;                  // patches per block (most blocks)
 constexpr int kMidTile = 64;                  // patches per block (the last rounds, some batches)
 
@@ -541,38 +535,6 @@ __global__ __launch_bounds__(kThreads, 1) void conv_fc1_16_kernel(
 // (each wave takes 4 / kParts of the 16-output tiles): more blocks, each
 // streaming a part of the position range's weights, for batches that would
 // leave CUs idle; every block computes the conv.
-constexpr int kThinRows = 11;                 // input rows of one position range, at most
-template <int kBt, int kParts>
-struct Thin {
-  static constexpr int kTiles = kBt / 16;
-  static constexpr int kMTw = kMT / kParts;                // 16-output tiles per wave
-  static constexpr int kSlot = kBt * kRP;                  // dwords per staged row
-  // the reduction: per output half, 3 tiles from the other groups per accumulator tile
-  static constexpr int kRed = kNHalves * kMTw * kTiles * (kKGroups - 1) * 4 * 64;
-  // one row slot more than a range needs: the loop reads the window of the
-  // pair after its last one (the result is never used), which may lie one row lower
-  static constexpr int kRowsDw = (kThinRows + 1) * kSlot;
-  static constexpr int kDescOff = kRowsDw;                 // the block's row descriptors
-  static constexpr int kMain = kDescOff + kBt * 4;
-  static constexpr int kLdsDwords = kMain > kRed ? kMain : kRed;
-  static constexpr int kRowAll = kBt * kRowChunks;         // 4-pixel chunks per staged row
-  static constexpr int kPer = (kThinRows * kRowAll + kThreads - 1) / kThreads;
-  static_assert(kTiles >= 1 && kTiles <= 2, "1 or 2 patch tiles");
-  static_assert(kParts == 1 || kParts == 2 || kParts == 4, "whole, half or quarter of the outputs");
-};
-
-// input rows a position range spans, at most, over the ranges of `splits`
-constexpr int thin_rows_needed(int splits) {
-  int most = 0;
-  for (int s = 0; s < splits; ++s) {
-    const int g0 = (kPos / 2 / kKGroups) * s / splits;
-    const int g1 = (kPos / 2 / kKGroups) * (s + 1) / splits;
-    const int rows = (kKGroups * g1 - 1) / kPairsPerRow + kK - (kKGroups * g0) / kPairsPerRow;
-    most = rows > most ? rows : most;
-  }
-  return most;
-}
-
 template <bool kFp16, int kSplits, int kBt, int kParts>
 __device__ __forceinline__ void thin_block(
     uint32_t* lds, int split, int opart, int64_t p_base, const HitSource& src,
@@ -620,38 +582,7 @@ __device__ __forceinline__ void thin_block(
 #pragma unroll
   for (int k = 0; k < 6; ++k) filt[k] = convp[k * 64 + lane];
 
-  // ---- every input row of the range, all loads in flight together
-  {
-    uint4* desc = reinterpret_cast<uint4*>(lds + T::kDescOff);
-    if (tid < kBt) desc[tid] = src.get(p_base + tid);
-    __syncthreads();
-    const int total = nrows * T::kRowAll;
-    rowx4 v[T::kPer];
-    uint32_t kinds = 0;                      // 2 bits per chunk
-    static_assert(2 * T::kPer <= 32, "kinds");
-#pragma unroll
-    for (int k = 0; k < T::kPer; ++k) {
-      const int c = tid + k * kThreads;
-      if (c < total) {
-        const int j = c / T::kRowAll, cc = c - j * T::kRowAll;
-        uint32_t kind;
-        v[k] = row_chunk_load(desc_from_lds(desc + cc / kRowChunks), r0 + j,
-                              cc - (cc / kRowChunks) * kRowChunks, w1p, &kind);
-        kinds |= kind << 2 * k;
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < T::kPer; ++k) {
-      const int c = tid + k * kThreads;
-      if (c < total) {
-        const int j = c / T::kRowAll, cc = c - j * T::kRowAll;
-        const int p = cc / kRowChunks, h = cc - (cc / kRowChunks) * kRowChunks;
-        const rowx4 x = row_chunk_finish(desc + p, r0 + j, h, v[k], (kinds >> 2 * k) & 3);
-        *reinterpret_cast<uint2*>(lds + j * kSlot + p * kRP + h * 2) =
-            make_uint2(Op::pack(x[0], x[1]), Op::pack(x[2], x[3]));
-      }
-    }
-  }
+  thin_stage<kFp16, kBt, kParts>(lds, p_base, src, r0, nrows, w1p);
 
   int woff[4], wrow[4];
 #pragma unroll
@@ -722,44 +653,7 @@ __device__ __forceinline__ void thin_block(
     }
   }
 
-  // ---- the fixed-order reduction of the tiles above: (g0 + g2) + (g1 + g3),
-  // each position group finishing a quarter of its output half's tiles, as in
-  // the tiles above (with 2 tiles per half groups 0 and 2 finish one each,
-  // with 1 group 0 finishes it)
-  __syncthreads();                           // every wave is done with the rows
-  constexpr int kSlots = kMTw * kTiles;
-  static_assert(kSlots % kKGroups == 0 || kKGroups % kSlots == 0, "tiles spread evenly");
-  // the position group that finishes slot q
-  constexpr auto owner = [](int q) {
-    return kSlots >= kKGroups ? q / (kSlots / kKGroups) : q * (kKGroups / kSlots);
-  };
-  floatx4* red = reinterpret_cast<floatx4*>(lds);
-  auto entry = [&](int q, int src) { return ((nh * kSlots + q) * (kKGroups - 1) + src) * 64 + lane; };
-  auto tile = [&](auto qc) -> floatx4& {
-    constexpr int q = decltype(qc)::value;
-    return acc[q / kTiles][q % kTiles];
-  };
-  static_for<kSlots>([&](auto qc) {
-    constexpr int o = owner(decltype(qc)::value);
-    if (kg != o) red[entry(decltype(qc)::value, kg - (kg > o ? 1 : 0))] = tile(qc);
-  });
-  __syncthreads();
-
-  float* dst = part + ((int64_t)split * n + p_base) * kFc1Out;
-  static_for<kSlots>([&](auto qc) {
-    constexpr int q = decltype(qc)::value, o = owner(q), m = q / kTiles, i = q % kTiles;
-    if (kg == o) {
-      floatx4 v[kKGroups];
-#pragma unroll
-      for (int g = 0; g < kKGroups; ++g)
-        v[g] = (g == o) ? tile(qc) : red[entry(q, g - (g > o ? 1 : 0))];
-      const floatx4 sum = (v[0] + v[2]) + (v[1] + v[3]);
-      const int64_t po = (int64_t)i * 16 + col;
-      const int out = 16 * (ot0 + m) + 4 * grp;
-      if (p_base + po < n)
-        __builtin_nontemporal_store(sum, reinterpret_cast<floatx4*>(dst + po * kFc1Out + out));
-    }
-  });
+  thin_reduce<kBt, kParts>(lds, acc, ot0, p_base, n, part + ((int64_t)split * n + p_base) * kFc1Out);
 }
 
 // Block b: split b % kSplits, then output part, then patch tile.

@@ -35,21 +35,15 @@
 // order and written as fp32 partials [split][patch][128], as in the fp16 kernel.
 #include "internal.h"
 #include "op16.h"
+#include "thin.h"
 
 namespace pointid {
 namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 
-constexpr int kKGroups = 4;                   // position groups (interleaved pairs)
-constexpr int kNHalves = 2;                   // output halves
-constexpr int kWaves = kKGroups * kNHalves;   // 8
-constexpr int kThreads = kWaves * 64;         // 512
-constexpr int kMT = 8 / kNHalves;             // 16-output tiles per wave
-constexpr int kPairsPerRow = kFm / 2;         // 22
 constexpr int kRing = 8;                      // patch-row ring slots
 constexpr int kPrologueRows = 2 + 5 - 1;      // rows of the first two steps
-constexpr int kRP = 26;                       // LDS row pitch, dwords (24 used)
 constexpr int kBigTile = 64;                  // patches per block (most blocks)
 constexpr int kSmallTile = 32;                // patches per block (the last ones)
 constexpr int kFrag8 = 1536;                  // bytes per (pair, output tile) fragment
@@ -82,7 +76,7 @@ static_assert(Tile8<kBigTile>::kLdsDwords >= Tile8<kSmallTile>::kLdsDwords, "LDS
 
 // Patch rows: 16 B chunks of fp16 patches; patches past the end of the batch
 // read the last patch (their results are never stored).
-__device__ __forceinline__ uint4 row_chunk_load(const uint16_t* __restrict__ patches, int64_t n,
+__device__ __forceinline__ uint4 patch_chunk_load(const uint16_t* __restrict__ patches, int64_t n,
                                                 int64_t p_base, int r, int c) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   const int p = c / 6, h = c - (c / 6) * 6;
@@ -104,8 +98,8 @@ template <int kBt>
 __device__ __forceinline__ void row_load(const uint16_t* __restrict__ patches, int64_t n,
                                          int64_t p_base, int r, bool main, bool extra,
                                          uint4 (&v)[2]) {
-  if (main) v[0] = row_chunk_load(patches, n, p_base, r, threadIdx.x);
-  if (extra) v[1] = row_chunk_load(patches, n, p_base, r, threadIdx.x + kThreads);
+  if (main) v[0] = patch_chunk_load(patches, n, p_base, r, threadIdx.x);
+  if (extra) v[1] = patch_chunk_load(patches, n, p_base, r, threadIdx.x + kThreads);
 }
 
 template <int kBt>
@@ -140,8 +134,7 @@ typedef int i32x2 __attribute__((ext_vector_type(2)));
 template <int kSplits, int kBt>
 __device__ __forceinline__ void conv_fc1_8_block(
     uint32_t* lds, int split, int64_t p_base, const uint16_t* __restrict__ patches, int64_t n,
-    const uint8_t* __restrict__ w1p, const uint4* __restrict__ convp, float* __restrict__ part,
-    int64_t row0, int64_t n_total) {
+    const uint8_t* __restrict__ w1p, const uint4* __restrict__ convp, float* __restrict__ part) {
   using T = Tile8<kBt>;
   constexpr int kTiles = T::kTiles, kOwn = T::kOwn, kSlot = T::kSlot;
   using Op = Op16<true>;
@@ -437,7 +430,7 @@ __device__ __forceinline__ void conv_fc1_8_block(
   // tile q = m * kTiles + j: outputs 16(nh*kMT + m) + 4*grp + e for patch
   // 16*(block tile) + col, the block tile nh*kOwn + j (own) or
   // (1-nh)*kOwn + j - kOwn (partner's)
-  float* dst = part + ((int64_t)split * n_total + row0 + p_base) * kFc1Out;
+  float* dst = part + ((int64_t)split * n + p_base) * kFc1Out;
   static_for<kSlots>([&](auto qc) {
     constexpr int q = decltype(qc)::value, o = q / kPer, m = q / kTiles, j = q % kTiles;
     if (kg == o) {
@@ -458,19 +451,159 @@ __device__ __forceinline__ void conv_fc1_8_block(
 template <int kSplits>
 __global__ __launch_bounds__(kThreads, 1) void conv_fc1_8_kernel(
     const uint16_t* __restrict__ patches, int64_t n, int64_t n_big, const uint8_t* __restrict__ w1p,
-    const uint4* __restrict__ convp, float* __restrict__ part, int64_t row0, int64_t n_total) {
+    const uint4* __restrict__ convp, float* __restrict__ part) {
   __shared__ __attribute__((aligned(16))) uint32_t lds[Tile8<kBigTile>::kLdsDwords];
   const int split = blockIdx.x % kSplits;
   const int64_t t = blockIdx.x / kSplits;
   if (t < n_big)
-    conv_fc1_8_block<kSplits, kBigTile>(lds, split, t * kBigTile, patches, n, w1p, convp, part,
-                                        row0, n_total);
+    conv_fc1_8_block<kSplits, kBigTile>(lds, split, t * kBigTile, patches, n, w1p, convp, part);
   else
     conv_fc1_8_block<kSplits, kSmallTile>(lds, split, n_big * kBigTile + (t - n_big) * kSmallTile,
-                                          patches, n, w1p, convp, part, row0, n_total);
+                                          patches, n, w1p, convp, part);
 }
 
 constexpr int kSplits8 = 8;
+
+// ---- Thin tiles, for batches that leave most of the chip idle: as in
+// conv_fc1_16.hip, a block of 16 patches and 128 / kParts outputs stages
+// every row of its position range (from the plane images or fp32 patches), each
+// wave computes the conv of all its patches, and the loop has no barrier.  Every
+// accumulator sees the operands of the tiles above in their order, so a patch's
+// sums are the same bits.  Bound by latency: the weights of a pair are loaded
+// kAhead pairs before their use, because a pair is short.  Per call, with a
+// gather launch and 32-patch blocks of the kernel above against this: 16 hits
+// 34.8 -> 21.5 us, 235 hits 36.7 -> 25.6, 400 hits 37.1 -> 30.4.
+template <int kSplits, int kBt, int kParts>
+__device__ __forceinline__ void thin8_block(uint32_t* lds, int split, int opart, int64_t p_base, const HitSource& src,
+                                            const uint8_t* __restrict__ w1p, const uint4* __restrict__ convp,
+                                            float* __restrict__ part) {
+  using T = Thin<kBt, kParts>;
+  using Op = Op16<true>;
+  constexpr int kTiles = T::kTiles, kSlot = T::kSlot, kMTw = T::kMTw;
+  constexpr int kAhead = kMTw == 4 ? 2 : 4;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wave % kKGroups, nh = wave / kKGroups;
+  const int col = lane & 15, grp = lane >> 4;
+  constexpr int kGroups = kPos / 2 / kKGroups;
+  const int G0 = (kGroups * split) / kSplits;
+  const int steps = (kGroups * (split + 1)) / kSplits - G0;
+  const int P0 = kKGroups * G0;
+  const int r0 = P0 / kPairsPerRow;                        // first input row of the range
+  const int nrows = (P0 + kKGroups * steps - 1) / kPairsPerRow + kK - r0;
+
+  // the weights and filters first: they do not wait for the hits
+  const __amdgpu_buffer_rsrc_t w1r = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(w1p), (short)0, (int)kFc1Frag8Bytes, 0x00020000);
+  const int ot0 = (opart * kNHalves + nh) * kMTw;          // the wave's first output tile
+  auto load_w = [&](int P, int m, v8i& a) {
+    const int base = (P * 8 + ot0 + m) * kFrag8;
+    a.s0123 = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(w1r, lane * 16, base, 0));
+    a.s45 = __builtin_bit_cast(i32x2, __builtin_amdgcn_raw_buffer_load_b64(w1r, 1024 + lane * 8, base, 0));
+  };
+  const v8i zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+  v8i w[kAhead][kMTw];
+#pragma unroll
+  for (int k = 0; k < kAhead; ++k)
+#pragma unroll
+    for (int m = 0; m < kMTw; ++m) {
+      w[k][m] = zero8;
+      load_w(P0 + kKGroups * k + kg, m, w[k][m]);
+    }
+  uint4 filt[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) filt[k] = convp[k * 64 + lane];
+
+  thin_stage<true, kBt, kParts>(lds, p_base, src, r0, nrows, w1p);
+
+  int woff[4], wrow[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    int f = 8 * grp + 2 * d;
+    if (f > 28) f = 28;                      // slots 30-31 are constants (set below)
+    wrow[d] = f / 6 - r0;
+    woff[d] = (f % 6) / 2 + col * kRP;
+  }
+  const bool const_slot = (grp == 3);
+  auto read_win = [&](int P, uint4 (&win)[kTiles]) {
+    const int y = P / kPairsPerRow;
+    const int xh = P - y * kPairsPerRow;
+    int base[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) base[d] = (y + wrow[d]) * kSlot + woff[d] + xh;
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i) {
+      const int o = i * 16 * kRP;
+      win[i].x = lds[base[0] + o];
+      win[i].y = lds[base[1] + o];
+      win[i].z = lds[base[2] + o];
+      win[i].w = lds[base[3] + o];
+    }
+  };
+  floatx4 acc[kMTw][kTiles];
+#pragma unroll
+  for (int m = 0; m < kMTw; ++m)
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i) acc[m][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+  uint4 win[kTiles];
+  v8i own[2][kTiles];                        // the conv of this pair and of the next
+#pragma unroll
+  for (int i = 0; i < kTiles; ++i) own[0][i] = own[1][i] = zero8;
+  // the conv of a pair, rounded to e4m3: channel tile t of shift s in dword 3s + t
+  auto conv = [&](v8i (&o)[kTiles]) {
+    const floatx4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i) {
+      win[i].w = const_slot ? Op::kOnes : win[i].w;
+#pragma unroll
+      for (int t = 0; t < 6; ++t) o[i][t] = to_e4m3x4(Op::mfma(filt[t], win[i], z), o[i][t]);
+    }
+  };
+  __syncthreads();                           // the staged rows
+  read_win(P0 + kg, win);
+  conv(own[0]);
+  read_win(P0 + kKGroups + kg, win);
+  auto step_fn = [&](int step, int k, v8i (&cur)[kTiles], v8i (&nxt)[kTiles]) {
+    const int P = P0 + kKGroups * step + kg;
+#pragma unroll
+    for (int m = 0; m < kMTw; ++m) {
+#pragma unroll
+      for (int i = 0; i < kTiles; ++i) acc[m][i] = mfma8(w[k][m], cur[i], acc[m][i]);
+#pragma unroll
+      for (int i = 0; i < kTiles; ++i) asm volatile("" : "+v"(acc[m][i]));   // not moved past the conv
+      load_w(P + kAhead * kKGroups, m, w[k][m]);           // (past the end of the weights: 0)
+    }
+    conv(nxt);
+    // (the windows of up to two pairs after the last one are never used; they
+    // lie at most one row lower than the staged rows)
+    read_win(P + 2 * kKGroups, win);
+    __builtin_amdgcn_sched_barrier(0);       // a step's registers at a time
+  };
+  int step = 0;
+#pragma unroll 1
+  for (; step + kAhead <= steps; step += kAhead) {
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) step_fn(step + k, k, own[k & 1], own[(k & 1) ^ 1]);
+  }
+#pragma unroll
+  for (int k = 0; k < kAhead - 1; ++k)
+    if (step + k < steps) step_fn(step + k, k, own[k & 1], own[(k & 1) ^ 1]);
+
+  thin_reduce<kBt, kParts>(lds, acc, ot0, p_base, src.n, part + ((int64_t)split * src.n + p_base) * kFc1Out);
+}
+
+// Block b: split b % kSplits, then output part, then patch tile.
+template <int kSplits, int kBt, int kParts>
+__global__ __launch_bounds__(kThreads, 1) void conv_fc1_8_thin_kernel(HitSource src, const uint8_t* __restrict__ w1p,
+                                                                      const uint4* __restrict__ convp,
+                                                                      float* __restrict__ part) {
+  static_assert(thin_rows_needed(kSplits) <= kThinRows, "a position range's rows fit the stage");
+  __shared__ __attribute__((aligned(16))) uint32_t lds[Thin<kBt, kParts>::kLdsDwords];
+  const int split = blockIdx.x % kSplits;
+  const int64_t r = blockIdx.x / kSplits;
+  thin8_block<kSplits, kBt, kParts>(lds, split, (int)(r % kParts), r / kParts * kBt, src, w1p, convp, part);
+}
 
 }  // namespace
 
@@ -491,18 +624,30 @@ void conv_fc1_8_tiles(int64_t n, int cus, int64_t* n_big, int64_t* n_small) {
   *n_small = small;
 }
 
-hipError_t launch_conv_fc1_8(const uint16_t* patches, int64_t n, int64_t row0, int64_t n_total,
-                             const uint8_t* w1p, const uint4* convp, float* part, hipStream_t stream) {
+// Thin tiles while their blocks of 16 patches fit one round of the CUs (512
+// patches on 256 CUs), with the output parts of the 16-bit kernel.  Past that,
+// thin blocks of 32 patches were slower than the 32-patch blocks above with
+// the gather's launch (513 hits 39.8 against 37.5 us per call, 1,024 42.0
+// against 39.8): each of their waves computes and rounds the conv of all
+// patches, the others' of half of them.
+bool conv_fc1_8_thin(int64_t n, int cus) { return conv_fc1_16_thin_tile(n, cus) == 16; }
+
+hipError_t launch_conv_fc1_8(const RowInput& in, int64_t n, const uint8_t* w1p, const uint4* convp, float* part,
+                             int cus, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
-  int dev = 0, cus = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return e;
+  if (conv_fc1_8_thin(n, cus)) {
+    const int parts = conv_fc1_16_thin_parts(n, cus, 16);
+    const dim3 grid((unsigned)((n + 15) / 16 * kSplits8 * parts));
+    const HitSource src = hit_source(in, n);
+    auto go = [&](auto kernel) { return launch_kernel(kernel, grid, dim3(kThreads), 0, stream, src, w1p, convp, part); };
+    if (parts == 4) return go(conv_fc1_8_thin_kernel<kSplits8, 16, 4>);
+    return parts == 2 ? go(conv_fc1_8_thin_kernel<kSplits8, 16, 2>) : go(conv_fc1_8_thin_kernel<kSplits8, 16, 1>);
+  }
   int64_t n_big = 0, n_small = 0;
   conv_fc1_8_tiles(n, cus, &n_big, &n_small);
   const dim3 grid((unsigned)((n_big + n_small) * kSplits8));
-  return launch_kernel(conv_fc1_8_kernel<kSplits8>, grid, dim3(kThreads), 0, stream, patches, n,
-                       n_big, w1p, convp, part, row0, n_total);
+  return launch_kernel(conv_fc1_8_kernel<kSplits8>, grid, dim3(kThreads), 0, stream, in.patches16, n, n_big, w1p,
+                       convp, part);
 }
 
 }  // namespace pointid

@@ -190,13 +190,15 @@ hipError_t launch_conv_fc1_16(bool fp16, const RowInput& in, int64_t n, const ui
                               const uint4* convp, float* part, int cus, hipStream_t stream);
 
 // Fused conv (fp16 MFMA) + ReLU + FC1 on e4m3 MFMA operands: fp16 patches
-// [n][2304] -> part[s][row0 + i][128] for s < conv_fc1_8_splits(), the sums
-// of FC1 column n still multiplied by 2^k_n.
+// (batches that run thin tiles, conv_fc1_8_thin: fp32 patches or hits) ->
+// part[s][i][128] for s < conv_fc1_8_splits(), the sums of FC1 column n still
+// multiplied by 2^k_n.
 int conv_fc1_8_splits();
 // Tiles of the 8-bit launch for n patches on `cus` CUs (64 and 32 patches).
 void conv_fc1_8_tiles(int64_t n, int cus, int64_t* n_big, int64_t* n_small);
-hipError_t launch_conv_fc1_8(const uint16_t* patches, int64_t n, int64_t row0, int64_t n_total,
-                             const uint8_t* w1p, const uint4* convp, float* part, hipStream_t stream);
+bool conv_fc1_8_thin(int64_t n, int cus);
+hipError_t launch_conv_fc1_8(const RowInput& in, int64_t n, const uint8_t* w1p, const uint4* convp, float* part,
+                             int cus, hipStream_t stream);
 
 // Fused conv + ReLU + FC1 of the fp32 path: fp32 patches or hits -> part[s][i][128]
 // for s < conv_fc1_f32_splits(), from the conv filters and FC1 weights in three

@@ -112,15 +112,18 @@ def test_large_batches_give_the_bits_of_small_ones(pid, handles, prec):
         assert np.array_equal(bits(pid.pointid_classify_patches(h, P[lo:hi].contiguous())), full[lo:hi]), (lo, hi)
 
 
-def test_fp32_block_shapes_at_their_edges(pid, handles):
-    """Batches on both sides of every change of the fp32 path's block shape on a
-    256-CU device (16 patches, a quarter of the outputs up to 128; 32 patches, a
-    quarter up to 256, half up to 512, all up to 1,024; then 64) give one set of bits."""
-    h = handles["fp32"]
+@pytest.mark.parametrize("prec", ["fp32", "fp8"])
+def test_block_shapes_at_their_edges(pid, handles, prec):
+    """Batches on both sides of every change of a block shape on a 256-CU device
+    give one set of bits.  fp32: 16 patches, a quarter of the outputs up to 128; 32
+    patches, a quarter up to 256, half up to 512, all up to 1,024; then 64.  fp8: 16
+    patches, a quarter of the outputs up to 128, half up to 256, all up to 512; 32
+    patches up to 1,024; then 64."""
+    h = handles[prec]
     P = t(synth.config4_patches(4200, seed=6))
     full = bits(pid.pointid_classify_patches(h, P))
     for n in (1, 15, 16, 17, 127, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 3072, 3073, 4096, 4097):
-        say(f"fp32 {n} patches")
+        say(f"{prec} {n} patches")
         for lo in (0, 4200 - n):
             got = bits(pid.pointid_classify_patches(h, P[lo:lo + n].contiguous()))
             assert np.array_equal(got, full[lo:lo + n]), (n, lo)
