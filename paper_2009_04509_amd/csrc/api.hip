@@ -430,11 +430,11 @@ int classify_table(pointid_handle h, const PlaneTable& planes, const RequestTabl
   int cus = 0;
   hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return hip_fail(e, "device attribute");
-  // The fp32 kernel, and the others for batches that fill at most one round
-  // of thin tiles, take the hits themselves.  The larger tiles read 16-bit
-  // patches from the gather: at the card's power limit the image reads cost
-  // the 16-bit kernel as much as the gather takes.
-  const bool direct = fp32 || (fp8 ? conv_fc1_8_thin(n, cus) : conv_fc1_16_thin_tile(n, cus) != 0);
+  // The fp32 kernel, the 16-bit kernels for batches of at most one round of
+  // 64-patch tiles and the 8-bit kernel for thin tiles take the hits themselves.
+  // Larger batches read 16-bit patches from the gather: at the card's power
+  // limit the image reads cost the 16-bit kernel as much as the gather takes.
+  const bool direct = fp32 || (fp8 ? conv_fc1_8_thin(n, cus) : conv_fc1_16_direct(n, cus));
   e = ws.reserve((direct ? 0 : pad256(patch_bytes(n))) + pad256(part_bytes(h->precision, n)));
   if (e != hipSuccess) return hip_fail(e, "scratch buffer");
   RowInput in;

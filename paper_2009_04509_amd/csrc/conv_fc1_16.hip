@@ -40,6 +40,8 @@
 //
 // The four position groups' partial sums are added in LDS in a fixed order and
 // written as fp32 partials [split][patch][128]; the tail kernel adds the splits.
+#include <type_traits>
+
 #include "internal.h"
 #include "op16.h"
 #include "rows.h"
@@ -142,6 +144,44 @@ struct Rows {
   }
 };
 
+// The rows of hits, read from the plane images (rows.h) with the descriptors at
+// `desc` in LDS; patches past the end of the batch hold zeros.
+template <int kBt>
+struct Rows<kBt, HitSource> {
+  static constexpr int kAll = kBt * kRowChunks;
+  static constexpr int kPer = (kAll + kThreads - 1) / kThreads;
+  static_assert(kAll % 64 == 0, "row chunks in whole waves");
+  rowx4 v[kPer];
+  uint32_t kinds;
+
+  __device__ __forceinline__ void load(const uint4* desc, const void* safe, int r) {
+    kinds = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int c = threadIdx.x + k * kThreads;
+      if (c < kAll) {
+        uint32_t kind;
+        v[k] = row_chunk_load(desc_from_lds(desc + c / kRowChunks), r, c - (c / kRowChunks) * kRowChunks, safe, &kind);
+        kinds |= kind << 2 * k;
+      }
+    }
+  }
+  template <bool kFp16>
+  __device__ __forceinline__ void store(uint32_t* lds, const uint4* desc, int r) const {
+    using Op = Op16<kFp16>;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int c = threadIdx.x + k * kThreads;
+      if (c < kAll) {
+        const int p = c / kRowChunks, h = c - (c / kRowChunks) * kRowChunks;
+        const rowx4 x = row_chunk_finish(desc + p, r, h, v[k], (kinds >> 2 * k) & 3);
+        *reinterpret_cast<uint2*>(lds + (r & (kRing - 1)) * Tile<kBt>::kSlot + p * kRP + h * 2) =
+            make_uint2(Op::pack(x[0], x[1]), Op::pack(x[2], x[3]));
+      }
+    }
+  }
+};
+
 // One block: patches p_base .. p_base + kBt - 1 (clamped to the batch) and
 // `ranges` consecutive position ranges from `split0`.  The pairs of a range
 // follow those of the range before it, so the patch rows in the ring run on
@@ -152,6 +192,20 @@ __device__ __forceinline__ void conv_fc1_block(
     uint32_t* lds, int split0, int ranges_, int64_t p_base, const In* __restrict__ patches, int64_t n,
     const uint4* __restrict__ w1p, const uint4* __restrict__ convp, float* __restrict__ part) {
   using T = Tile<kBt>;
+  constexpr bool kHits = std::is_same<In, HitSource>::value;
+  uint4* desc = reinterpret_cast<uint4*>(lds + T::kLdsDwords);   // (hits only)
+  if constexpr (kHits) {
+    if (threadIdx.x < kBt) desc[threadIdx.x] = patches->get(p_base + threadIdx.x);
+    __syncthreads();
+  }
+  auto load_row = [&](Rows<kBt, In>& row, int rr) {
+    if constexpr (kHits) row.load(desc, w1p, rr);
+    else row.load(patches, n, p_base, rr);
+  };
+  auto store_row = [&](const Rows<kBt, In>& row, int rr) {
+    if constexpr (kHits) row.template store<kFp16>(lds, desc, rr);
+    else row.template store<kFp16>(lds, rr);
+  };
   const int ranges = kMulti ? ranges_ : 1;
   constexpr int kTiles = T::kTiles, kOwn = T::kOwn, kSlot = T::kSlot;
   constexpr int kSlots = kMT * kTiles;       // accumulator tiles of a wave
@@ -209,11 +263,11 @@ __device__ __forceinline__ void conv_fc1_block(
     if (tid < 6 * 64) fv = convp[tid];
 #pragma unroll
     for (int j = 0; j < kPrologueRows; ++j)
-      if (r0 + j <= loaded_hi) v[j].load(patches, n, p_base, r0 + j);
+      if (r0 + j <= loaded_hi) load_row(v[j], r0 + j);
     if (tid < 6 * 64) cwl[tid] = fv;
 #pragma unroll
     for (int j = 0; j < kPrologueRows; ++j)
-      if (r0 + j <= loaded_hi) v[j].template store<kFp16>(lds, r0 + j);
+      if (r0 + j <= loaded_hi) store_row(v[j], r0 + j);
   }
   __syncthreads();
 
@@ -264,21 +318,22 @@ __device__ __forceinline__ void conv_fc1_block(
   };
 
   // FC1 fragments of this wave's outputs through a buffer resource: the
-  // fragment's place is a scalar offset, so the loads need one per-lane
-  // register and no per-lane arithmetic; reads past the end return 0.
+  // fragment's place is a scalar offset and the output tile an immediate one, so
+  // the loads need one per-lane register, no per-lane arithmetic and one scalar
+  // addition per K-step; reads past the end return 0.
   const __amdgpu_buffer_rsrc_t w1r = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint4*>(w1p), (short)0, (int)(kFc1Frags * 16), 0x00020000);
-  const int voff = lane * 16;
+  const int voff = lane * 16 + nh * kMT * 1024;
   auto load_one = [&](int P, int q, int m) {
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
-                                         w1r, voff, ((P * 3 + q) * 8 + nh * kMT + m) * 1024, 0));
+                                         w1r, voff + m * 1024, (P * 3 + q) * 8 * 1024, 0));
   };
 
   int step = 0;                              // of the block's first range on
   bool row_pending = false;                  // row loaded_hi + 1 is on its way, in rv
   Rows<kBt, In> rv;
 #pragma unroll
-  for (int k = 0; k < Rows<kBt, In>::kPer; ++k) rv.v[k] = make_uint4(0, 0, 0, 0);
+  for (int k = 0; k < Rows<kBt, In>::kPer; ++k) rv.v[k] = {};
 #pragma unroll 1
   for (int split = split0; split < split0 + ranges; ++split) {
   const int step_end = range_begin(split + 1) - range_begin(split0);
@@ -389,9 +444,9 @@ __device__ __forceinline__ void conv_fc1_block(
         // The slot it overwrites held a row below every row that any wave
         // still reads; the barriers publish it before the step that first
         // needs it.  Block-uniform conditions.
-        if (row_pending) rv.template store<kFp16>(lds, ++loaded_hi);
+        if (row_pending) store_row(rv, ++loaded_hi);
         row_pending = top_row(step + kAhead) > loaded_hi;
-        if (row_pending) rv.load(patches, n, p_base, loaded_hi + 1);
+        if (row_pending) load_row(rv, loaded_hi + 1);
       }
 #pragma unroll
       for (int i = 0; i < kOwn; ++i) own[i] = nxt[i];
@@ -518,6 +573,17 @@ __global__ __launch_bounds__(kThreads, 1) void conv_fc1_16_kernel(
         n, w1p, convp, part);
 }
 
+// The same for the hits of a batch whose tiles of 64 patches fit one round of
+// the CUs: it reads the rows of the planes itself.
+template <bool kFp16>
+__global__ __launch_bounds__(kThreads, 1) void conv_fc1_16_hits_kernel(HitSource src, const uint4* __restrict__ w1p,
+                                                                       const uint4* __restrict__ convp,
+                                                                       float* __restrict__ part) {
+  __shared__ __attribute__((aligned(16))) uint32_t lds[Tile<kMidTile>::kLdsDwords + kMidTile * 4];
+  conv_fc1_block<kFp16, kMidTile, HitSource, false>(lds, blockIdx.x % kSplits16, 1,
+                                                    (int64_t)(blockIdx.x / kSplits16) * kMidTile, &src, src.n, w1p,
+                                                    convp, part);
+}
 
 // ---- Thin tiles: batches that leave most of the chip idle.  Then one block's
 // K-loop is the whole call, and the barrier per K-step and the swap through
@@ -728,6 +794,19 @@ int conv_fc1_16_thin_parts(int64_t n, int cus, int thin) {
   return 2 * blocks <= cus ? 2 : 1;
 }
 
+// Hits the kernels read from the planes themselves: batches of thin tiles, and
+// of one round of 64-patch tiles (1,025 to 2,048 patches on 256 CUs).  Such a
+// call is one block long, the chip's power limit is not reached, and the
+// gather's launch is what can be saved: 1,100 hits 59.7 -> 56.7 us per call, 2,048
+// hits 65.7 -> 63.3.  In 96-patch tiles the row addresses leave too few
+// registers: 2,600 hits 86.1 us, with the gather 82.0.
+bool conv_fc1_16_direct(int64_t n, int cus) {
+  if (conv_fc1_16_thin_tile(n, cus)) return true;
+  int64_t n_big = 0, n_mid = 0;
+  conv_fc1_16_tiles(n, cus, &n_big, &n_mid);
+  return n_big == 0 && n_mid * kSplits16 <= cus;
+}
+
 template <bool kFp16>
 hipError_t launch_typed(const RowInput& in, int64_t n, const uint4* w1p, const uint4* convp,
                         float* part, int cus, hipStream_t stream) {
@@ -746,6 +825,9 @@ hipError_t launch_typed(const RowInput& in, int64_t n, const uint4* w1p, const u
   }
   int64_t n_big = 0, n_mid = 0;
   conv_fc1_16_tiles(n, cus, &n_big, &n_mid);
+  if (!in.patches && !in.patches16)
+    return launch_kernel(conv_fc1_16_hits_kernel<kFp16>, dim3((unsigned)(n_mid * kSplits16)), dim3(kThreads), 0, stream,
+                         hit_source(in, n), w1p, convp, part);
   // blocks of several ranges for the whole rounds of tiles there are
   const int64_t round = cus >= kSplits16 ? cus / kSplits16 : 1;
   Blocks16 bl = {};

@@ -177,8 +177,8 @@ struct RowInput;
 hipError_t device_cus(int* cus);
 
 // Fused conv + ReLU + FC1 on 16-bit MFMA: fp32 patches (rounded to bf16 or
-// fp16 in the kernel), 16-bit patches, or hits (batches that run thin tiles
-// only) -> part[s][i][128] for s < conv_fc1_16_splits().
+// fp16 in the kernel), 16-bit patches, or hits (batches that
+// conv_fc1_16_direct accepts) -> part[s][i][128] for s < conv_fc1_16_splits().
 int conv_fc1_16_splits();
 // Tiles of the launch over n patches on `cus` CUs: n_big tiles of 96 patches,
 // then n_mid of 64 (a batch that fits one round of thin tiles of 16 or 32
@@ -186,6 +186,7 @@ int conv_fc1_16_splits();
 void conv_fc1_16_tiles(int64_t n, int cus, int64_t* n_big, int64_t* n_mid);
 int conv_fc1_16_thin_tile(int64_t n, int cus);
 int conv_fc1_16_thin_parts(int64_t n, int cus, int thin);
+bool conv_fc1_16_direct(int64_t n, int cus);
 hipError_t launch_conv_fc1_16(bool fp16, const RowInput& in, int64_t n, const uint4* w1p,
                               const uint4* convp, float* part, int cus, hipStream_t stream);
 

@@ -1,6 +1,6 @@
 """GPU: the fused kernels' sources of patch rows and their block shapes.
 
-Small batches (and every batch of the fp32 path) read the rows of their hits
+Batches of up to one round of blocks (and every batch of the fp32 path) read the rows of their hits
 from the plane images themselves: hits must get exactly the bits that the
 oracle's patches of the same hits get as pre-cut patches, at every edge of the
 planes, at any image alignment and row pitch, for one array of hits, requests,
@@ -77,7 +77,7 @@ def test_hits_get_the_bits_of_their_patches(pid, handles, prec):
         buf = t(np.concatenate([np.zeros(k % 4, np.float32), im.ravel()]))
         imgs.append(im)
         dev.append(buf[k % 4:].view(W, T))               # base 0, 4, 8 or 12 bytes past 16
-    for n in (1, 16, 17, 129, 300, 513, 1024, 1025, 1500):
+    for n in (1, 16, 17, 129, 300, 513, 1024, 1025, 1500, 2048, 2049, 3072, 3073):
         hh = edge_hits(rng, imgs, n)
         say(f"{prec} {n} hits at the edges")
         want = bits(pid.pointid_classify_patches(h, t(oracle.gather_patches_planes(imgs, hh))))
