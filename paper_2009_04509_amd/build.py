@@ -84,8 +84,10 @@ def build(verbose: bool = False, jobs: int = 8, sanitize: str | None = None) -> 
     flags, link, objdir = FLAGS, [], OBJDIR
     if sanitize:
         cflags, link, tag = SANITIZE[sanitize]
-        # -O1 -g keeps the reports readable; the device code is the same
-        flags = [f for f in FLAGS if f != "-O3"] + ["-O1", "-g"] + cflags
+        # -O1 -g keeps the reports readable; on the host alone: the device code is
+        # the same (and its debug info crashes the compiler on the largest kernels)
+        flags = ([f for f in FLAGS if f != "-O3"]
+                 + ["-Xarch_host", "-O1", "-Xarch_host", "-g", "-Xarch_device", "-O3"] + cflags)
         objdir = os.path.join(CSRC, f"_build_{tag}")
     out = library_path(sanitize)
     os.makedirs(objdir, exist_ok=True)
