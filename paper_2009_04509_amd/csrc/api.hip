@@ -662,15 +662,15 @@ int pointid_create(const pointid_weights* w, int precision, int device,
   const int* fc1_exp_dev = nullptr;
   if (fp8) {
     pieces.push_back({nullptr, (size_t)kConvFrags * 16, (const void**)&hnd->w.conv_frag});
-    pieces.push_back({nullptr, (size_t)kFc1Frag8Bytes, (const void**)&hnd->w.fc1_frag8});
+    pieces.push_back({nullptr, (size_t)conv_fc1_8_weight_bytes(), (const void**)&hnd->w.fc1_frag8});
     pieces.push_back({fc1_scale.data(), sizeof(float) * kFc1Out, (const void**)&hnd->w.fc1_scale});
     pieces.push_back({fc1_exp.data(), sizeof(int) * kFc1Out, (const void**)&fc1_exp_dev});
   } else if (half) {
     pieces.push_back({nullptr, (size_t)kConvFrags * 16, (const void**)&hnd->w.conv_frag});
-    pieces.push_back({nullptr, (size_t)kFc1Frags * 16, (const void**)&hnd->w.fc1_frag});
+    pieces.push_back({nullptr, (size_t)conv_fc1_16_weight_bytes(), (const void**)&hnd->w.fc1_frag});
   } else {
     pieces.push_back({nullptr, (size_t)kF32Parts * kConvFrags * 16, (const void**)&hnd->w.conv_frag});
-    pieces.push_back({nullptr, (size_t)kF32Parts * kFc1Frags * 16, (const void**)&hnd->w.fc1_frag});
+    pieces.push_back({nullptr, (size_t)conv_fc1_f32_weight_bytes(), (const void**)&hnd->w.fc1_frag});
   }
   size_t total = 0;
   std::vector<size_t> offs;

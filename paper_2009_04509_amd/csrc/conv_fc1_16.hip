@@ -57,6 +57,9 @@ constexpr int kRing = 8;                      // patch-row ring slots
 constexpr int kPrologueRows = 2 + 5 - 1;
 constexpr int kBigTile = 96;                  // patches per block (most blocks)
 constexpr int kMidTile = 64;                  // patches per block (the last rounds, some batches)
+// a wave loads the weights of its next pair, kKGroups pairs further on
+constexpr int64_t kWeightBytes = (kPos / 2 + kKGroups) * kFc1PairBytes16;
+static_assert(kFc1PairBytes16 * (kPos / 2) == kFc1Frags * 16, "packed pairs");
 
 // First step (kKGroups pairs) of position range s, of 242 in all.
 __host__ __device__ constexpr int range_begin(int s) {
@@ -320,9 +323,10 @@ __device__ __forceinline__ void conv_fc1_block(
   // FC1 fragments of this wave's outputs through a buffer resource: the
   // fragment's place is a scalar offset and the output tile an immediate one, so
   // the loads need one per-lane register, no per-lane arithmetic and one scalar
-  // addition per K-step; reads past the end return 0.
+  // addition per K-step.  (The resource's bounds check does not cover the scalar
+  // offset: the pair after a wave's last one is read, and allocated.)
   const __amdgpu_buffer_rsrc_t w1r = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint4*>(w1p), (short)0, (int)(kFc1Frags * 16), 0x00020000);
+      const_cast<uint4*>(w1p), (short)0, (int)kWeightBytes, 0x00020000);
   const int voff = lane * 16 + nh * kMT * 1024;
   auto load_one = [&](int P, int q, int m) {
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
@@ -625,7 +629,7 @@ __device__ __forceinline__ void thin_block(
 
   // the weights and filters first: they do not wait for the hits
   const __amdgpu_buffer_rsrc_t w1r = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint4*>(w1p), (short)0, (int)(kFc1Frags * 16), 0x00020000);
+      const_cast<uint4*>(w1p), (short)0, (int)kWeightBytes, 0x00020000);
   const int ot0 = (opart * kNHalves + nh) * kMTw;           // the wave's first output tile
   const int voff = lane * 16 + ot0 * 1024;
   auto load_one = [&](int P, int q, int m) {
@@ -697,7 +701,7 @@ __device__ __forceinline__ void thin_block(
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const int nq = (q + 1) % 3;            // the next K-step
-      // FC1 of K-step q (past the end of the weights the reload reads 0)
+      // FC1 of K-step q (the pair after the last one is loaded too)
 #pragma unroll
       for (int m = 0; m < kMTw; ++m) {
 #pragma unroll
@@ -739,6 +743,7 @@ __global__ __launch_bounds__(kThreads, 1) void conv_fc1_16_thin_kernel(
 }  // namespace
 
 int conv_fc1_16_splits() { return kSplits16; }
+int64_t conv_fc1_16_weight_bytes() { return kWeightBytes; }
 
 // One block per CU and (tile, split), so a round of the CUs holds `per_round`
 // tiles.  Whole rounds of big tiles, then the rest as rounds of mid tiles or

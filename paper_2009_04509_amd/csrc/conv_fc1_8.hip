@@ -48,6 +48,11 @@ constexpr int kBigTile = 64;                  // patches per block (most blocks)
 constexpr int kSmallTile = 32;                // patches per block (the last ones)
 constexpr int kFrag8 = 1536;                  // bytes per (pair, output tile) fragment
 constexpr int kSwapTile = 64 * 6;             // dwords per swapped patch tile
+// a wave loads the weights of its next pair, kKGroups pairs further on, the
+// thin tiles those of up to kMaxAhead pairs
+constexpr int kMaxAhead = 4;
+constexpr int64_t kWeightBytes = (kPos / 2 + kMaxAhead * kKGroups) * kFc1PairBytes8;
+static_assert(kFc1PairBytes8 == 8 * kFrag8, "packed pairs");
 
 // LDS of a block of kBt patches (dwords): ring | conv filter fragments | swap
 // buffers; the final reduction reuses it from the start.
@@ -196,10 +201,11 @@ __device__ __forceinline__ void conv_fc1_8_block(
       if (r0 + j <= loaded_hi) row_store<kBt>(lds, r0 + j, rmain, extra, v[j]);
   }
 
-  // FC1 fragments of this wave's output tiles through a buffer resource:
-  // reads past the end of the weights return 0
+  // FC1 fragments of this wave's output tiles through a buffer resource (the
+  // pair after the last one is read too, and allocated: the bounds check leaves
+  // out the scalar offset)
   const __amdgpu_buffer_rsrc_t w1r = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(w1p), (short)0, (int)((int64_t)(kPos / 2) * 8 * kFrag8), 0x00020000);
+      const_cast<uint8_t*>(w1p), (short)0, (int)kWeightBytes, 0x00020000);
   // Operand tuples (weights w, the wave's own conv fragments, the partner's)
   // live across the whole loop and are updated in place in dwords 0-5, so
   // their zero dwords 6-7 are set once.
@@ -480,7 +486,7 @@ __device__ __forceinline__ void thin8_block(uint32_t* lds, int split, int opart,
   using T = Thin<kBt, kParts>;
   using Op = Op16<true>;
   constexpr int kTiles = T::kTiles, kSlot = T::kSlot, kMTw = T::kMTw;
-  constexpr int kAhead = kMTw == 4 ? 2 : 4;
+  constexpr int kAhead = kMTw == 4 ? 2 : kMaxAhead;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -495,7 +501,7 @@ __device__ __forceinline__ void thin8_block(uint32_t* lds, int split, int opart,
 
   // the weights and filters first: they do not wait for the hits
   const __amdgpu_buffer_rsrc_t w1r = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(w1p), (short)0, (int)kFc1Frag8Bytes, 0x00020000);
+      const_cast<uint8_t*>(w1p), (short)0, (int)kWeightBytes, 0x00020000);
   const int ot0 = (opart * kNHalves + nh) * kMTw;          // the wave's first output tile
   auto load_w = [&](int P, int m, v8i& a) {
     const int base = (P * 8 + ot0 + m) * kFrag8;
@@ -572,7 +578,7 @@ __device__ __forceinline__ void thin8_block(uint32_t* lds, int split, int opart,
       for (int i = 0; i < kTiles; ++i) acc[m][i] = mfma8(w[k][m], cur[i], acc[m][i]);
 #pragma unroll
       for (int i = 0; i < kTiles; ++i) asm volatile("" : "+v"(acc[m][i]));   // not moved past the conv
-      load_w(P + kAhead * kKGroups, m, w[k][m]);           // (past the end of the weights: 0)
+      load_w(P + kAhead * kKGroups, m, w[k][m]);           // (past the last pair too)
     }
     conv(nxt);
     // (the windows of up to two pairs after the last one are never used; they
@@ -608,6 +614,7 @@ __global__ __launch_bounds__(kThreads, 1) void conv_fc1_8_thin_kernel(HitSource 
 }  // namespace
 
 int conv_fc1_8_splits() { return kSplits8; }
+int64_t conv_fc1_8_weight_bytes() { return kWeightBytes; }
 
 // As for the fp16 kernel: big tiles fill whole rounds of the CUs; the rest is
 // cut into small tiles when they fit in one round.

@@ -56,6 +56,8 @@ constexpr int kRing = 6;                      // patch rows in LDS
 constexpr int kRP = 26;                       // LDS row pitch of one part, dwords (24 used)
 static_assert((kWaves - 2) / kPairsPerRow + 1 + kK <= kRing, "rows of one step of 8 pairs");
 static_assert(kWaves < kPairsPerRow, "at most one new row per step");
+// a wave loads the weights of its next pair, kWaves pairs further on
+constexpr int64_t kWeightBytes = (kPairs + kWaves) * kParts3 * kFc1PairBytes16;
 
 // first pair of range s (whole groups of 4 pairs: 120 or 124 pairs each)
 __host__ __device__ constexpr int range_begin(int s) { return 4 * (kPairs / 4 * s / kSplits); }
@@ -136,10 +138,11 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
   const int P0 = range_begin(split), P_end = range_begin(split + 1);
   const int steps = (P_end - P0 + kWaves - 1) / kWaves;
 
-  // FC1 fragments through a buffer resource (reads past the end return 0):
+  // FC1 fragments through a buffer resource (the pair after the last one is read
+  // too, and allocated: the bounds check leaves out the scalar offset):
   // group G of a pair is K-step G / kMT, output tile G % kMT
   const __amdgpu_buffer_rsrc_t w1r = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint4*>(w1p), (short)0, (int)(kParts3 * kFc1Frags * 16), 0x00020000);
+      const_cast<uint4*>(w1p), (short)0, (int)kWeightBytes, 0x00020000);
   const int voff = lane * 16 + opart * kMT * kParts3 * 1024;
   auto load_set = [&](int P, int G, uint4 (&w)[kParts3]) {
 #pragma unroll
@@ -434,6 +437,7 @@ __global__ __launch_bounds__(64) void pack_conv_f32_kernel(const float* __restri
 }  // namespace
 
 int conv_fc1_f32_splits() { return kSplits; }
+int64_t conv_fc1_f32_weight_bytes() { return kWeightBytes; }
 
 // Small batches: patches per block and output parts, (0, 0) past 512 patches
 // on 256 CUs.  The shapes whose blocks fit one round of the CUs, by the time of

@@ -111,8 +111,11 @@ struct DeviceWeights {
   const float* fc1_scale;
 };
 
-// Bytes of the 8-bit packed FC1 weights.
-constexpr int64_t kFc1Frag8Bytes = (int64_t)(kPos / 2) * 8 * 1536;
+// The packed FC1 weights go pair by pair.  Every kernel loads the weights of a
+// wave's next pairs before it is known whether there are any, so the pairs that
+// follow the last one are read too (never used): the allocation holds them.
+constexpr int64_t kFc1PairBytes16 = 3 * 8 * 64 * 16;      // times the parts on fp32 handles
+constexpr int64_t kFc1PairBytes8 = 8 * 1536;
 
 // Fragment counts of the 16-bit packed weights.
 constexpr int64_t kConvFrags = 2 * 3 * 64;
@@ -180,6 +183,8 @@ hipError_t device_cus(int* cus);
 // fp16 in the kernel), 16-bit patches, or hits (batches that
 // conv_fc1_16_direct accepts) -> part[s][i][128] for s < conv_fc1_16_splits().
 int conv_fc1_16_splits();
+// Bytes of packed FC1 weights that the kernels may read (see kFc1PairBytes16).
+int64_t conv_fc1_16_weight_bytes();
 // Tiles of the launch over n patches on `cus` CUs: n_big tiles of 96 patches,
 // then n_mid of 64 (a batch that fits one round of thin tiles of 16 or 32
 // patches, conv_fc1_16_thin_tile, runs those instead).
@@ -195,6 +200,7 @@ hipError_t launch_conv_fc1_16(bool fp16, const RowInput& in, int64_t n, const ui
 // part[s][i][128] for s < conv_fc1_8_splits(), the sums of FC1 column n still
 // multiplied by 2^k_n.
 int conv_fc1_8_splits();
+int64_t conv_fc1_8_weight_bytes();
 // Tiles of the 8-bit launch for n patches on `cus` CUs (64 and 32 patches).
 void conv_fc1_8_tiles(int64_t n, int cus, int64_t* n_big, int64_t* n_small);
 bool conv_fc1_8_thin(int64_t n, int cus);
@@ -206,6 +212,7 @@ hipError_t launch_conv_fc1_8(const RowInput& in, int64_t n, const uint8_t* w1p, 
 // bf16 parts each (launch_pack_f32).
 constexpr int kF32Parts = 3;
 int conv_fc1_f32_splits();
+int64_t conv_fc1_f32_weight_bytes();
 // Tiles of the launch over n patches on `cus` CUs: n_big of 64 patches, then
 // n_small of 32; small batches instead run blocks of 16 * tiles patches and
 // 128 / parts outputs (tiles = 0: not a small batch).
