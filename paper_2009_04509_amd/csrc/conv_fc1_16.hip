@@ -246,10 +246,15 @@ __device__ __forceinline__ void conv_fc1_block(
   const int wcol = col * kRP + nh * kOwn * 16 * kRP;
   const bool const_slot = (grp == 3);
 
-  // ---- patch rows.  The window of step s+1 is read during step s, and a new
-  // row's loads are issued a step before it goes into the ring: the ring is
-  // filled kAhead steps ahead of the step being computed.
-  constexpr int kAhead = 3;
+  // ---- patch rows.  The window of step s+1 is read during step s.  Gathered and
+  // pre-cut rows: a row's loads are issued at the start of a step and it goes
+  // into the ring at its end, two steps ahead of the step that needs it, so that
+  // no row is held in registers from one step to the next (2,600 pre-cut patches
+  // 83.8 -> 79.1 us per call, 16,384 414.2 -> 401.3: fp32 rows spilled registers).
+  // Rows of hits come from further away: they go into the ring a step after
+  // their loads, three steps ahead (1,100 hits 59.2 us without, 58.2 with).
+  constexpr bool kLate = kHits;
+  constexpr int kAhead = kLate ? 3 : 2;
   static_assert(kKGroups * kAhead + kKGroups - 1 < kPairsPerRow && 1 + kK < kRing,
                 "rows up to 1 + 4 past a step's first");
   auto top_row = [&](int step) {             // highest input row a step needs
@@ -383,6 +388,10 @@ __device__ __forceinline__ void conv_fc1_block(
   for (; step < step_end; ++step) {
     const int P = P0 + kKGroups * step + kg;
     uint4 win_next[kOwn];
+    if constexpr (!kLate) {                  // block-uniform
+      row_pending = top_row(step + kAhead) > loaded_hi;
+      if (row_pending) load_row(rv, loaded_hi + 1);
+    }
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const int nq = (q + 1) % 3;            // the next K-step
@@ -439,7 +448,7 @@ __device__ __forceinline__ void conv_fc1_block(
       oth_group(3);
       w[q][3] = load_one(P + kKGroups, q, 3);
       __builtin_amdgcn_sched_barrier(0);
-      if (q == 0) {
+      if (kLate && q == 0) {
         // Patch rows.  Loads return in order, and a row comes from further
         // away than the weights: its loads follow a K-step's weight loads, the
         // next weight loads come half a K-step later and are used two and a
@@ -457,6 +466,9 @@ __device__ __forceinline__ void conv_fc1_block(
       if (q == 2) {
 #pragma unroll
         for (int i = 0; i < kOwn; ++i) win[i] = win_next[i];
+        // (the slot it overwrites held a row below every row that any wave still
+        // reads; first needed two steps later)
+        if (!kLate && row_pending) store_row(rv, ++loaded_hi);
       }
       buf ^= 1;
       // publishes the next K-step's swap fragments (and a new row); the
@@ -515,13 +527,15 @@ __device__ __forceinline__ void conv_fc1_block(
         }
       });
     };
-    constexpr int kPass = T::kRedTiles;
-    floatx4* red = reinterpret_cast<floatx4*>(lds + T::kSwapOff);
-    reduce(std::integral_constant<int, 0>{}, std::integral_constant<int, kPass>{}, red);
-    // (one range per block: the second pass through LDS that the first leaves alone)
-    if constexpr (kMulti) __syncthreads();
-    reduce(std::integral_constant<int, kPass>{}, std::integral_constant<int, kPer - kPass>{},
-           kMulti ? red : reinterpret_cast<floatx4*>(lds));
+    if constexpr (kMulti) {
+      constexpr int kPass = T::kRedTiles;
+      floatx4* red = reinterpret_cast<floatx4*>(lds + T::kSwapOff);
+      reduce(std::integral_constant<int, 0>{}, std::integral_constant<int, kPass>{}, red);
+      __syncthreads();
+      reduce(std::integral_constant<int, kPass>{}, std::integral_constant<int, kPer - kPass>{}, red);
+    } else {
+      reduce(std::integral_constant<int, 0>{}, std::integral_constant<int, kPer>{}, reinterpret_cast<floatx4*>(lds));
+    }
     if (split + 1 < split0 + ranges) __syncthreads();
   }
 }
@@ -543,31 +557,44 @@ __global__ __launch_bounds__(kThreads, 1) void conv_fc1_16_kernel(
     const In* __restrict__ patches, int64_t n, Blocks16 bl, const uint4* __restrict__ w1p, const uint4* __restrict__ convp,
     float* __restrict__ part) {
   __shared__ __attribute__((aligned(16))) uint32_t lds[Tile<kBigTile>::kLdsDwords];
-  int64_t b = blockIdx.x, first = 0, tiles = bl.big4;
-  int ranges = 4;
-  bool mid = false;
-  // segment of block b: 8 blocks (one per XCD) hold `ranges` tiles
-  auto blocks = [&] { return (tiles + ranges - 1) / ranges * 8; };
-  auto next = [&](int64_t t, int r) {
-    b -= blocks();
-    first += tiles;
-    tiles = t;
-    ranges = r;
-  };
-  if (b >= blocks()) next(bl.big2, 2);
-  if (ranges == 2 && b >= blocks()) next(bl.big1, 1);
-  if (ranges == 1 && b >= blocks()) {
-    next(bl.mid2, 2);
-    first = 0;
-    mid = true;
-    if (b >= blocks()) next(bl.mid1, 1);
+  int64_t first = 0, t;
+  int ranges = 1, split;
+  bool mid;
+  if constexpr (kMulti) {
+    // segment of block b: 8 blocks (one per XCD) hold 1 << lr tiles, each block
+    // 1 << lr ranges of one.  (In shifts, and only here: the same arithmetic with
+    // 64-bit divisions cost every block about 1 us, 2,049 hits 80.4 -> 81.9 us.)
+    int64_t b = blockIdx.x, tiles = bl.big4;
+    int lr = 2;
+    mid = false;
+    auto blocks = [&] { return (tiles + (1 << lr) - 1) >> lr << 3; };
+    auto next = [&](int64_t n_tiles, int l) {
+      b -= blocks();
+      first += tiles;
+      tiles = n_tiles;
+      lr = l;
+    };
+    if (b >= blocks()) next(bl.big2, 1);
+    if (lr == 1 && b >= blocks()) next(bl.big1, 0);
+    if (lr == 0 && b >= blocks()) {
+      next(bl.mid2, 1);
+      first = 0;
+      mid = true;
+      if (b >= blocks()) next(bl.mid1, 0);
+    }
+    // XCD x = b % 8 takes range group x % (8 / ranges): the blocks that run on
+    // one XCD at a time stream the same weights through its L2
+    const int x = (int)(b & 7);
+    ranges = 1 << lr;
+    t = (b >> 3 << lr) + (x >> (3 - lr));
+    if (t >= tiles) return;
+    split = (x & ((kSplits16 >> lr) - 1)) << lr;
+  } else {
+    split = blockIdx.x % kSplits16;
+    t = blockIdx.x / kSplits16;
+    mid = t >= bl.big1;
+    if (mid) t -= bl.big1;
   }
-  // XCD x = b % 8 takes range group x % (8 / ranges): the blocks that run on
-  // one XCD at a time stream the same weights through its L2
-  const int groups = kSplits16 / ranges, x = (int)(b % 8);
-  const int64_t t = b / 8 * ranges + x / groups;
-  if (t >= tiles) return;
-  const int split = x % groups * ranges;
   if (!mid)
     conv_fc1_block<kFp16, kBigTile, In, kMulti>(lds, split, ranges, (first + t) * kBigTile, patches, n, w1p, convp,
                                     part);
