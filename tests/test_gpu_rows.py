@@ -112,6 +112,30 @@ def test_large_batches_give_the_bits_of_small_ones(pid, handles, prec):
         assert np.array_equal(bits(pid.pointid_classify_patches(h, P[lo:hi].contiguous())), full[lo:hi]), (lo, hi)
 
 
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+def test_gathered_batches_give_the_bits_of_small_ones(pid, handles, prec):
+    """Hits past one round of 64-patch tiles come as 16-bit patches from the gather.
+    On a 256-CU device the sizes are on both sides of every change of the blocks: 96-patch
+    tiles (one range; from 6,144 hits two, from 12,288 four), 64-patch ones
+    (one range, two from two rounds on: 3,073 to 4,096 hits, or behind 96-patch
+    tiles), odd numbers of tiles in every kind."""
+    h = handles[prec]
+    rng = np.random.default_rng(17)
+    imgs = [rng.normal(0, 4, (W, T)).astype(np.float32) for W, T in [(200, 700), (90, 333), (37, 101)]]
+    dev = [t(im) for im in imgs]
+    n_all = 21000
+    p = rng.integers(0, 3, n_all)
+    hh = np.stack([p, rng.integers(0, np.array([200, 90, 37])[p]),
+                   rng.integers(0, np.array([700, 333, 101])[p])], 1).astype(np.int32)
+    d = t(hh)
+    want = np.concatenate([bits(pid.pointid_classify_planes(h, dev, d[a:a + 1000].contiguous()))
+                           for a in range(0, n_all, 1000)])
+    for n in (2049, 3072, 3073, 3137, 4095, 4096, 4097, 5121, 6143, 6145, 7000, 8193, 9217, 12287, 12289,
+              13000, 15361, 16384, 18433, 20641, 21000):
+        say(f"{prec} {n} gathered hits")
+        assert np.array_equal(bits(pid.pointid_classify_planes(h, dev, d[:n].contiguous())), want[:n]), n
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp8"])
 def test_block_shapes_at_their_edges(pid, handles, prec):
     """Batches on both sides of every change of a block shape on a 256-CU device
