@@ -4,11 +4,12 @@
 // patches themselves (rows.h): no patch is written and read back.
 //
 // Arithmetic.  Every fp32 operand (pixel, filter, map value, FC1 weight) is
-// taken as the exact sum of three bf16 values, high + middle + low (3 x 8
-// significand bits), and a product as the six of its nine partial products
+// taken as the exact sum of three bf16 values, high + middle + low, each the rest
+// rounded to nearest, and a product as the six of its nine partial products
 // that reach fp32's precision: hh, hm, mh, mm, hl, lh.  Each partial product is
 // exact and all are added in fp32 MFMA accumulators; what is left out is below
-// 2^-22 of a product at most (2^-25 on average).  The bf16 MFMA runs at 16 times
+// 2^-24.2 of a product (2^-27.5 in the mean square), less than fp32 rounds off a
+// product (2^-24 and 2^-25.2).  The bf16 MFMA runs at 16 times
 // the rate of the fp32 one, so six of them take 3/8 of its time (event of 50,000
 // hits: 11.7 ms per call with fp32 MFMAs, 6.26 here).  It is no less precise:
 // against the network in 64 bits the event's scores are off by a relative 1.6e-6
@@ -91,17 +92,20 @@ struct Block {
   static_assert(kLds * 4 <= 160 * 1024 && kPer % kPass == 0 && kQ * kMT % kSets == 0 && kRowAll % 64 == 0, "block");
 };
 
-// a == high + middle + low exactly, each a bf16 value in the upper half of its
-// word: the significand cut after 8 and 16 bits.  (Infinity gives NaN parts.)
-__device__ __forceinline__ void cut3(float a, uint32_t& h, uint32_t& m, uint32_t& l) {
-  h = __float_as_uint(a) & 0xFFFF0000u;
-  const float r = a - __uint_as_float(h);
-  m = __float_as_uint(r) & 0xFFFF0000u;
-  l = __float_as_uint(r - __uint_as_float(m));
-}
-// the upper halves of a and b, a's in the low half
-__device__ __forceinline__ uint32_t uppers(uint32_t a, uint32_t b) {
-  return __builtin_amdgcn_perm(b, a, 0x07060302u);
+// a == high + middle + low exactly, and b, a's parts in the low halves: high is a
+// rounded to bf16 (nearest even), middle the rest of at most 16 bits rounded, low
+// the rest of at most 8.  (Below 2^-109 the low part is cut off under 2^-133.)
+// Cut instead of rounded, the parts cost 1 % less time (event) and a product can
+// be off by 2^-22.7.
+__device__ __forceinline__ void split3(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+  using Op = Op16<false>;
+  h = Op::pack(a, b);
+  a -= __uint_as_float(h << 16);
+  b -= __uint_as_float(h & 0xFFFF0000u);
+  m = Op::pack(a, b);
+  a -= __uint_as_float(m << 16);
+  b -= __uint_as_float(m & 0xFFFF0000u);
+  l = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);   // the upper halves
 }
 __device__ __forceinline__ floatx4 mfma(const uint4& a, const uint4& b, const floatx4& c) {
   return Op16<false>::mfma(a, b, c);
@@ -189,18 +193,17 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
       if (c < B::kRowAll) {
         const int p = c / kRowChunks, h = c - (c / kRowChunks) * kRowChunks;
         const rowx4 x = row_chunk_finish(desc + p, r, h, row.v[k], (row.kinds >> 2 * k) & 3);
-        uint32_t hi[4], mi[4], lo[4];
         bool inf = false;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          cut3(x[j], hi[j], mi[j], lo[j]);
-          inf |= (__float_as_uint(x[j]) << 1) == 0xFF000000u;
-        }
+        for (int j = 0; j < 4; ++j) inf |= (__float_as_uint(x[j]) << 1) == 0xFF000000u;
         if (inf) flags[p] = 1;
+        uint2 hi, mi, lo;
+        split3(x[0], x[1], hi.x, mi.x, lo.x);
+        split3(x[2], x[3], hi.y, mi.y, lo.y);
         uint32_t* d = lds + r % kRing * kSlot + p * kRP + h * 2;
-        *reinterpret_cast<uint2*>(d) = make_uint2(uppers(hi[0], hi[1]), uppers(hi[2], hi[3]));
-        *reinterpret_cast<uint2*>(d + B::kPart) = make_uint2(uppers(mi[0], mi[1]), uppers(mi[2], mi[3]));
-        *reinterpret_cast<uint2*>(d + 2 * B::kPart) = make_uint2(uppers(lo[0], lo[1]), uppers(lo[2], lo[3]));
+        *reinterpret_cast<uint2*>(d) = hi;
+        *reinterpret_cast<uint2*>(d + B::kPart) = mi;
+        *reinterpret_cast<uint2*>(d + 2 * B::kPart) = lo;
       }
     }
   };
@@ -280,15 +283,10 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
 #pragma unroll
           for (int k = 0; k < kParts3; ++k) f[k] = filters[(k * 6 + tb) * 64 + lane];
           const floatx4 cb = mfma6(f, win, z);
-          uint32_t h[8], m[8], l[8];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            cut3(fmaxf(ca[e], 0.f), h[e], m[e], l[e]);
-            cut3(fmaxf(cb[e], 0.f), h[4 + e], m[4 + e], l[4 + e]);
-          }
-          b[i][0] = make_uint4(uppers(h[0], h[1]), uppers(h[2], h[3]), uppers(h[4], h[5]), uppers(h[6], h[7]));
-          b[i][1] = make_uint4(uppers(m[0], m[1]), uppers(m[2], m[3]), uppers(m[4], m[5]), uppers(m[6], m[7]));
-          b[i][2] = make_uint4(uppers(l[0], l[1]), uppers(l[2], l[3]), uppers(l[4], l[5]), uppers(l[6], l[7]));
+          split3(fmaxf(ca[0], 0.f), fmaxf(ca[1], 0.f), b[i][0].x, b[i][1].x, b[i][2].x);
+          split3(fmaxf(ca[2], 0.f), fmaxf(ca[3], 0.f), b[i][0].y, b[i][1].y, b[i][2].y);
+          split3(fmaxf(cb[0], 0.f), fmaxf(cb[1], 0.f), b[i][0].z, b[i][1].z, b[i][2].z);
+          split3(fmaxf(cb[2], 0.f), fmaxf(cb[3], 0.f), b[i][0].w, b[i][1].w, b[i][2].w);
         }
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(0);
