@@ -371,7 +371,7 @@ int run_network_fp32(pointid_handle h, const RowInput& in, int64_t n, float* sco
   if (e != hipSuccess) return hip_fail(e, "workspace (FC1 partials)");
   {
     KernelTimer kt("conv_fc1_f32", stream);
-    e = launch_conv_fc1_f32(in, n, h->w.fc1_frag, h->w.conv_frag, part, cus, stream);
+    e = launch_conv_fc1_f32(in, n, h->w, part, cus, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "conv_fc1_f32 launch");
   return run_tail(h, part, conv_fc1_f32_splits(), n, scores, stream, ws, reqs);
@@ -627,6 +627,7 @@ int pointid_create(const pointid_weights* w, int precision, int device,
   hnd->device = device;
   hnd->precision = precision;
   hnd->w.precision = precision;
+  if (precision == POINTID_FP32) hnd->w.conv_limit = conv_fc1_f32_limit(w->conv_w, w->conv_b);
   const bool half = precision != POINTID_FP32;
   const bool fp8 = precision == POINTID_FP8;
   // 8-bit handles: per FC1 output n the exponent k_n, the largest with

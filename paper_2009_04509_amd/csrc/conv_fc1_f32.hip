@@ -38,6 +38,15 @@
 // MFMAs per range and group and a fixed tree over the groups, whatever the shape
 // of the block.  Small batches share the 128 outputs over 2 or 4 blocks
 // (`kParts`; each computes the conv).
+//
+// Range.  A finite pixel that could take a conv sum past a quarter of fp32's
+// range, an infinite one or a NaN (ConvF32::limit: none of them occurs in charge
+// images), and FC1 sums that are not finite, have no place in three parts: the
+// block computes the sums of such a patch again in plain fp32, product by product,
+// so that infinities, NaNs and overflows come out as fp32 arithmetic gives them.
+#include <algorithm>
+#include <cmath>
+
 #include "internal.h"
 #include "op16.h"
 #include "rows.h"
@@ -63,9 +72,17 @@ constexpr int64_t kWeightBytes = (kPairs + kWaves) * kParts3 * kFc1PairBytes16;
 // first pair of range s (whole groups of 4 pairs: 120 or 124 pairs each)
 __host__ __device__ constexpr int range_begin(int s) { return 4 * (kPairs / 4 * s / kSplits); }
 
+// The conv filters and biases in fp32, and the magnitude below which a pixel can
+// be taken apart (see plain_patch).
+struct ConvF32 {
+  const float* w;
+  const float* b;
+  float limit;
+};
+
 // Block of 16 kTiles patches and 128 / kParts outputs.  LDS (dwords): ring
-// [part][row][patch] | conv filters | row descriptors | infinity flags; the
-// reduction reuses it from the start.
+// [part][row][patch] | conv filters | row descriptors | flags of patches to
+// compute in plain fp32; the reduction reuses it up to the descriptors.
 template <int kTiles, int kParts>
 struct Block {
   static constexpr int kBt = 16 * kTiles;
@@ -73,7 +90,6 @@ struct Block {
   static constexpr int kSlot = kBt * kRP;                  // dwords per row and part
   static constexpr int kPart = kRing * kSlot;
   static constexpr int kConvOff = kParts3 * kPart;
-  static constexpr int kDescOff = kConvOff + kParts3 * 6 * 64 * 4;
   // the reduction, at most 16 accumulator tiles a pass, of each one from each
   // of the other 7 waves
   static constexpr int kSlots = kMT * kTiles;
@@ -81,9 +97,9 @@ struct Block {
   static constexpr int kPass = kPer < 2 ? kPer : 2;        // of them per pass
   static constexpr int kOwners = kSlots / kPer;
   static constexpr int kRed = kOwners * kPass * (kWaves - 1) * 256;
-  static constexpr int kDesc = kBt * 4;
-  static constexpr int kMain = kDescOff + kDesc;
-  static constexpr int kFlagOff = kMain > kRed ? kMain : kRed;
+  static constexpr int kConvEnd = kConvOff + kParts3 * 6 * 64 * 4;
+  static constexpr int kDescOff = kConvEnd > kRed ? kConvEnd : kRed;
+  static constexpr int kFlagOff = kDescOff + kBt * 4;
   static constexpr int kLds = kFlagOff + kBt;
   // register sets of weights: one wave's L2 latency is behind as many output tiles
   static constexpr int kSets = kTiles == 4 ? 3 : 6;
@@ -127,12 +143,79 @@ __device__ __forceinline__ void mfma6x2(const uint4 (&a)[kParts3], const uint4 (
   }
 }
 
+// The FC1 sums of one patch (row descriptor d) over pairs P0 .. P_end - 1 in
+// plain fp32, by the whole block, to dst[128] for the outputs of [o_lo, o_hi).
+// The window of a pair has six columns, the taps of the one that a position does
+// not use are 0, as in the MFMA kernels: an infinite or NaN pixel makes the maps
+// of both positions NaN, which the ReLU takes to 0.  0.15 ms a patch and
+// block; LDS is free to use from the start.
+constexpr int kPlainPairs = 4;                // pairs of a pass, one per 128 threads
+constexpr int kPlainRows = 11;                // input rows of a range of at most 31 groups of 4 pairs
+static_assert((4 * ((kPairs / 4 + kSplits - 1) / kSplits) - 1 + kPairsPerRow - 1) / kPairsPerRow + kK <= kPlainRows, "rows");
+__device__ __forceinline__ void plain_patch(float* lds, const uint4& d, int P0, int P_end, int o_lo, int o_hi,
+                                            const uint4* __restrict__ w1p, const ConvF32& conv, float* dst) {
+  typedef __attribute__((address_space(1))) const float* gptr;
+  static_assert(kPlainPairs * 128 == kThreads && kPlainPairs * 2 * kCh <= kThreads, "threads of a pass");
+  constexpr int kMaps = kPlainRows * kPatch, kSums = kMaps + kPlainPairs * 2 * kCh;
+  const int tid = threadIdx.x, r0 = P0 / kPairsPerRow, rows = (P_end - 1) / kPairsPerRow + kK - r0;
+  __syncthreads();
+  for (int i = tid; i < rows * kPatch; i += kThreads) {
+    const uint32_t r = (uint32_t)(r0 + i / kPatch), c = (uint32_t)(i % kPatch);
+    const bool in = r >= (d.w & 255u) && r < ((d.w >> 8) & 255u) && c >= ((d.w >> 16) & 255u) && c < d.w >> 24;
+    lds[i] = in ? ((gptr)row_chunk_addr(d, (int)r, 0))[c] : 0.f;
+  }
+  const int o = tid & 127, g = tid >> 7;
+  float acc = 0.f;
+  for (int P = P0; P < P_end; P += kPlainPairs) {
+    __syncthreads();
+    if (tid < kPlainPairs * 2 * kCh) {
+      const int ch = tid % kCh, s = tid / kCh % 2, Pm = P + tid / (2 * kCh);
+      const float* x = lds + (Pm / kPairsPerRow - r0) * kPatch + 2 * (Pm % kPairsPerRow);
+      float m = 0.f;
+      for (int f = 0; f < 30; ++f) {
+        const int u = f / 6, c = f % 6 - s;
+        m = fmaf(c >= 0 && c < kK ? conv.w[ch * kK * kK + u * kK + c] : 0.f, x[u * kPatch + f % 6], m);
+      }
+      lds[kMaps + tid] = fmaxf(m + conv.b[ch], 0.f);
+    }
+    __syncthreads();
+    if (o >= o_lo && o < o_hi) {
+      // the weights from their parts (an exact sum), in the order of pack_fc1_f32_kernel
+      float sum = 0.f;
+      for (int k = 0; k < kQ * 4; ++k) {
+        const int q = k >> 2, sub = k & 3;
+        const uint4* w = w1p + (((int64_t)(P + g) * kQ + q) * kMTiles + o / 16) * kParts3 * 64 + 16 * sub + (o & 15);
+        const uint4 part[kParts3] = {w[0], w[64], w[128]};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          float v[kParts3];
+#pragma unroll
+          for (int t = 0; t < kParts3; ++t) {
+            const uint32_t dw = j < 2 ? part[t].x : j < 4 ? part[t].y : j < 6 ? part[t].z : part[t].w;
+            v[t] = __uint_as_float(j & 1 ? dw & 0xFFFF0000u : dw << 16);
+          }
+          const int st = 2 * q + (j >> 2);
+          sum = fmaf((v[0] + v[1]) + v[2],
+                     lds[kMaps + g * 2 * kCh + st / 3 * kCh + 16 * (st % 3) + 4 * sub + (j & 3)], sum);
+        }
+      }
+      acc += sum;
+    }
+  }
+  __syncthreads();
+  lds[kSums + tid] = acc;
+  __syncthreads();
+  if (tid < 128 && o >= o_lo && o < o_hi)
+    dst[o] = (lds[kSums + tid] + lds[kSums + 128 + tid]) + (lds[kSums + 256 + tid] + lds[kSums + 384 + tid]);
+}
+
 // One block: patches p_base .. p_base + kBt - 1 (those past the batch hold
 // zeros and are not stored), range `split`, output part `opart`.
 template <int kTiles, int kParts>
 __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int opart, int64_t p_base,
                                                    const HitSource& src, const uint4* __restrict__ w1p,
-                                                   const uint4* __restrict__ convp, float* __restrict__ part) {
+                                                   const uint4* __restrict__ convp, const ConvF32& conv,
+                                                   float* __restrict__ part) {
   using B = Block<kTiles, kParts>;
   constexpr int kSlot = B::kSlot, kMT = B::kMT, kSets = B::kSets, kBt = B::kBt;
   const int tid = threadIdx.x;
@@ -161,7 +244,7 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
 
   // ---- patch rows
   uint4* desc = reinterpret_cast<uint4*>(lds + B::kDescOff);
-  uint32_t* flags = lds + B::kFlagOff;       // patches with an infinite pixel
+  uint32_t* flags = lds + B::kFlagOff;       // patches to compute in plain fp32
   if (tid < kBt) {
     desc[tid] = src.get(p_base + tid);
     flags[tid] = 0;
@@ -193,10 +276,10 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
       if (c < B::kRowAll) {
         const int p = c / kRowChunks, h = c - (c / kRowChunks) * kRowChunks;
         const rowx4 x = row_chunk_finish(desc + p, r, h, row.v[k], (row.kinds >> 2 * k) & 3);
-        bool inf = false;
+        bool fits = true;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) inf |= (__float_as_uint(x[j]) << 1) == 0xFF000000u;
-        if (inf) flags[p] = 1;
+        for (int j = 0; j < 4; ++j) fits &= fabsf(x[j]) < conv.limit;
+        if (!fits) flags[p] = 1;
         uint2 hi, mi, lo;
         split3(x[0], x[1], hi.x, mi.x, lo.x);
         split3(x[2], x[3], hi.y, mi.y, lo.y);
@@ -336,14 +419,24 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
 #pragma unroll
         for (int g = 0; g < kWaves; ++g)
           v[g] = g == g0 ? acc[q / kTiles][q % kTiles] : red[entry(o, j, g - (g > g0 ? 1 : 0))];
-        floatx4 sum = ((v[0] + v[4]) + (v[1] + v[5])) + ((v[2] + v[6]) + (v[3] + v[7]));
+        const floatx4 sum = ((v[0] + v[4]) + (v[1] + v[5])) + ((v[2] + v[6]) + (v[3] + v[7]));
         const int p = 16 * (q % kTiles) + col, out = 16 * (opart * kMT + q / kTiles) + 4 * grp;
-        // an infinite pixel: its maps are infinite, and their FC1 sums NaN (the
-        // parts of an infinity would leave no trace behind the ReLU)
-        if (flags[p]) sum = (floatx4){__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+        const floatx4 z = sum * 0.f;
+        if (!((z[0] + z[1]) + (z[2] + z[3]) == 0.f)) flags[p] = 1;   // not finite
         if (p_base + p < src.n) __builtin_nontemporal_store(sum, reinterpret_cast<floatx4*>(dst + p * kFc1Out + out));
       }
     }
+  }
+
+  // ---- the patches without a place in three parts, one after the other (the
+  // stores above to their sums come before the barrier, these after it)
+  __syncthreads();
+  uint64_t todo = __ballot(lane < kBt && flags[lane < kBt ? lane : 0] != 0 && p_base + lane < src.n);
+  while (todo) {                             // the same in every wave
+    const int p = __ffsll((unsigned long long)todo) - 1;
+    todo &= todo - 1;
+    plain_patch(reinterpret_cast<float*>(lds), desc_from_lds(desc + p), P0, P_end, opart * kMT * 16,
+                (opart + 1) * kMT * 16, w1p, conv, dst + p * kFc1Out);
   }
 }
 
@@ -353,28 +446,28 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
 // eight are 3 % longer.
 __global__ __launch_bounds__(kThreads, 1) void conv_fc1_f32_kernel(HitSource src, int64_t n_big,
                                                                    const uint4* __restrict__ w1p,
-                                                                   const uint4* __restrict__ convp,
+                                                                   const uint4* __restrict__ convp, ConvF32 conv,
                                                                    float* __restrict__ part) {
   __shared__ __attribute__((aligned(16))) uint32_t lds[Block<4, 1>::kLds];
   const int64_t t = blockIdx.x / kSplits;
   const int split = (int)((blockIdx.x + t / 32) % kSplits);
   if (t < n_big)
-    conv_fc1_f32_block<4, 1>(lds, split, 0, t * 64, src, w1p, convp, part);
+    conv_fc1_f32_block<4, 1>(lds, split, 0, t * 64, src, w1p, convp, conv, part);
   else
-    conv_fc1_f32_block<2, 1>(lds, split, 0, n_big * 64 + (t - n_big) * 32, src, w1p, convp, part);
+    conv_fc1_f32_block<2, 1>(lds, split, 0, n_big * 64 + (t - n_big) * 32, src, w1p, convp, conv, part);
 }
 
 // Block b: split b % kSplits, then output part, then patch tile.
 template <int kTiles, int kParts>
 __global__ __launch_bounds__(kThreads, 1) void conv_fc1_f32_small_kernel(HitSource src,
                                                                          const uint4* __restrict__ w1p,
-                                                                         const uint4* __restrict__ convp,
+                                                                         const uint4* __restrict__ convp, ConvF32 conv,
                                                                          float* __restrict__ part) {
   __shared__ __attribute__((aligned(16))) uint32_t lds[Block<kTiles, kParts>::kLds];
   const int split = blockIdx.x % kSplits;
   const int64_t r = blockIdx.x / kSplits;
   conv_fc1_f32_block<kTiles, kParts>(lds, split, (int)(r % kParts), r / kParts * (16 * kTiles), src, w1p, convp,
-                                     part);
+                                     conv, part);
 }
 
 // The parts of a weight: rounded to nearest (their products' rest is then of
@@ -435,6 +528,22 @@ __global__ __launch_bounds__(64) void pack_conv_f32_kernel(const float* __restri
 }  // namespace
 
 int conv_fc1_f32_splits() { return kSplits; }
+// Pixels below the limit keep every sum of products of a conv, in whatever order
+// and by parts, below a quarter of fp32's range (parts may be of either sign and
+// add up to 1.02 times their value).  0, which no pixel is below, where a filter or
+// a bias leaves no room or is not finite itself.
+float conv_fc1_f32_limit(const float* conv_w, const float* conv_b) {
+  constexpr double kRoom = 0x1p126;
+  double limit = kRoom;
+  for (int k = 0; k < kCh; ++k) {
+    double sum = 0.0;
+    for (int i = 0; i < kK * kK; ++i) sum += std::fabs((double)conv_w[k * kK * kK + i]);
+    const double at = (kRoom - 1.02 * std::fabs((double)conv_b[k])) / std::max(1.02 * sum, 1.0);
+    limit = at < limit ? at : limit;
+    if (!(at > 0)) return 0.f;
+  }
+  return (float)limit;
+}
 int64_t conv_fc1_f32_weight_bytes() { return kWeightBytes; }
 
 // Small batches: patches per block and output parts, (0, 0) past 512 patches
@@ -483,22 +592,24 @@ hipError_t launch_pack_f32(const float* conv_w, const float* conv_b, const float
                        fc1_frag);
 }
 
-hipError_t launch_conv_fc1_f32(const RowInput& in, int64_t n, const uint4* w1p, const uint4* convp, float* part,
-                               int cus, hipStream_t stream) {
+hipError_t launch_conv_fc1_f32(const RowInput& in, int64_t n, const DeviceWeights& w, float* part, int cus,
+                               hipStream_t stream) {
   if (n <= 0) return hipSuccess;
+  const uint4 *w1p = w.fc1_frag, *convp = w.conv_frag;
+  const ConvF32 conv = {w.conv_w, w.conv_b, w.conv_limit};
   const HitSource src = hit_source(in, n);
   int tiles = 0, parts = 0;
   conv_fc1_f32_small(n, cus, &tiles, &parts);
   if (tiles) {
     const dim3 grid((unsigned)((n + 16 * tiles - 1) / (16 * tiles) * parts * kSplits));
-    auto go = [&](auto kernel) { return launch_kernel(kernel, grid, dim3(kThreads), 0, stream, src, w1p, convp, part); };
+    auto go = [&](auto kernel) { return launch_kernel(kernel, grid, dim3(kThreads), 0, stream, src, w1p, convp, conv, part); };
     if (tiles == 1) return go(conv_fc1_f32_small_kernel<1, 4>);
     return parts == 4 ? go(conv_fc1_f32_small_kernel<2, 4>) : go(conv_fc1_f32_small_kernel<2, 2>);
   }
   int64_t n_big = 0, n_small = 0;
   conv_fc1_f32_tiles(n, cus, &n_big, &n_small);
   return launch_kernel(conv_fc1_f32_kernel, dim3((unsigned)((n_big + n_small) * kSplits)), dim3(kThreads), 0, stream,
-                       src, n_big, w1p, convp, part);
+                       src, n_big, w1p, convp, conv, part);
 }
 
 }  // namespace pointid

@@ -103,7 +103,9 @@ struct DeviceWeights {
   const uint4* conv_frag;    // [2 shifts][3 channel tiles][64 lanes] x 8 halves
   const uint4* fc1_frag;     // [968 pairs][3 K-steps][8 output tiles][64 lanes] x 8 halves
   // fp32 handles (see conv_fc1_f32.hip): the same in three bf16 parts,
-  // conv_frag [part][shift][channel tile], fc1_frag [pair][K-step][output tile][part]
+  // conv_frag [part][shift][channel tile], fc1_frag [pair][K-step][output tile][part],
+  // and the magnitude from which on a pixel is computed with in plain fp32
+  float conv_limit;
   // 8-bit handles (see conv_fc1_8.hip): e4m3 fragments [968 pairs][8 output
   // tiles] x (64 lanes x 16 B, then 64 lanes x 8 B), and the factor 2^-k_n
   // the tail multiplies FC1 output n's sums by (nullptr on other handles)
@@ -211,6 +213,8 @@ hipError_t launch_conv_fc1_8(const RowInput& in, int64_t n, const uint8_t* w1p, 
 // for s < conv_fc1_f32_splits(), from the conv filters and FC1 weights in three
 // bf16 parts each (launch_pack_f32).
 constexpr int kF32Parts = 3;
+// DeviceWeights::conv_limit of the filters [48][25] and biases [48]
+float conv_fc1_f32_limit(const float* conv_w, const float* conv_b);
 int conv_fc1_f32_splits();
 int64_t conv_fc1_f32_weight_bytes();
 // Tiles of the launch over n patches on `cus` CUs: n_big of 64 patches, then
@@ -218,8 +222,8 @@ int64_t conv_fc1_f32_weight_bytes();
 // 128 / parts outputs (tiles = 0: not a small batch).
 void conv_fc1_f32_tiles(int64_t n, int cus, int64_t* n_big, int64_t* n_small);
 void conv_fc1_f32_small(int64_t n, int cus, int* tiles, int* parts);
-hipError_t launch_conv_fc1_f32(const RowInput& in, int64_t n, const uint4* w1p, const uint4* convp, float* part,
-                               int cus, hipStream_t stream);
+hipError_t launch_conv_fc1_f32(const RowInput& in, int64_t n, const DeviceWeights& w, float* part, int cus,
+                               hipStream_t stream);
 
 hipError_t launch_pack_f32(const float* conv_w, const float* conv_b, const float* fc1_w, uint4* conv_frag,
                            uint4* fc1_frag, hipStream_t stream);

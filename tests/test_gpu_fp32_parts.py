@@ -1,5 +1,7 @@
 """GPU: the fp32 path's arithmetic on three bf16 parts per operand and six of the
-nine partial products (conv_fc1_f32.hip): every product to fp32's precision."""
+nine partial products (conv_fc1_f32.hip): every product to fp32's precision, and
+what parts cannot hold (infinities, NaNs, values near the end of the range)
+as fp32 arithmetic gives it."""
 
 import sys
 
@@ -115,3 +117,66 @@ def test_single_products(pid, kind):
     say(f"{kind}: max {np.abs(e).max():.2f} rms {np.sqrt((e * e).mean()):.2f} mean {e.mean():.2f} x 2^-24")
     assert np.abs(e).max() <= (5.8 if kind == "any" else 2.05)
     assert kind == "any" or abs(e.mean()) <= 1.05
+
+
+def one_signed(w, sign):
+    return {**w, "fc1_w": sign * np.abs(w["fc1_w"])}
+
+
+@pytest.mark.parametrize("n", [3, 300, 600, 1100])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38, -3.0e38, 1e37])
+def test_pixels_out_of_range(pid, value, n):
+    """A few patches with an infinite, NaN or huge pixel, in every shape of block;
+    FC1 weights of one sign make infinite sums of either sign, of both signs NaN
+    ones (0 behind the ReLU).  The other patches keep their bits."""
+    base = synth.he_normal_weights()
+    P = synth.config4_patches(n, seed=n).astype(F)
+    clean = P.copy()
+    rng = np.random.default_rng(n)
+    at = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, 6)]))
+    for i in at:
+        P[i, rng.integers(0, 48), rng.integers(0, 48)] = value
+    P[at[0], 0, 0], P[at[1], 47, 47] = value, value      # pixels of one position, and of the last range
+    nets = {"both": base, "plus": one_signed(base, 1), "minus": one_signed(base, -1),
+            "small": {**base, "fc1_w": base["fc1_w"] * F(2.0**-100)}}
+    if np.isfinite(value):      # (with the others FC2's sums would pass the range in one order and not in another)
+        nets = {"small": nets["small"]}
+    for name, w in nets.items():
+        say(f"{value} {n} {name}")
+        got = classify(pid, w, P)
+        want = network(w, P[at])
+        assert np.array_equal(np.isnan(got[at]), np.isnan(want)), name
+        assert np.nanmax(np.abs(got[at] - want), initial=0) <= 1e-4, name
+        rest = np.setdiff1d(np.arange(n), at)
+        assert np.array_equal(got[rest].view(np.uint32), classify(pid, w, clean)[rest].view(np.uint32)), name
+
+
+@pytest.mark.parametrize("where, value", [("conv_w", np.inf), ("conv_w", np.nan), ("conv_b", -np.inf), ("conv_b", np.inf),
+                                          ("conv_w", 3.4e38), ("fc1_w", np.inf), ("fc1_w", -np.inf), ("fc1_w", np.nan),
+                                          ("fc1_w", 3.4e38)])
+def test_weights_out_of_range(pid, where, value):
+    """One weight past the range, all patches computed in plain fp32."""
+    base = {k: np.array(v) for k, v in synth.he_normal_weights().items()}
+    P = np.abs(synth.config4_patches(20, seed=3)).astype(F) + F(0.1)
+    for w in (base, one_signed(base, 1)):
+        w = {k: np.array(v) for k, v in w.items()}
+        v = w[where].reshape(-1)
+        v[len(v) // 2] = value
+        got, want = classify(pid, w, P), network(w, P)
+        say(where, value, want[0])
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        assert np.nanmax(np.abs(got - want), initial=0) <= 1e-4
+
+
+@pytest.mark.parametrize("value", [3.0e38, 1e30, 1e-30, 2.0**-100])
+def test_scale_of_one_pixel(pid, value):
+    """Patches of one pixel each, filters scaled to it: the scores rest on the pixel's parts alone."""
+    w = {k: np.array(v) for k, v in synth.he_normal_weights().items()}
+    rng = np.random.default_rng(2)
+    P = np.zeros((40, 48, 48), F)
+    for i in range(40):
+        P[i, rng.integers(0, 48), rng.integers(0, 48)] = value * (0.5 + 0.5 * rng.random()) * rng.choice([-1, 1])
+    w["conv_w"] = (w["conv_w"] / value * 100).astype(F)
+    got, want = classify(pid, w, P), network(w, P)
+    assert np.abs(want - want[0]).max() > 1e-2           # the pixel is what tells them apart
+    assert np.abs(got - want).max() <= 2e-6 * 100

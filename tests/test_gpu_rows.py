@@ -155,10 +155,11 @@ def test_block_shapes_at_their_edges(pid, handles, prec):
 
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.0e38, 1e-30])
 def test_fp32_extreme_pixels(pid, handles, value):
-    """One extreme pixel per patch: an infinite one makes every FC1 sum NaN, which
-    the ReLU takes to 0 as it takes a NaN map value to 0; a finite one is an fp32
-    number like any other, to the last bit of its bf16 parts.  Against the
-    network in 64 bits, the tolerance that of the other fp32 tests."""
+    """One extreme pixel in every other patch: an infinite one makes every FC1 sum NaN
+    (weights of both signs), which the ReLU takes to 0 as it takes a NaN map value
+    to 0, so that these patches all have the scores of the biases; a finite one
+    leaves the other patches as they are.  Against the network in 64 bits, the
+    tolerance that of the other fp32 tests."""
     h = handles["fp32"]
     w = {k: np.asarray(v, np.float64) for k, v in synth.he_normal_weights().items()}
     P = synth.config4_patches(40, seed=7).astype(np.float32)
@@ -179,6 +180,7 @@ def test_fp32_extreme_pixels(pid, handles, value):
         assert np.isfinite(h1).all()
     if np.isinf(value):
         assert (h1[1::2] == 0).all()
+        assert np.array_equal(got[1::2].view(np.uint32), np.repeat(got[1:2], 20, 0).view(np.uint32))
     if value == 3.0e38:                                  # past fp32's range further on: only the others
         got, h1 = got[::2], h1[::2]
     h2 = np.maximum(h1 @ w["fc2_w"] + w["fc2_b"], 0)
