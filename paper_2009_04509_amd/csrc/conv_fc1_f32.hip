@@ -442,19 +442,21 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
 
 // Tiles t < n_big hold 64 patches, the ones after them 32.  Block b runs on XCD
 // b % 8, whose L2 the blocks there share for their range's weights; the ranges
-// move on by one XCD every 32 tiles (a round of 256 CUs), because two of the
-// eight are 3 % longer.
+// move on by one XCD every round of the CUs (a row of the grid), because two of
+// the eight are 3 % longer.
 __global__ __launch_bounds__(kThreads, 1) void conv_fc1_f32_kernel(HitSource src, int64_t n_big,
                                                                    const uint4* __restrict__ w1p,
                                                                    const uint4* __restrict__ convp, ConvF32 conv,
                                                                    float* __restrict__ part) {
   __shared__ __attribute__((aligned(16))) uint32_t lds[Block<4, 1>::kLds];
-  const int64_t t = blockIdx.x / kSplits;
-  const int split = (int)((blockIdx.x + t / 32) % kSplits);
+  const int64_t t = blockIdx.y * (gridDim.x / kSplits) + blockIdx.x / kSplits;
+  const int split = (int)((blockIdx.x + blockIdx.y) % kSplits);
+  const int64_t p_base = t < n_big ? t * 64 : n_big * 64 + (t - n_big) * 32;
+  if (p_base >= src.n) return;               // (the last row)
   if (t < n_big)
-    conv_fc1_f32_block<4, 1>(lds, split, 0, t * 64, src, w1p, convp, conv, part);
+    conv_fc1_f32_block<4, 1>(lds, split, 0, p_base, src, w1p, convp, conv, part);
   else
-    conv_fc1_f32_block<2, 1>(lds, split, 0, n_big * 64 + (t - n_big) * 32, src, w1p, convp, conv, part);
+    conv_fc1_f32_block<2, 1>(lds, split, 0, p_base, src, w1p, convp, conv, part);
 }
 
 // Block b: split b % kSplits, then output part, then patch tile.
@@ -546,6 +548,9 @@ float conv_fc1_f32_limit(const float* conv_w, const float* conv_b) {
 }
 int64_t conv_fc1_f32_weight_bytes() { return kWeightBytes; }
 
+// Tiles that one round of the CUs holds.
+static int64_t tiles_per_round(int cus) { return cus >= kSplits ? cus / kSplits : 1; }
+
 // Small batches: patches per block and output parts, (0, 0) past 512 patches
 // on 256 CUs.  The shapes whose blocks fit one round of the CUs, by the time of
 // a K-step in the block (two waves per SIMD, 16 cycles per MFMA; 3 KiB of
@@ -554,7 +559,7 @@ int64_t conv_fc1_f32_weight_bytes() { return kWeightBytes; }
 // quarter 1,540, half 2,300; 32 patches and all outputs 3,840 (the blocks of
 // the other kernel).
 void conv_fc1_f32_small(int64_t n, int cus, int* tiles, int* parts) {
-  const int64_t per_round = cus >= kSplits ? cus / kSplits : 1;
+  const int64_t per_round = tiles_per_round(cus);
   *tiles = *parts = 0;
   if ((n + 15) / 16 * 4 <= per_round) {
     *tiles = 1;
@@ -572,7 +577,7 @@ void conv_fc1_f32_small(int64_t n, int cus, int* tiles, int* parts) {
 // rest is cut into tiles of 32 when those fit in one round, which then takes
 // about half as long.
 void conv_fc1_f32_tiles(int64_t n, int cus, int64_t* n_big, int64_t* n_small) {
-  const int64_t per_round = cus >= kSplits ? cus / kSplits : 1;     // tiles per round
+  const int64_t per_round = tiles_per_round(cus);
   int64_t big = n / (64 * per_round) * per_round;
   const int64_t rest = n - big * 64;
   int64_t small = (rest + 31) / 32;
@@ -608,8 +613,9 @@ hipError_t launch_conv_fc1_f32(const RowInput& in, int64_t n, const DeviceWeight
   }
   int64_t n_big = 0, n_small = 0;
   conv_fc1_f32_tiles(n, cus, &n_big, &n_small);
-  return launch_kernel(conv_fc1_f32_kernel, dim3((unsigned)((n_big + n_small) * kSplits)), dim3(kThreads), 0, stream,
-                       src, n_big, w1p, convp, conv, part);
+  const int64_t round = tiles_per_round(cus), all = n_big + n_small;
+  const dim3 grid((unsigned)((all < round ? all : round) * kSplits), (unsigned)((all + round - 1) / round));
+  return launch_kernel(conv_fc1_f32_kernel, grid, dim3(kThreads), 0, stream, src, n_big, w1p, convp, conv, part);
 }
 
 }  // namespace pointid
