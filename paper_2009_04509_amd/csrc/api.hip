@@ -442,18 +442,18 @@ int classify_table(pointid_handle h, const PlaneTable& planes, const RequestTabl
   in.reqs = &reqs;
   in.div = tick_div;
   if (!direct) {
-    void* patches = nullptr;
-    e = ws.get(patch_bytes(n), &patches);
+    uint16_t* patches = nullptr;
+    e = ws.get(patch_bytes(n), (void**)&patches);
     if (e != hipSuccess) return hip_fail(e, "workspace (patches)");
     {
       KernelTimer kt("gather", stream);
       const int dt = fp8 ? POINTID_FP16 : h->precision;
       e = scores ? launch_gather(planes, reqs.hits[0], reqs.plane[0] < 0 ? 3 : 2, n, patches, dt, stream,
                                  tick_div)
-                 : launch_gather_requests(planes, reqs, patches, dt, stream);
+                 : launch_gather_requests(planes, reqs, patches, dt == POINTID_FP16, stream);
     }
     if (e != hipSuccess) return hip_fail(e, "gather launch");
-    in.patches16 = static_cast<const uint16_t*>(patches);
+    in.patches16 = patches;
   }
   if (fp8) return run_network_8(h, in, n, scores, cus, stream, ws, out);
   return fp32 ? run_network_fp32(h, in, n, scores, cus, stream, ws, out)
@@ -963,7 +963,7 @@ int pointid_classify_patches(pointid_handle h, const float* patches, int64_t n,
   if (e != hipSuccess) return hip_fail(e, "workspace (16-bit patches)");
   {
     KernelTimer kt("patches_to_16", stream);
-    e = launch_patches_to_16(true, patches, n, pb, stream);
+    e = launch_patches_to_fp16(patches, n, pb, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "16-bit cast launch");
   in.patches16 = pb;

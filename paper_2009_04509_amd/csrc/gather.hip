@@ -193,14 +193,14 @@ __global__ __launch_bounds__(256) void gather_kernel(PlaneTable planes, Src src,
   }
 }
 
-// Elementwise fp32 -> 16-bit (RNE) for pre-cut patches: 8 values per thread.
-template <bool kFp16>
-__global__ __launch_bounds__(256) void to_16_kernel(const float4* __restrict__ in, int64_t n8,
-                                                    uint4* __restrict__ out) {
+// Elementwise fp32 -> fp16 (RNE) for the pre-cut patches of 8-bit handles: 8
+// values per thread.
+__global__ __launch_bounds__(256) void to_fp16_kernel(const float4* __restrict__ in, int64_t n8,
+                                                      uint4* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n8) return;
   const float4 a = in[2 * i], b = in[2 * i + 1];
-  using Op = Op16<kFp16>;
+  using Op = Op16<true>;
   out[i] = make_uint4(Op::pack(a.x, a.y), Op::pack(a.z, a.w), Op::pack(b.x, b.y),
                       Op::pack(b.z, b.w));
 }
@@ -289,40 +289,38 @@ hipError_t device_cus(int* cus) {
                          : hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
 }
 
-hipError_t launch_patches_to_16(bool fp16, const float* in, int64_t n, uint16_t* out,
-                                hipStream_t stream) {
+hipError_t launch_patches_to_fp16(const float* in, int64_t n, uint16_t* out, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
   const int64_t n8 = n * kPatchPix / 8;
   const dim3 grid((unsigned)((n8 + 255) / 256));
   const float4* src = reinterpret_cast<const float4*>(in);
   uint4* dst = reinterpret_cast<uint4*>(out);
-  if (fp16) return launch_kernel(to_16_kernel<true>, grid, dim3(256), 0, stream, src, n8, dst);
-  return launch_kernel(to_16_kernel<false>, grid, dim3(256), 0, stream, src, n8, dst);
+  return launch_kernel(to_fp16_kernel, grid, dim3(256), 0, stream, src, n8, dst);
 }
 
-template <class Src>
-hipError_t launch_gather_src(const PlaneTable& planes, const Src& src, int64_t n, void* out,
-                             int out_dtype, hipStream_t stream) {
+template <int kOut, class Src>
+static hipError_t launch_gather_src(const PlaneTable& planes, const Src& src, int64_t n, void* out,
+                                    hipStream_t stream) {
   if (n <= 0) return hipSuccess;
   const dim3 grid((unsigned)((n + kWaves - 1) / kWaves));
-  if (out_dtype == POINTID_BF16)
-    return launch_kernel(gather_kernel<POINTID_BF16, Src>, grid, dim3(256), 0, stream, planes, src, n, out);
-  if (out_dtype == POINTID_FP16)
-    return launch_kernel(gather_kernel<POINTID_FP16, Src>, grid, dim3(256), 0, stream, planes, src, n, out);
-  return launch_kernel(gather_kernel<POINTID_FP32, Src>, grid, dim3(256), 0, stream, planes, src, n, out);
+  return launch_kernel(gather_kernel<kOut, Src>, grid, dim3(256), 0, stream, planes, src, n, out);
 }
 
 hipError_t launch_gather(const PlaneTable& planes, const int32_t* hits,
                          int hit_stride, int64_t n, void* out, int out_dtype,
                          hipStream_t stream, int tick_div) {
-  return launch_gather_src(planes, HitArray{hits, hit_stride, tick_div}, n, out, out_dtype,
-                           stream);
+  const HitArray src{hits, hit_stride, tick_div};
+  if (out_dtype == POINTID_BF16) return launch_gather_src<POINTID_BF16>(planes, src, n, out, stream);
+  if (out_dtype == POINTID_FP16) return launch_gather_src<POINTID_FP16>(planes, src, n, out, stream);
+  return launch_gather_src<POINTID_FP32>(planes, src, n, out, stream);
 }
 
-hipError_t launch_gather_requests(const PlaneTable& planes, const RequestTable& reqs, void* out,
-                                  int out_dtype, hipStream_t stream) {
+hipError_t launch_gather_requests(const PlaneTable& planes, const RequestTable& reqs, uint16_t* out, bool fp16,
+                                  hipStream_t stream) {
   if (reqs.n < 1 || reqs.n > kMaxRequests) return hipErrorInvalidValue;
-  return launch_gather_src(planes, RequestHits{reqs}, reqs.start[reqs.n], out, out_dtype, stream);
+  const RequestHits src{reqs};
+  return fp16 ? launch_gather_src<POINTID_FP16>(planes, src, reqs.start[reqs.n], out, stream)
+              : launch_gather_src<POINTID_BF16>(planes, src, reqs.start[reqs.n], out, stream);
 }
 
 }  // namespace pointid

@@ -150,13 +150,13 @@ struct RequestTable {
   int32_t n;
 };
 
-// Gather of the hits of the requests of `reqs` into patches [start[n]][48][48].
-hipError_t launch_gather_requests(const PlaneTable& planes, const RequestTable& reqs, void* out,
-                                  int out_dtype, hipStream_t stream);
+// Gather of the hits of the requests of `reqs` into fp16 or bf16 patches
+// [start[n]][48][48] (fp32 handles read their rows from the planes).
+hipError_t launch_gather_requests(const PlaneTable& planes, const RequestTable& reqs, uint16_t* out, bool fp16,
+                                  hipStream_t stream);
 
-// Round fp32 patches [n][2304] to bf16 or fp16 (RNE) bit patterns.
-hipError_t launch_patches_to_16(bool fp16, const float* in, int64_t n, uint16_t* out,
-                                hipStream_t stream);
+// Round fp32 patches [n][2304] to fp16 (RNE) bit patterns.
+hipError_t launch_patches_to_fp16(const float* in, int64_t n, uint16_t* out, hipStream_t stream);
 
 // Repack fp32 conv/FC1 weights into 16-bit MFMA fragments.
 hipError_t launch_pack_16(bool fp16, const float* conv_w, const float* conv_b,
