@@ -23,6 +23,12 @@
 //          word and the bit from bit counts, and consecutive lanes store
 //          consecutive rows.  (A pass with one step per wave at a time, whatever
 //          its few hits, was bound by instruction issue: 39.6 us on the event.)
+//          Where a wave's steps hold 32 hits or more each, a step at a time costs
+//          less than the searches: lanes take 4 ticks each, and the step's ticks
+//          are put in order through LDS (event's planes, us per call with the
+//          searches and a step at a time: every local maximum, 85 of 256 ticks, 189
+//          and 155; those above 1.2 sigma of the noise, 26 a step, 122 and 115;
+//          above 1.6, 13 a step, 108 and 112; above 4, signal only, 82 and 90).
 // The image is read once (the bits are 1/32 of it), so the whole call is bound
 // by HBM reads of the image.
 #include "pointid.h"
@@ -192,11 +198,14 @@ __device__ __forceinline__ int nth_bit(uint32_t x, int r) {
   return pos;
 }
 
-// 64 steps of one wave: their first hit, bits, plane, wire and first tick.
+// 64 steps of one wave: their first hit, bits, plane, wire and first tick; a
+// step's hits in order (at most every second tick).
+constexpr int kDenseStep = 32;
 struct EmitStage {
   int32_t start[64];
   uint32_t bits[64][8];
   int32_t plane[64], row[64], tick[64];
+  int32_t order[kHitStep / 2];
 };
 
 __global__ __launch_bounds__(64 * kMaskWaves) void hits_emit_kernel(
@@ -274,28 +283,58 @@ __global__ __launch_bounds__(64 * kMaskWaves) void hits_emit_kernel(
     p0 = __builtin_amdgcn_readlane(p, 63);
     wave_lds_order();
     const int lim = (int)(found < capacity - base ? found : capacity - base);
-    for (int i = lane; i < lim; i += 64) {
-      int k = 0;                                         // the last step that starts at or before hit i
+    const int live = (int)(g1 - c < 64 ? g1 - c : 64);
+    if (found >= kDenseStep * live) {
+      // lane l with the ticks 4l .. 4l + 3 of a step
+      for (int k = 0; k < live; ++k) {                   // (wave-uniform)
+        const uint32_t x = sg.bits[k][lane >> 3] >> (4 * (lane & 7)) & 15u;
+        const int first = __builtin_amdgcn_readfirstlane(sg.start[k]);
+        if (first >= lim) break;
+        const int next = k < live - 1 ? __builtin_amdgcn_readfirstlane(sg.start[k + 1]) : found;
+        int pos = 0;
 #pragma unroll
-      for (int d = 32; d > 0; d >>= 1) k += sg.start[k + d] <= i ? d : 0;
-      int r = i - sg.start[k];
-      uint32_t x = 0;
-      int word = 0;
-      bool open = true;
+        for (int j = 0; j < 4; ++j) {
+          const uint64_t b = __ballot((x >> j & 1u) != 0);
+          pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, pos));
+        }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {                      // the word holding its r-th hit
-        const uint32_t v = sg.bits[k][j];
-        const int m = __popc(v);
-        const bool here = open && r < m;
-        x = here ? v : x;
-        word = here ? j : word;
-        open = open && !here;
-        r -= open ? m : 0;
+        for (int j = 0; j < 4; ++j)
+          if (x >> j & 1u) sg.order[pos++] = 4 * lane + j;
+        wave_lds_order();
+        const int n_k = (next < lim ? next : lim) - first;
+        const int p = sg.plane[k], w = sg.row[k], t = sg.tick[k];
+        for (int i = lane; i < n_k; i += 64) {
+          int32_t* o = hits + 3 * (base + first + i);
+          o[0] = p;
+          o[1] = w;
+          o[2] = t + sg.order[i];
+        }
+        wave_lds_order();
       }
-      int32_t* o = hits + 3 * (base + i);
-      o[0] = sg.plane[k];
-      o[1] = sg.row[k];
-      o[2] = sg.tick[k] + 32 * word + nth_bit(x, r);
+    } else {
+      for (int i = lane; i < lim; i += 64) {
+        int k = 0;                                         // the last step that starts at or before hit i
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) k += sg.start[k + d] <= i ? d : 0;
+        int r = i - sg.start[k];
+        uint32_t x = 0;
+        int word = 0;
+        bool open = true;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {                      // the word holding its r-th hit
+          const uint32_t v = sg.bits[k][j];
+          const int m = __popc(v);
+          const bool here = open && r < m;
+          x = here ? v : x;
+          word = here ? j : word;
+          open = open && !here;
+          r -= open ? m : 0;
+        }
+        int32_t* o = hits + 3 * (base + i);
+        o[0] = sg.plane[k];
+        o[1] = sg.row[k];
+        o[2] = sg.tick[k] + 32 * word + nth_bit(x, r);
+      }
     }
     wave_lds_order();
     base += found;

@@ -202,3 +202,33 @@ def test_planted_peaks(pid, shapes):
         assert np.array_equal(got.cpu().numpy()[:m], want[:m])
         assert (got.cpu().numpy()[m:] == -7).all()
     h.close()
+
+
+@pytest.mark.parametrize("threshold", [-1e30, 0.5, 1.0, 1.2, 2.0])
+def test_dense_hits(pid, threshold):
+    """Noise with from every local maximum (85 of 256 ticks) down to 5 hits a step, on
+    both sides of where the emit goes step by step; a plane of nothing but maxima
+    (every second tick), one of none; capacities that end inside a step."""
+    rng = np.random.default_rng(8)
+    shapes = [(300, 6000), (40, 999), (5, 256), (3, 257), (7, 1)]
+    imgs = [rng.normal(0, 1, s).astype(np.float32) for s in shapes]
+    imgs.append(np.tile(np.array([3, -3], np.float32), (30, 700)))
+    imgs.append(np.full((20, 300), -2e30, np.float32))
+    imgs.append(np.concatenate([imgs[0][:200], imgs[5][:2].repeat(100, 0)[:, :1].repeat(6000, 1)]).astype(np.float32))
+    dev = [torch.from_numpy(im).to(DEV) for im in imgs]
+    want = []
+    for p, im in enumerate(imgs):
+        x = np.pad(im, ((0, 0), (1, 1)), constant_values=-np.inf)
+        w, t = np.nonzero((im > np.float32(threshold)) & (im > x[:, :-2]) & (im >= x[:, 2:]))
+        want.append(np.stack([np.full(len(w), p), w, t], 1))
+    want = np.concatenate(want).astype(np.int32)
+    h = pid.pointid_create(synth.he_normal_weights(), "fp16", 0)
+    for cap in (len(want) + 5, len(want) // 2, 1001, 1):
+        say(f"dense hits above {threshold}: {len(want)}, capacity {cap}")
+        out = torch.full((cap + 3, 3), -7, dtype=torch.int32, device=DEV)
+        got, n = pid.pointid_find_hits(h, dev, threshold, capacity=cap, hits_out=out)
+        assert int(n.item()) == len(want)
+        m = min(cap, len(want))
+        assert np.array_equal(out.cpu().numpy()[:m], want[:m])
+        assert (out.cpu().numpy()[m:] == -7).all()
+    h.close()
