@@ -153,6 +153,11 @@ struct HitSource {
     return patches ? patch_row_desc(patches, p) : request_row_desc(planes, reqs, div, p);
   }
 };
+// Pre-cut patches alone, whose rows need no descriptor.
+struct PatchSource {
+  const float* patches;
+  int64_t n;
+};
 inline HitSource hit_source(const RowInput& in, int64_t n) {
   HitSource s = {};
   s.patches = in.patches;

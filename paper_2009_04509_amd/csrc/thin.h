@@ -91,6 +91,41 @@ __device__ __forceinline__ void thin_stage(uint32_t* lds, int64_t p_base, const 
   }
 }
 
+// The same for pre-cut patches: no descriptors, no barrier behind them, 8 pixels a
+// thread and turn (patches past the batch: its last one, never stored).  `safe`
+// is not needed.
+template <bool kFp16, int kBt, int kParts>
+__device__ __forceinline__ void thin_stage(uint32_t* lds, int64_t p_base, const PatchSource& src, int r0, int nrows,
+                                           const void*) {
+  using Op = Op16<kFp16>;
+  constexpr int kChunks = kPatch / 8, kRow = kBt * kChunks, kPer = (kThinRows * kRow + kThreads - 1) / kThreads;
+  const int tid = threadIdx.x, total = nrows * kRow;
+  rowx4 v[kPer][2];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int c = tid + k * kThreads;
+    if (c < total) {
+      const int j = c / kRow, cc = c - j * kRow, p = cc / kChunks, h = cc - p * kChunks;
+      const int64_t at = p_base + p < src.n ? p_base + p : src.n - 1;
+      const rowx4* from = reinterpret_cast<const rowx4*>(src.patches + at * kPatchPix + (r0 + j) * kPatch + 8 * h);
+      v[k][0] = __builtin_nontemporal_load(from);
+      v[k][1] = __builtin_nontemporal_load(from + 1);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int c = tid + k * kThreads;
+    if (c < total) {
+      const int j = c / kRow, cc = c - j * kRow, p = cc / kChunks, h = cc - p * kChunks;
+      uint32_t* d = lds + j * Thin<kBt, kParts>::kSlot + p * kRP + h * 4;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        *reinterpret_cast<uint2*>(d + 2 * i) =
+            make_uint2(Op::pack(v[k][i][0], v[k][i][1]), Op::pack(v[k][i][2], v[k][i][3]));
+    }
+  }
+}
+
 // The fixed-order reduction (g0 + g2) + (g1 + g3) over the position groups of a
 // thin block, and its store to part[.][p_base ..] (`dst`: the block's first
 // patch): each position group finishes a quarter of its output half's tiles
