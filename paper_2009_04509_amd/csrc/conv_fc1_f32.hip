@@ -11,10 +11,10 @@
 // 2^-24.2 of a product (2^-27.5 in the mean square), less than fp32 rounds off a
 // product (2^-24 and 2^-25.2).  The bf16 MFMA runs at 16 times
 // the rate of the fp32 one, so six of them take 3/8 of its time (event of 50,000
-// hits: 11.7 ms per call with fp32 MFMAs, 6.26 here).  It is no less precise:
-// against the network in 64 bits the event's scores are off by a relative 1.6e-6
-// (fp32 MFMAs: 1.8e-6), those of pre-cut patches by 5.7e-7 (6.4e-7), because a
-// K = 32 MFMA rounds its accumulator once per 32 inputs.
+// hits: 12.1 ms per call with fp32 MFMAs, 6.0 to 6.2 here).  Sums come out no less
+// precise: against the network in 64 bits the event's scores are off by a relative
+// 1.5e-6 (fp32 MFMAs: 1.7e-6), those of 235 pre-cut patches by 5.1e-7 (5.7e-7),
+// because a K = 32 MFMA rounds its accumulator once per 32 inputs.
 //
 // Map positions go in pairs (x, x+1), x even, in 8 contiguous ranges (split-K)
 // of 8 interleaved position groups, one per wave (wave g takes the pairs
@@ -317,6 +317,27 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
   }
   const bool const_slot = grp == 3;
 
+  // the window of patch tile i at the lane's four places
+  auto read_win = [&](const uint32_t (&base)[4], int i, uint4 (&win)[kParts3]) {
+#pragma unroll
+    for (int k = 0; k < kParts3; ++k) {
+      const uint32_t* s = lds + k * B::kPart + i * 16 * kRP;
+      win[k].x = s[base[0]];
+      win[k].y = s[base[1]];
+      win[k].z = s[base[2]];
+      win[k].w = s[base[3]];
+      asm volatile("" : "+v"(win[k].w));     // read by every lane: a select, not a branch
+      win[k].w = const_slot ? (k == 0 ? 0x00003F80u : 0u) : win[k].w;
+    }
+  };
+  // ReLU, and the maps of two conv tiles into an FC1 operand
+  auto split_maps = [](const floatx4& ca, const floatx4& cb, uint4 (&b)[kParts3]) {
+    split3(fmaxf(ca[0], 0.f), fmaxf(ca[1], 0.f), b[0].x, b[1].x, b[2].x);
+    split3(fmaxf(ca[2], 0.f), fmaxf(ca[3], 0.f), b[0].y, b[1].y, b[2].y);
+    split3(fmaxf(cb[0], 0.f), fmaxf(cb[1], 0.f), b[0].z, b[1].z, b[2].z);
+    split3(fmaxf(cb[2], 0.f), fmaxf(cb[3], 0.f), b[0].w, b[1].w, b[2].w);
+  };
+
   floatx4 acc[kMT][kTiles];
 #pragma unroll
   for (int m = 0; m < kMT; ++m)
@@ -344,32 +365,47 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
         const int ta = (q == 2) ? 3 + 1 : (q == 1 ? 2 : 0), tb = (q == 0) ? 1 : (q == 1 ? 3 : 3 + 2);
         // The conv is a chain of LDS reads, MFMAs and conversions; a wave in it
         // goes first, and the other wave of the SIMD fills its gaps with FC1
-        // (event, one box: 6.18 -> 6.01 ms, with the two chains in turn 5.96)
+        // (event: 6.18 -> 6.01 ms, with the two chains in turn 5.96)
         __builtin_amdgcn_s_setprio(2);
         uint4 b[kTiles][kParts3];
-#pragma unroll
-        for (int i = 0; i < kTiles; ++i) {
-          uint4 win[kParts3], f[kParts3];
+        if constexpr (kTiles < 4) {
+          // with registers for it, the chains of all tiles and both conv tiles in
+          // turn, then the conversions (235 patches 85.2 -> 83.4 us per call, 400 88.5
+          // -> 86.3: an MFMA otherwise waits for the one before it)
+          floatx4 ca[kTiles], cb[kTiles];
+          uint4 win[kTiles][kParts3], fa[kParts3], fb[kParts3];
 #pragma unroll
           for (int k = 0; k < kParts3; ++k) {
-            const uint32_t* s = lds + k * B::kPart + i * 16 * kRP;
-            f[k] = filters[(k * 6 + ta) * 64 + lane];
-            win[k].x = s[base[0]];
-            win[k].y = s[base[1]];
-            win[k].z = s[base[2]];
-            win[k].w = s[base[3]];
-            asm volatile("" : "+v"(win[k].w));   // read by every lane: a select, not a branch
-            win[k].w = const_slot ? (k == 0 ? 0x00003F80u : 0u) : win[k].w;
+            fa[k] = filters[(k * 6 + ta) * 64 + lane];
+            fb[k] = filters[(k * 6 + tb) * 64 + lane];
           }
-          const floatx4 z = {0.f, 0.f, 0.f, 0.f};
-          const floatx4 ca = mfma6(f, win, z);
 #pragma unroll
-          for (int k = 0; k < kParts3; ++k) f[k] = filters[(k * 6 + tb) * 64 + lane];
-          const floatx4 cb = mfma6(f, win, z);
-          split3(fmaxf(ca[0], 0.f), fmaxf(ca[1], 0.f), b[i][0].x, b[i][1].x, b[i][2].x);
-          split3(fmaxf(ca[2], 0.f), fmaxf(ca[3], 0.f), b[i][0].y, b[i][1].y, b[i][2].y);
-          split3(fmaxf(cb[0], 0.f), fmaxf(cb[1], 0.f), b[i][0].z, b[i][1].z, b[i][2].z);
-          split3(fmaxf(cb[2], 0.f), fmaxf(cb[3], 0.f), b[i][0].w, b[i][1].w, b[i][2].w);
+          for (int i = 0; i < kTiles; ++i) {
+            read_win(base, i, win[i]);
+            ca[i] = cb[i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+          }
+#pragma unroll
+          for (int k = 0; k < 6; ++k)
+#pragma unroll
+            for (int i = 0; i < kTiles; ++i) {
+              ca[i] = mfma(fa[kPartA[k]], win[i][kPartB[k]], ca[i]);
+              cb[i] = mfma(fb[kPartA[k]], win[i][kPartB[k]], cb[i]);
+            }
+#pragma unroll
+          for (int i = 0; i < kTiles; ++i) split_maps(ca[i], cb[i], b[i]);
+        } else {
+#pragma unroll
+          for (int i = 0; i < kTiles; ++i) {
+            uint4 win[kParts3], f[kParts3];
+            read_win(base, i, win);
+#pragma unroll
+            for (int k = 0; k < kParts3; ++k) f[k] = filters[(k * 6 + ta) * 64 + lane];
+            const floatx4 z = {0.f, 0.f, 0.f, 0.f};
+            const floatx4 ca = mfma6(f, win, z);
+#pragma unroll
+            for (int k = 0; k < kParts3; ++k) f[k] = filters[(k * 6 + tb) * 64 + lane];
+            split_maps(ca, mfma6(f, win, z), b[i]);
+          }
         }
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(0);
@@ -443,7 +479,9 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
 // Tiles t < n_big hold 64 patches, the ones after them 32.  Block b runs on XCD
 // b % 8, whose L2 the blocks there share for their range's weights; the ranges
 // move on by one XCD every round of the CUs (a row of the grid), because two of
-// the eight are 3 % longer.
+// the eight are 3 % longer.  256 registers, 54 more spilled: nearly all of them
+// around the first rows; the 64-patch loop holds 11 scratch loads and 6 stores
+// per 720 MFMAs.
 __global__ __launch_bounds__(kThreads, 1) void conv_fc1_f32_kernel(HitSource src, int64_t n_big,
                                                                    const uint4* __restrict__ w1p,
                                                                    const uint4* __restrict__ convp, ConvF32 conv,
