@@ -647,7 +647,7 @@ def serving(args, torch, pid, synth):
 
 def hit_finding(args, torch, pid, synth):
     """Config 3 planes: one step finds every hit of the event's 18 planes
-    (pointid_find_hits, three launches).  Algorithmic bytes of a step: the image
+    (pointid_find_hits, two launches).  Algorithmic bytes of a step: the image
     read once, plus 12 B written per hit found."""
     import oracle
     dev = "cuda:0"
@@ -680,9 +680,14 @@ def hit_finding(args, torch, pid, synth):
     pid.pointid_timing_enable(False)
     ms_step = evs[0].elapsed_time(evs[-1]) / args.steps
     per_step = np.array([evs[i].elapsed_time(evs[i + 1]) for i in range(args.steps)])
-    mask_bytes = rows * 24 * 32
-    work = {"hits_mask": image_bytes + mask_bytes + 4 * rows,
-            "hits_emit": mask_bytes + 4 * rows + 8 * rows + 12 * n_hits}
+    # the hit bits (32 B per step of 256 ticks), and one int32 count per worker (at most
+    # 8,192, with equal numbers of steps) and per block of 4 workers
+    steps = sum(a.shape[0] * -(-a.shape[1] // 256) for a in imgs_np)
+    workers = -(-steps // -(-steps // 8192))
+    count_bytes = 4 * (workers + -(-workers // 4))
+    mask_bytes = 32 * steps
+    work = {"hits_mask": image_bytes + mask_bytes + count_bytes,
+            "hits_emit": mask_bytes + count_bytes + 12 * n_hits}
     kern = {}
     for name, wb in work.items():
         tot, cnt = pid.pointid_timing_query(name)

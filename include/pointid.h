@@ -63,7 +63,10 @@ enum {
 
 /* arithmetic of a handle (pointid_create) or element type of a patch buffer */
 enum {
-    POINTID_FP32 = 0,           /* fp32 inputs, weights, accumulation */
+    POINTID_FP32 = 0,           /* fp32 inputs, weights, accumulation; conv and FC1
+                                   products from exact bf16 parts of both factors,
+                                   off by less than fp32 rounds off a product
+                                   (2^-24 of it) */
     POINTID_BF16 = 1,           /* bf16 patch, conv filter, conv output and FC1
                                    filter (round to nearest even); fp32
                                    accumulation, biases, FC2 and heads */
@@ -190,7 +193,7 @@ int pointid_classify_planes(pointid_handle h, const pointid_plane *planes,
  * cannot allocate (code under HIP graph capture, tight serving loops, hosts
  * that forbid hipMalloc): the same arguments, kernels and bits, with the
  * call's scratch (patches and split-K partials) in a fixed device array of
- * the library (104 MiB per GPU, held from the first call on a GPU until the
+ * the library (68 MiB per GPU, held from the first call on a GPU until the
  * process ends) instead of the handle's cache.  n_hits is at most 8192.
  * Every call on one GPU shares that array: calls that overlap on one GPU
  * (other streams or threads) race and must be ordered by the caller.  No
@@ -293,8 +296,8 @@ int pointid_batcher_wait(pointid_batcher b, uint64_t ticket);
  *   patches device fp32 [n][48][48] (row = wire, column = tick), 16-byte aligned
  *   scores  device fp32 [n][4], 16-byte aligned
  * 16-bit and 8-bit handles round the patches to their 16-bit type first
- * (8-bit handles: fp16), inside the fused kernel for up to 4,096 patches on
- * 16-bit handles, else in a separate pass.
+ * (8-bit handles: fp16), inside the fused kernel, past 16 patches per 8
+ * compute units (512 on 256) on 8-bit handles in a separate pass.
  * Errors: EINVAL (NULL handle, n < 0, NULL or misaligned pointer with n > 0),
  * ENOMEM, EHIP.
  */
