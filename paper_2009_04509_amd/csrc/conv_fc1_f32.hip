@@ -11,9 +11,9 @@
 // 2^-24.2 of a product (2^-27.5 in the mean square), less than fp32 rounds off a
 // product (2^-24 and 2^-25.2).  The bf16 MFMA runs at 16 times
 // the rate of the fp32 one, so six of them take 3/8 of its time (event of 50,000
-// hits: 12.1 ms per call with fp32 MFMAs, 6.0 to 6.2 here).  Sums come out no less
+// hits: 12.1 ms per call with fp32 MFMAs, 6.0 to 6.3 here).  Sums come out no less
 // precise: against the network in 64 bits the event's scores are off by a relative
-// 1.5e-6 (fp32 MFMAs: 1.7e-6), those of 235 pre-cut patches by 5.1e-7 (5.7e-7),
+// 1.7e-6 (fp32 MFMAs: 2.1e-6), those of 235 pre-cut patches by 5.2e-7 (5.6e-7),
 // because a K = 32 MFMA rounds its accumulator once per 32 inputs.
 //
 // Map positions go in pairs (x, x+1), x even, in 8 contiguous ranges (split-K)
@@ -317,18 +317,17 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
   }
   const bool const_slot = grp == 3;
 
-  // the window of patch tile i at the lane's four places
-  auto read_win = [&](const uint32_t (&base)[4], int i, uint4 (&win)[kParts3]) {
-#pragma unroll
-    for (int k = 0; k < kParts3; ++k) {
-      const uint32_t* s = lds + k * B::kPart + i * 16 * kRP;
-      win[k].x = s[base[0]];
-      win[k].y = s[base[1]];
-      win[k].z = s[base[2]];
-      win[k].w = s[base[3]];
-      asm volatile("" : "+v"(win[k].w));     // read by every lane: a select, not a branch
-      win[k].w = const_slot ? (k == 0 ? 0x00003F80u : 0u) : win[k].w;
-    }
+  // part k of the window of patch tile i at the lane's four places
+  auto read_win = [&](const uint32_t (&base)[4], int i, int k) {
+    const uint32_t* s = lds + k * B::kPart + i * 16 * kRP;
+    uint4 win;
+    win.x = s[base[0]];
+    win.y = s[base[1]];
+    win.z = s[base[2]];
+    win.w = s[base[3]];
+    asm volatile("" : "+v"(win.w));          // read by every lane: a select, not a branch
+    win.w = const_slot ? (k == 0 ? 0x00003F80u : 0u) : win.w;
+    return win;
   };
   // ReLU, and the maps of two conv tiles into an FC1 operand
   auto split_maps = [](const floatx4& ca, const floatx4& cb, uint4 (&b)[kParts3]) {
@@ -381,7 +380,8 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
           }
 #pragma unroll
           for (int i = 0; i < kTiles; ++i) {
-            read_win(base, i, win[i]);
+#pragma unroll
+            for (int k = 0; k < kParts3; ++k) win[i][k] = read_win(base, i, k);
             ca[i] = cb[i] = (floatx4){0.f, 0.f, 0.f, 0.f};
           }
 #pragma unroll
@@ -396,15 +396,20 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
         } else {
 #pragma unroll
           for (int i = 0; i < kTiles; ++i) {
+            // (filter and window part by part: the window first, as above, made the
+            // 64-patch loop wait more, event 6.11 -> 6.47 ms)
             uint4 win[kParts3], f[kParts3];
-            read_win(base, i, win);
 #pragma unroll
-            for (int k = 0; k < kParts3; ++k) f[k] = filters[(k * 6 + ta) * 64 + lane];
+            for (int k = 0; k < kParts3; ++k) {
+              f[k] = filters[(k * 6 + ta) * 64 + lane];
+              win[k] = read_win(base, i, k);
+            }
             const floatx4 z = {0.f, 0.f, 0.f, 0.f};
             const floatx4 ca = mfma6(f, win, z);
 #pragma unroll
             for (int k = 0; k < kParts3; ++k) f[k] = filters[(k * 6 + tb) * 64 + lane];
-            split_maps(ca, mfma6(f, win, z), b[i]);
+            const floatx4 cb = mfma6(f, win, z);
+            split_maps(ca, cb, b[i]);
           }
         }
         __builtin_amdgcn_sched_barrier(0);
