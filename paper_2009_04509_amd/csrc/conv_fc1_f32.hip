@@ -42,8 +42,9 @@
 // Range.  A finite pixel that could take a conv sum past a quarter of fp32's
 // range, an infinite one or a NaN (ConvF32::limit: none of them occurs in charge
 // images), and FC1 sums that are not finite, have no place in three parts: the
-// block computes the sums of such a patch again in plain fp32, product by product,
-// so that infinities, NaNs and overflows come out as fp32 arithmetic gives them.
+// block computes the sums of such a patch (for sums, those of their 16 outputs) again
+// in plain fp32, product by product, so that infinities, NaNs and overflows come out as
+// fp32 arithmetic gives them, whatever the shape of the block.
 #include <algorithm>
 #include <cmath>
 
@@ -81,8 +82,8 @@ struct ConvF32 {
 };
 
 // Block of 16 kTiles patches and 128 / kParts outputs.  LDS (dwords): ring
-// [part][row][patch] | conv filters | row descriptors | flags of patches to
-// compute in plain fp32; the reduction reuses it up to the descriptors.
+// [part][row][patch] | conv filters | row descriptors | per patch the 16-output
+// tiles to compute in plain fp32, a bit each; the reduction reuses it up to the descriptors.
 template <int kTiles, int kParts>
 struct Block {
   static constexpr int kBt = 16 * kTiles;
@@ -144,7 +145,7 @@ __device__ __forceinline__ void mfma6x2(const uint4 (&a)[kParts3], const uint4 (
 }
 
 // The FC1 sums of one patch (row descriptor d) over pairs P0 .. P_end - 1 in
-// plain fp32, by the whole block, to dst[128] for the outputs of [o_lo, o_hi).
+// plain fp32, by the whole block, to dst[128] for the 16-output tiles of `tiles`.
 // The window of a pair has six columns, the taps of the one that a position does
 // not use are 0, as in the MFMA kernels: an infinite or NaN pixel makes the maps
 // of both positions NaN, which the ReLU takes to 0.  0.15 ms a patch and
@@ -152,7 +153,7 @@ __device__ __forceinline__ void mfma6x2(const uint4 (&a)[kParts3], const uint4 (
 constexpr int kPlainPairs = 4;                // pairs of a pass, one per 128 threads
 constexpr int kPlainRows = 11;                // input rows of a range of at most 31 groups of 4 pairs
 static_assert((4 * ((kPairs / 4 + kSplits - 1) / kSplits) - 1 + kPairsPerRow - 1) / kPairsPerRow + kK <= kPlainRows, "rows");
-__device__ __forceinline__ void plain_patch(float* lds, const uint4& d, int P0, int P_end, int o_lo, int o_hi,
+__device__ __forceinline__ void plain_patch(float* lds, const uint4& d, int P0, int P_end, uint32_t tiles,
                                             const uint4* __restrict__ w1p, const ConvF32& conv, float* dst) {
   typedef __attribute__((address_space(1))) const float* gptr;
   static_assert(kPlainPairs * 128 == kThreads && kPlainPairs * 2 * kCh <= kThreads, "threads of a pass");
@@ -165,6 +166,7 @@ __device__ __forceinline__ void plain_patch(float* lds, const uint4& d, int P0, 
     lds[i] = in ? ((gptr)row_chunk_addr(d, (int)r, 0))[c] : 0.f;
   }
   const int o = tid & 127, g = tid >> 7;
+  const bool mine = (tiles >> (o / 16) & 1u) != 0;
   float acc = 0.f;
   for (int P = P0; P < P_end; P += kPlainPairs) {
     __syncthreads();
@@ -179,7 +181,7 @@ __device__ __forceinline__ void plain_patch(float* lds, const uint4& d, int P0, 
       lds[kMaps + tid] = fmaxf(m + conv.b[ch], 0.f);
     }
     __syncthreads();
-    if (o >= o_lo && o < o_hi) {
+    if (mine) {
       // the weights from their parts (an exact sum), in the order of pack_fc1_f32_kernel
       float sum = 0.f;
       for (int k = 0; k < kQ * 4; ++k) {
@@ -205,7 +207,7 @@ __device__ __forceinline__ void plain_patch(float* lds, const uint4& d, int P0, 
   __syncthreads();
   lds[kSums + tid] = acc;
   __syncthreads();
-  if (tid < 128 && o >= o_lo && o < o_hi)
+  if (tid < 128 && mine)
     dst[o] = (lds[kSums + tid] + lds[kSums + 128 + tid]) + (lds[kSums + 256 + tid] + lds[kSums + 384 + tid]);
 }
 
@@ -244,7 +246,7 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
 
   // ---- patch rows
   uint4* desc = reinterpret_cast<uint4*>(lds + B::kDescOff);
-  uint32_t* flags = lds + B::kFlagOff;       // patches to compute in plain fp32
+  uint32_t* flags = lds + B::kFlagOff;       // what to compute in plain fp32
   if (tid < kBt) {
     desc[tid] = src.get(p_base + tid);
     flags[tid] = 0;
@@ -279,7 +281,7 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
         bool fits = true;
 #pragma unroll
         for (int j = 0; j < 4; ++j) fits &= fabsf(x[j]) < conv.limit;
-        if (!fits) flags[p] = 1;
+        if (!fits) flags[p] = ~0u;
         uint2 hi, mi, lo;
         split3(x[0], x[1], hi.x, mi.x, lo.x);
         split3(x[2], x[3], hi.y, mi.y, lo.y);
@@ -463,7 +465,7 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
         const floatx4 sum = ((v[0] + v[4]) + (v[1] + v[5])) + ((v[2] + v[6]) + (v[3] + v[7]));
         const int p = 16 * (q % kTiles) + col, out = 16 * (opart * kMT + q / kTiles) + 4 * grp;
         const floatx4 z = sum * 0.f;
-        if (!((z[0] + z[1]) + (z[2] + z[3]) == 0.f)) flags[p] = 1;   // not finite
+        if (!((z[0] + z[1]) + (z[2] + z[3]) == 0.f)) atomicOr(&flags[p], 1u << out / 16);   // not finite
         if (p_base + p < src.n) __builtin_nontemporal_store(sum, reinterpret_cast<floatx4*>(dst + p * kFc1Out + out));
       }
     }
@@ -476,8 +478,8 @@ __device__ __forceinline__ void conv_fc1_f32_block(uint32_t* lds, int split, int
   while (todo) {                             // the same in every wave
     const int p = __ffsll((unsigned long long)todo) - 1;
     todo &= todo - 1;
-    plain_patch(reinterpret_cast<float*>(lds), desc_from_lds(desc + p), P0, P_end, opart * kMT * 16,
-                (opart + 1) * kMT * 16, w1p, conv, dst + p * kFc1Out);
+    plain_patch(reinterpret_cast<float*>(lds), desc_from_lds(desc + p), P0, P_end,
+                flags[p] & ((1u << kMT) - 1) << opart * kMT, w1p, conv, dst + p * kFc1Out);
   }
 }
 

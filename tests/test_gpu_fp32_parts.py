@@ -168,6 +168,20 @@ def test_weights_out_of_range(pid, where, value):
         assert np.nanmax(np.abs(got - want), initial=0) <= 1e-4
 
 
+def test_overflown_sums_in_every_block_shape(pid):
+    """FC1 sums of two outputs overflow to minus infinity (0 behind the ReLU): the
+    others keep their bits, whichever outputs share a block."""
+    w = {k: np.array(v) for k, v in synth.he_normal_weights().items()}
+    w["fc1_w"][5000::9000, 5] = -3.0e38
+    w["fc1_w"][100::9000, 90] = -3.0e38
+    P = (synth.config4_patches(1100, seed=4) * 20).astype(F)
+    full = classify(pid, w, P)
+    want = network(w, P[:20])
+    assert np.isfinite(full).all() and np.abs(full[:20] - want).max() <= 1e-4
+    for n in (1, 20, 200, 400, 700):
+        assert np.array_equal(classify(pid, w, P[:n]).view(np.uint32), full[:n].view(np.uint32)), n
+
+
 @pytest.mark.parametrize("value", [3.0e38, 1e30, 1e-30, 2.0**-100])
 def test_scale_of_one_pixel(pid, value):
     """Patches of one pixel each, filters scaled to it: the scores rest on the pixel's parts alone."""
